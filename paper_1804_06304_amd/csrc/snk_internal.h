@@ -181,6 +181,13 @@ hipError_t launch_pack_pair(const float *J, float2 *Jp, int nx, int ny, int nz, 
 // (whole-wave groups, Monte-Carlo sums) stages each contour's ball in an LDS box of that many voxels.
 hipError_t launch_evolve(const EvolveArgs &a, int dim, int lanes, int unroll, int layout, bool trace,
                          hipStream_t s);
+// The kernels launch_evolve dispatches to, one translation unit each (they compile in parallel).
+hipError_t launch_evolve_mc2(const EvolveArgs &a, int lanes, int unroll, int layout, bool trace, hipStream_t s);
+hipError_t launch_evolve_mc3(const EvolveArgs &a, int lanes, int unroll, int layout, bool trace, hipStream_t s);
+hipError_t launch_evolve_gradi(const EvolveArgs &a, int dim, int lanes, int layout, bool trace, hipStream_t s);
+hipError_t launch_evolve_exact(const EvolveArgs &a, int dim, int lanes, int layout, bool trace, hipStream_t s);
+int evolve_stage_blocks2(int lanes, int unroll, int layout);
+int evolve_stage_blocks3(int lanes, int unroll, int layout);
 // a.tile_cap > 0: each workgroup stages its contour's ball in an LDS box of that many voxels.
 hipError_t launch_evolve_batch(const BatchArgs &a, int dim, int lanes, int unroll, int layout, bool persistent,
                                int grid, hipStream_t s);
