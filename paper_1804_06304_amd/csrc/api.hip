@@ -380,9 +380,9 @@ struct McShape {
 // and there are more than four of them per CU (the common case of one volume with a few thousand
 // cells: their footprints overflow the L2, which a handful of contours per CU do not, where
 // staging only adds latency): two waves per contour when a contour has at least four pair-points
-// per lane of them, else one (unless set), four pair-points in flight with two waves (two if that
-// would leave contours waiting, or with one wave), and the largest box whose LDS still leaves room
-// for all of them. Otherwise no box and the lane rule of pick_lanes.
+// per lane of them, else one (unless set), two pair-points in flight (slab evolve 2.34 ms; four, which
+// need 128 registers and spill, 2.80), and the largest box whose LDS still leaves room for all of them.
+// Otherwise no box and the lane rule of pick_lanes.
 McShape mc_shape(snk_ctx *c, int M, int layout) {
     McShape s;
     s.lanes = pick_lanes(c);
@@ -400,19 +400,13 @@ McShape mc_shape(snk_ctx *c, int M, int layout) {
     if (per_cu <= 4) return s;
     const int G = c->lanes > 0 ? c->lanes : (pairs >= 512 ? 128 : (pairs >= 128 ? 64 : 0));
     if (G < 64) return s;
-    // two-wave groups with at least four pair-points per lane take all four in one pass when the
-    // contours still fit at that register count
-    int U = c->unroll > 0 ? c->unroll : ((G == 128 && pairs >= 4 * G) ? 4 : 2);
-    for (;;) {
-        const int key = ((c->P.dim * 512 + G) * 8 + U) * 4 + layout;
-        if (key != c->stage_key) {
-            c->stage_blocks = snk::evolve_stage_blocks_per_cu(c->P.dim, G, U, layout);
-            c->stage_key = key;
-        }
-        if (per_cu <= c->stage_blocks) break;
-        if (c->unroll > 0 || U == 2) return s;
-        U = 2;
+    const int U = c->unroll > 0 ? c->unroll : 2;
+    const int key = ((c->P.dim * 512 + G) * 8 + U) * 4 + layout;
+    if (key != c->stage_key) {
+        c->stage_blocks = snk::evolve_stage_blocks_per_cu(c->P.dim, G, U, layout);
+        c->stage_key = key;
     }
+    if (per_cu > c->stage_blocks) return s;
     const size_t other = snk::evolve_lds_bytes(c->P.dim, G, M, 0);
     // LDS is handed out in 512-byte blocks
     const size_t budget = std::min<size_t>((size_t)c->lds_per_cu / (size_t)per_cu, 65536) & ~(size_t)511;
@@ -699,9 +693,9 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
         a.nb_cap = kNbCap;
         a.kappa = (float)c->repel_kappa;
     }
-    if (snk::evolve_lds_bytes(c->P.dim, lanes, a.p.M, 0) > 65536)
+    if (!snk::evolve_lds_accepts(c->P.dim, lanes, a.p.M, 0))
         return fail(c, SNK_EINVAL, "n_rays too large for the evolve kernel's LDS (64 KiB per workgroup)");
-    if (snk::evolve_lds_bytes(c->P.dim, lanes, a.p.M, a.tile_cap) > 65536)
+    if (!snk::evolve_lds_accepts(c->P.dim, lanes, a.p.M, a.tile_cap))
         return fail(c, SNK_EINVAL, "LDS box too large (the evolve kernel's LDS is 64 KiB per workgroup)");
     if (standalone) {
         HIPTRY(c, hipMemsetAsync(c->d_counters, 0, sizeof(unsigned long long), c->stream));

@@ -500,6 +500,7 @@ snk::BatchArgs batch_args(snk_engine *e, const ClassKey &k, int b, int end, int 
     a.counter = e->d_counters;
     a.max_D = k.D;
     a.max_M = k.M;
+    a.L = k.L;
     return a;
 }
 
@@ -515,7 +516,7 @@ snk_status launch_classes(snk_engine *e, const ItemPlan &pl, int chunk, const st
         const ClassKey &k = pl.classes[c].first;
         const int b = pl.classes[c].second.first, end = pl.classes[c].second.second;
         const Launch &L = shapes[c];
-        if (snk::evolve_lds_bytes(k.dim, L.lanes, k.M, L.tile) > 65536)
+        if (!snk::evolve_lds_accepts(k.dim, L.lanes, k.M, L.tile))
             return efail(e, SNK_EINVAL, "n_rays too large for this launch shape's LDS");
         snk::BatchArgs a = batch_args(e, k, b, end, (int)c, chunk, L.tile);
         EHIP(e, snk::launch_evolve_batch(a, k.dim, L.lanes, L.unroll, e->layout, L.persistent != 0, L.grid,
@@ -549,7 +550,7 @@ snk_status shapes_for(snk_engine *e, const ItemPlan &pl, bool allow_trials, std:
             for (int g : {64, 128, 256}) {
                 for (int u : {1, 2}) {
                     for (int tile : {0, 2048, 4224, 8192}) {
-                        if (snk::evolve_lds_bytes(k.dim, g, k.M, tile) > 65536) continue;
+                        if (!snk::evolve_lds_accepts(k.dim, g, k.M, tile)) continue;
                         const int max_cu = snk::evolve_batch_max_blocks(k.dim, g, u, e->layout, k.M, tile);
                         // -1: one workgroup per item; 0: persistent, all it can hold; else that many
                         int cands[3] = {-1, 0, 0};

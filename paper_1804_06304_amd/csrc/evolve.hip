@@ -27,11 +27,16 @@ int evolve_stage_blocks_per_cu(int dim, int lanes, int unroll, int layout) {
 
 size_t evolve_lds_bytes(int dim, int lanes, int M, int tile_cap) {
     const int MH = M / 2;
-    const int G = lanes;
-    const int per = (draw_floats(G, MH) + 3) & ~3;
-    const int cpb = G < 64 ? 64 / G : 1;
-    const int waves = G > 64 ? G / 64 : 1;
-    return sizeof(float) * ((size_t)cpb * per + (G > 64 ? 2 * (2 + dim) * waves : 0) + (size_t)tile_cap);
+    if (lanes < 64) return sizeof(float) * (size_t)(64 / lanes * ((draw_floats(lanes, MH) + 3) & ~3));
+    const DrawPlan d = draw_plan(dim, MH);
+    return wave_lds_bytes(lanes, wave_draw_floats(dim, d.K, d.KR, MH), tile_cap);
+}
+
+bool evolve_lds_accepts(int dim, int lanes, int M, int tile_cap) {
+    const int per = (draw_floats(lanes, M / 2) + 3) & ~3;
+    const int cpb = lanes < 64 ? 64 / lanes : 1;
+    const int waves = lanes > 64 ? lanes / 64 : 1;
+    return sizeof(float) * ((size_t)cpb * per + (lanes > 64 ? 2 * (2 + dim) * waves : 0) + (size_t)tile_cap) <= 65536;
 }
 
 }  // namespace snk

@@ -9,12 +9,12 @@ namespace {
 // fixed grid pops items from a device work queue until it is exhausted (every workgroup reaches
 // the exit); otherwise one workgroup per item. STAGE: the workgroup's LDS ends with a box of
 // a.tile_cap voxels for the contour it is running (restaged for each item).
-template <int DIM, int G, int U, int LAYOUT, bool PERSISTENT, bool STAGE>
-__global__ __launch_bounds__(G, U == 1 ? 8 : 1) void evolve_batch_kernel(BatchArgs a) {
+// FULL: L = 16 and whole passes (full_passes).
+template <int DIM, int G, int U, int LAYOUT, bool PERSISTENT, bool STAGE, bool FULL>
+__global__ __launch_bounds__(G, (waves_asked<DIM, G, U, STAGE, false, FULL>())) void evolve_batch_kernel(BatchArgs a) {
     static_assert(G >= 64, "batched groups span whole waves");
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ int item_sh;
-    const int per = (draw_floats(G, a.max_M / 2) + 3) & ~3;
     for (int round = 0;; ++round) {
         int item;
         if constexpr (PERSISTENT) {
@@ -31,19 +31,28 @@ __global__ __launch_bounds__(G, U == 1 ? 8 : 1) void evolve_batch_kernel(BatchAr
         const JobParams p = uniform_copy(&a.jobs[job].p);
         DevContour *st = uniform_copy(&a.jobs[job].st);
         const int target = __builtin_amdgcn_readfirstlane(a.jobs[job].target);
-        run_group<DIM, G, U, false, LAYOUT, false, STAGE>(p, st + cid, a.chunk, target, nullptr, lds, lds + per,
-                                                         a.counter, lds + lds_floats<DIM, G>(a.max_M / 2),
-                                                         STAGE ? a.tile_cap : 0);
+        run_wave<DIM, G, U, false, LAYOUT, false, STAGE, false, FULL>(
+            p, (Cold<JobParams>)&a.jobs[job].p, st + cid, a.chunk, target, nullptr, lds, a.draw_k, a.rot_k, a.counter,
+            STAGE ? a.tile_cap : 0, Repel{nullptr, 0, -1});
         __syncthreads();
     }
 }
 
 template <int DIM, int G, int U, int LAYOUT, bool PERSISTENT, bool STAGE>
-hipError_t batch_t(const BatchArgs &a, int grid, hipStream_t s) {
-    const size_t lds = sizeof(float) * ((size_t)lds_floats<DIM, G>(a.max_M / 2) + (STAGE ? (size_t)a.tile_cap : 0));
+hipError_t batch_t(BatchArgs a, int grid, hipStream_t s) {
     const int g = PERSISTENT ? grid : a.n_items;
     if (g <= 0) return hipSuccess;
-    hipLaunchKernelGGL((evolve_batch_kernel<DIM, G, U, LAYOUT, PERSISTENT, STAGE>), dim3(g), dim3(G), lds, s, a);
+    const DrawPlan d = draw_plan(DIM, a.max_M / 2);
+    a.draw_k = d.K;
+    a.rot_k = d.KR;
+    const size_t lds = wave_lds_bytes(G, wave_draw_floats(DIM, d.K, d.KR, a.max_M / 2), STAGE ? a.tile_cap : 0);
+    if constexpr (U >= 2)
+        if (full_passes(G, U, a.max_M, a.L)) {
+            hipLaunchKernelGGL((evolve_batch_kernel<DIM, G, U, LAYOUT, PERSISTENT, STAGE, true>), dim3(g), dim3(G), lds,
+                               s, a);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((evolve_batch_kernel<DIM, G, U, LAYOUT, PERSISTENT, STAGE, false>), dim3(g), dim3(G), lds, s, a);
     return hipGetLastError();
 }
 
@@ -81,12 +90,13 @@ hipError_t batch_g(const BatchArgs &a, int lanes, int unroll, int layout, bool p
     }
 }
 
+// Workgroups per CU of the general instance (a FULL one needs no more registers).
 template <int DIM, int G, int U, int LAYOUT, bool STAGE>
 int max_blocks_t(int max_M, int tile_cap) {
     int blocks = 0;
-    const size_t lds = sizeof(float) * ((size_t)lds_floats<DIM, G>(max_M / 2) + (STAGE ? (size_t)tile_cap : 0));
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, evolve_batch_kernel<DIM, G, U, LAYOUT, true, STAGE>, G,
-                                                     lds) != hipSuccess)
+    const size_t lds = evolve_lds_bytes(DIM, G, max_M, STAGE ? tile_cap : 0);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &blocks, evolve_batch_kernel<DIM, G, U, LAYOUT, true, STAGE, false>, G, lds) != hipSuccess)
         return 1;
     return blocks > 0 ? blocks : 1;
 }

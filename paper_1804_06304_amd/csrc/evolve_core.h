@@ -24,7 +24,8 @@
 //      dE/dR = (B_R - (d/R) A)/(2R)^d, dE/dc = B_c/(2R)^d, eps = eps0/sqrt(n),
 //      dR = -(eps/2) dE/dR, dc = -(eps/2) dE/dc (the p,q steps of Eqs. (12)-(15) mapped through
 //      c = (p+q)/2, R = (q_x - p_x)/2), clamps R, re-anchors c, and tests OUT / convergence.
-// Every lane of a group runs the identical update, so the state stays in registers.
+// Sub-wave groups (run_group) hold the state in every lane; whole-wave groups (run_wave) step the axes of
+// the centre in lanes of their own.
 //
 // Volume layouts: plain FP32 [z][y][x] (2^d/2 eight-byte pair loads per point), or "quad": one
 // 16-byte record per voxel holding J(x,y), J(x+1,y), J(x,y+1), J(x+1,y+1) of its plane (one 16-byte
@@ -48,24 +49,28 @@ constexpr uint32_t kBufferWord3 = 0x00020000u;  // raw buffer descriptor, gfx9 f
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// The rounds stay a loop: unrolled, the compiler keeps all twenty round keys in scalar registers for
-// the whole kernel and spills other uniform values to make room.
+// The rounds stay a loop of two rounds: fully unrolled, the compiler keeps all twenty round keys in scalar
+// registers for the whole kernel and spills other uniform values to make room; one round per step costs
+// two register moves a round (the words change places).
 __device__ __forceinline__ void philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                          uint32_t k1, uint32_t out[4]) {
 #pragma unroll 1
-    for (int r = 0; r < 10; ++r) {
-        // one 32 x 32 -> 64-bit product gives both halves
-        const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
-        const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-        const uint32_t n0 = hi1 ^ c1 ^ k0;
-        const uint32_t n2 = hi0 ^ c3 ^ k1;
-        c0 = n0;
-        c1 = lo1;
-        c2 = n2;
-        c3 = lo0;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
+    for (int r = 0; r < 5; ++r) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            // one 32 x 32 -> 64-bit product gives both halves
+            const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+            const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+            const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
+            const uint32_t n0 = hi1 ^ c1 ^ k0;
+            const uint32_t n2 = hi0 ^ c3 ^ k1;
+            c0 = n0;
+            c1 = lo1;
+            c2 = n2;
+            c3 = lo0;
+            k0 += 0x9E3779B9u;
+            k1 += 0xBB67AE85u;
+        }
     }
     out[0] = c0;
     out[1] = c1;
@@ -181,8 +186,9 @@ __device__ __forceinline__ void divmod_small(int j, int d, float inv_d, int &q, 
 }
 
 // Phase 1 of block b: the Philox draws of its K iterations (n_first .. n_first + K - 1), one per
-// lane: pair draws -> table row k (parked in pu.x) and xi; rotation draws -> Q.
-template <int DIM, int G>
+// lane: pair draws -> table row k (parked in pu.x) and xi; rotation draws -> Q (ROT = false: none, for
+// directions that stay fixed).
+template <int DIM, int G, bool ROT = true>
 __device__ __forceinline__ void draws_phase1(const Draws &d, int buf, uint32_t n_first, uint32_t id,
                                              const JobParams &p, int gl) {
     const int per = d.MH + 1;
@@ -198,7 +204,7 @@ __device__ __forceinline__ void draws_phase1(const Draws &d, int buf, uint32_t n
         if (pair) {
             d.pu[sl * d.MH + r].x = __int_as_float((int)__umulhi(x[0], (uint32_t)p.D));
             d.pu[sl * d.MH + r].w = unit_open(x[1]);
-        } else {
+        } else if constexpr (ROT) {
             float Q[9];
             if (p.flags & 1) {
 #pragma unroll
@@ -240,6 +246,122 @@ __device__ __forceinline__ void draws_phase2(const Draws &d, int buf, const JobP
         o.z = DIM == 3 ? u[2] : 0.0f;
     }
 }
+
+// A record in constant memory (the kernel's arguments, or a table no kernel of the launch writes) read where
+// it is needed: the compiler would load every field before the loop and, out of scalar registers, spill them
+// to lanes of a vector register; through a pointer it cannot see through, a field is one scalar load at
+// its use. For what an iteration seldom needs.
+template <typename T>
+using Cold = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ Cold<T> cold(Cold<T> p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Draw buffers of a whole-wave group: pairs pu[m] = (u_x/h_x, u_y/h_y, u_z/h_z, xi) of two blocks of K
+// iterations (the one in use and the next), and the rotations of KR iterations (a multiple of K).
+//   - Pairs: 64 draws are one wave's pass. A block's passes go to the group's waves in turn, starting with
+//     another wave each block, so a block of one pass (K MH <= 64) costs each wave a pass every WAVES
+//     blocks. The host picks K (draw_plan) so that the passes are nearly full.
+//   - Rotations: one lane draws an iteration's, so a pass gives KR of them; apart from the pairs' passes
+//     because a pass that holds even one rotation runs its whole code (about 150 instructions in 3D),
+//     which with both in the same pass was a third of the draws' cost.
+// Schedule within iteration it = b K + sl: at sl = 0 each wave's first pass of block b + 1 draws and fetches
+// its table rows after the iteration's gathers (whose registers are free then) and applies the rotation
+// at its end, so the fetch's latency hides behind the reduction and the step; at the end of sl = K - 1 a
+// wave draws the next KR rotations when block b + 2 is their first. Both ends lie behind the iteration's
+// reduction barrier, so with K >= 2 every value is written at least one barrier before another wave reads
+// it, and after the last read of what it overwrites.
+template <int DIM>
+constexpr int rot_floats() {
+    return DIM == 3 ? 9 : 2;
+}
+
+template <int DIM, int G>
+struct WaveDraws {
+    static constexpr int WAVES = G / 64;
+    float4 *pu;
+    float *rot;
+    int K, KR, MH, T, passes;
+    float inv_mh;
+    __device__ __forceinline__ WaveDraws(float *base, int K_, int KR_, int MH_) {
+        K = K_;
+        KR = KR_;
+        MH = MH_;
+        T = K * MH;
+        passes = (T + 63) >> 6;
+        inv_mh = 1.0f / (float)MH;
+        pu = reinterpret_cast<float4 *>(base);
+        rot = base + 8 * T;
+    }
+    // rotations of iterations n_first .. n_first + KR - 1, one per lane of the calling wave
+    __device__ __forceinline__ void rotations(uint32_t n_first, uint32_t id, Cold<JobParams> cp, int lane) const {
+        const Cold<JobParams> p = cold(cp);
+        for (int s = lane; s < KR; s += 64) {
+            float Q[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f};
+            if (!(p->flags & 1)) {
+                uint32_t x[4];
+                philox10(0u, n_first + (uint32_t)s, id, 0u, p->key0, p->key1, x);
+                rotation_from<DIM>(x, Q);
+            }
+            float *o = rot + s * rot_floats<DIM>();
+            if constexpr (DIM == 3) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) o[i] = Q[i];
+            } else {
+                o[0] = Q[0];   // cos
+                o[1] = Q[3];   // sin
+            }
+        }
+    }
+    // one pair's draw: its place, table row (not yet rotated) and jitter
+    struct Pending {
+        float t[3], xi;
+        int s, m;
+        bool on;
+    };
+    __device__ __forceinline__ Pending begin(int r, uint32_t n_first, uint32_t id, Cold<JobParams> cp, int lane) const {
+        const Cold<JobParams> p = cold(cp);
+        Pending d;
+        const int j = r * 64 + lane;
+        d.on = j < T;
+        divmod_small(d.on ? j : 0, MH, inv_mh, d.s, d.m);
+        uint32_t x[4];
+        philox10((uint32_t)d.m, n_first + (uint32_t)d.s, id, 1u, p->key0, p->key1, x);
+        const int k = (int)__umulhi(x[0], (uint32_t)p->D);
+        d.xi = unit_open(x[1]);
+        d.t[0] = d.t[1] = d.t[2] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < DIM; ++i) d.t[i] = p->dirs[k * DIM + i];
+        return d;
+    }
+    // u = Q t / h of the block's iteration s, whose rotation is entry rot0 + s
+    __device__ __forceinline__ void finish(const Pending &d, int buf, int rot0, Cold<JobParams> cp) const {
+        if (!d.on) return;
+        const Cold<JobParams> p = cold(cp);
+        const float *q = rot + (rot0 + d.s) * rot_floats<DIM>();
+        float Q[9];
+        if constexpr (DIM == 3) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) Q[i] = q[i];
+        } else {
+            Q[0] = q[0];
+            Q[1] = -q[1];
+            Q[3] = q[1];
+            Q[4] = q[0];
+        }
+        float u[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < DIM; ++i) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int jj = 0; jj < DIM; ++jj) acc = fmaf(Q[i * 3 + jj], d.t[jj], acc);
+            u[i] = acc * p->g.inv_h[i];
+        }
+        pu[(buf * K + d.s) * MH + d.m] = make_float4(u[0], u[1], u[2], d.xi);
+    }
+};
 
 // ---------------------------------------------------------------------------------------------
 // Reductions (fixed order; every lane of a group ends with identical totals)
@@ -291,17 +413,18 @@ __device__ __forceinline__ float cross_row_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);            // even row + odd row of the half
 }
 
-// Totals over the 64 lanes of a wave of NR = 4 or 5 per-lane values, in scalar registers. Values 0..3
-// are reduced together: lanes exchange values so that after two quad steps each lane holds the
-// quad's sum of one value, j = 2 (lane & 1) + ((lane >> 1) & 1); the row and cross-row steps then
-// add the copies of that value (the same value sits in lanes i, i + 4, i + 8, ...). A fifth value
-// takes the same row and cross-row steps on its own. The order of every addition is fixed, so the
-// totals do not depend on timing.
+// Totals over the 64 lanes of a wave of NR = 4 or 5 per-lane values. Values 0..3 are reduced together:
+// lanes exchange values so that after two quad steps each lane holds the quad's sum of one value,
+// j = 2 (lane & 1) + ((lane >> 1) & 1); the row and cross-row steps then add the copies of that value
+// (the same value sits in lanes i, i + 4, i + 8, ...). A fifth value takes the same steps on its own.
+// Every value is added over the same tree whatever its place, and the order of every addition is fixed,
+// so the totals do not depend on timing. On return x holds, in lane i, the total of value 0, 2, 1, 3 for
+// i & 3 = 0, 1, 2, 3, and z in every lane that of value 4.
 template <int NR>
-__device__ __forceinline__ void wave_sums(const float *v, float *tot) {
+__device__ __forceinline__ void wave_quads(const float *v, float &x, float &z) {
     static_assert(NR == 4 || NR == 5, "four or five sums");
-    const int lane = __lane_id();
-    const bool b0 = (lane & 1) != 0, b1 = (lane & 2) != 0;
+    const bool b0 = __builtin_amdgcn_inverse_ballot_w64(0xAAAAAAAAAAAAAAAAull);
+    const bool b1 = __builtin_amdgcn_inverse_ballot_w64(0xCCCCCCCCCCCCCCCCull);
     // lane pairs (2i, 2i + 1): the even lane keeps values 0 and 1, the odd one 2 and 3
     const float k0 = b0 ? v[2] : v[0], k1 = b0 ? v[3] : v[1];
     const float s0 = b0 ? v[0] : v[2], s1 = b0 ? v[1] : v[3];
@@ -309,8 +432,8 @@ __device__ __forceinline__ void wave_sums(const float *v, float *tot) {
     const float w1 = k1 + dpp<0xB1>(s1);
     // lanes i and i ^ 2: keep w_b1, add the partner's copy of the same value
     const float keep = b1 ? w1 : w0, send = b1 ? w0 : w1;
-    float x = keep + dpp<0x4E>(send);     // quad_perm [2, 3, 0, 1]
-    float z = 0.0f;
+    x = keep + dpp<0x4E>(send);           // quad_perm [2, 3, 0, 1]
+    z = 0.0f;
     if constexpr (NR == 5) {
         z = v[4] + dpp<0xB1>(v[4]);
         z = z + dpp<0x4E>(z);
@@ -322,27 +445,21 @@ __device__ __forceinline__ void wave_sums(const float *v, float *tot) {
         z += dpp<0x124>(z);
     }
     x = cross_row_sum(x);
-    // value j's total sits in lane 0 (j = 0), 2 (j = 1), 1 (j = 2), 3 (j = 3)
-    tot[0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0));
-    tot[1] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 2));
-    tot[2] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 1));
-    tot[3] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 3));
-    if constexpr (NR == 5) {
-        z = cross_row_sum(z);
-        tot[4] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(z)));
-    }
+    if constexpr (NR == 5) z = cross_row_sum(z);
 }
 
+// Sum over a sub-wave group of 16 or 32 lanes.
 template <int G>
-__device__ __forceinline__ float group_sum_wave(float v) {
-    if constexpr (G == 16) {
-        return row_sum16(v);
-    } else if constexpr (G == 32) {
-        v = row_sum16(v);
-        return v + __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x401F));  // lane ^ 16
-    } else {
-        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to_63(v)), 63));
-    }
+__device__ __forceinline__ float group_sum(float v) {
+    v = row_sum16(v);
+    if constexpr (G == 32)
+        v += __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), 0x401F));  // lane ^ 16
+    return v;
+}
+
+// Sum over a wave, in every lane.
+__device__ __forceinline__ float wave_sum(float v) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_sum_to_63(v)), 63));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -365,13 +482,9 @@ struct Vol {
     static constexpr bool kSmall = LAYOUT != kGlobalPlain;  // 24-bit index arithmetic
     const float *J;
     __amdgpu_buffer_rsrc_t rsrc;
-    int n[3];
     int nx, nxy;
     int so1, so2, so3;  // byte offsets of the neighbour loads (buffer layouts)
     __device__ __forceinline__ Vol(const Geometry &g) {
-        n[0] = g.nx;
-        n[1] = g.ny;
-        n[2] = g.nz;
         nx = g.nx;
         nxy = g.nx * g.ny;
         J = g.J;
@@ -402,11 +515,11 @@ struct Vol {
             return J[idx];
         }
     }
-    // Loads the corners of the cell whose lower corner has linear voxel index `idx` (< 2^31 for
-    // the buffer layouts).
-    __device__ __forceinline__ void load(long idx, Corners<DIM> &c) const {
+    // Loads the corners of the cell whose lower corner has linear voxel index base + rel (< 2^31 for
+    // the buffer layouts; base uniform, so its byte offset stays in a scalar register).
+    __device__ __forceinline__ void load(long rel, long base, Corners<DIM> &c) const {
         if constexpr (LAYOUT == kBufferQuad) {
-            const int vo = (int)idx * 16;
+            const int vo = (int)rel * 16 + (int)base * 16;
             const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo, 0, 0);
             c.v[0] = __uint_as_float(a.x);
             c.v[1] = __uint_as_float(a.y);
@@ -421,7 +534,7 @@ struct Vol {
             }
         } else if constexpr (LAYOUT == kBufferPair) {
             // (J(x,y), J(x,y+1)) then (J(x+1,y), J(x+1,y+1)), of plane z and then of plane z+1
-            const int vo = (int)idx * 8;
+            const int vo = (int)rel * 8 + (int)base * 8;
             const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(rsrc, vo, 0, 0);
             c.v[0] = __uint_as_float(a.x);
             c.v[2] = __uint_as_float(a.y);
@@ -435,7 +548,7 @@ struct Vol {
                 c.v[7] = __uint_as_float(b.w);
             }
         } else if constexpr (LAYOUT == kBufferPlain) {
-            const int vo = (int)idx * 4;
+            const int vo = (int)rel * 4 + (int)base * 4;
             const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(rsrc, vo, 0, 0);
             const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(rsrc, vo, so1, 0);
             c.v[0] = __uint_as_float(a.x);
@@ -451,7 +564,7 @@ struct Vol {
                 c.v[7] = __uint_as_float(f.y);
             }
         } else {
-            const float *q = J + idx;
+            const float *q = J + (base + rel);
             const Pair a = *reinterpret_cast<const Pair *>(q);
             const Pair b = *reinterpret_cast<const Pair *>(q + nx);
             c.v[0] = a.lo;
@@ -476,10 +589,9 @@ template <int DIM>
 struct TileVol {
     static constexpr bool kSmall = true;
     const float *t;
-    int n[3];
     int nx, nxy;
-    __device__ __forceinline__ void load(long idx, Corners<DIM> &c) const {
-        const float *q = t + (int)idx;
+    __device__ __forceinline__ void load(long rel, long base, Corners<DIM> &c) const {
+        const float *q = t + ((int)base + (int)rel);
         c.v[0] = q[0];
         c.v[1] = q[1];
         c.v[2] = q[nx];
@@ -561,13 +673,14 @@ __device__ __forceinline__ int floor_to_int(float x) {
     return i;
 }
 
-// Point x = anchor + off + rad * du (voxel units) -> corner index and fractions. CLAMP = false is
-// used only when every sample of the iteration is known to lie inside, where both agree. SMALL: the
-// row and plane strides fit 24-bit multiplies (buffer layouts).
+// Point x = anchor + off + rad * du (voxel units) -> corner index, relative to the anchor voxel
+// (CLAMP: to voxel 0), and fractions. CLAMP = false is used only when every sample of the iteration is
+// known to lie inside, where both agree. SMALL: the row and plane strides fit 24-bit multiplies
+// (buffer layouts).
 // out (CLAMP only, may be null): per axis 0.0 where the coordinate lies beyond the volume's faces
 // (the clamped interpolant is flat there), else 1.0; the last face itself counts as inside.
 template <int DIM, bool CLAMP, bool SMALL>
-__device__ __forceinline__ long locate(const Frame<DIM> &fr, const int n[3], int nx, int nxy, const float w[3],
+__device__ __forceinline__ long locate(const Frame<DIM> &fr, const int *n, int nx, int nxy, const float w[3],
                                        float f[3], float *in = nullptr) {
     if constexpr (!CLAMP) {
         int i[3] = {0, 0, 0};
@@ -579,11 +692,11 @@ __device__ __forceinline__ long locate(const Frame<DIM> &fr, const int n[3], int
         if constexpr (SMALL) {
             int rel = __mul24(i[1], nx) + i[0];
             if constexpr (DIM == 3) rel += __mul24(i[2], nxy);
-            return fr.base + rel;
+            return rel;
         } else {
             long rel = (long)i[1] * nx + i[0];
             if constexpr (DIM == 3) rel += (long)i[2] * nxy;
-            return fr.base + rel;
+            return rel;
         }
     } else {
         long idx = 0;
@@ -620,17 +733,18 @@ __device__ __forceinline__ float cube_or_square_root(float tau) {
 
 // Sums of one lane for one iteration over pair-points q = gl, gl + G, ... < P (pair m = q / L,
 // radial index l = q % L), U pair-points in flight.
-// FULL: L divides G and G U divides P, so every pass of every lane holds U valid pair-points, all at
-// the lane's radial index l0 (pairs m0 + k G / L), and the passes are uniform: no per-pair-point
-// index stepping or validity tests. The arithmetic of each pair-point is the same in both forms.
-// GRADI: the centre sums are sum S grad I (voxel-coordinate gradient of the interpolant, zero along
+// FULL: L = 16 and G U divides P, so every pass of every lane holds U valid pair-points, all at the lane's
+// radial index gl % 16 (pairs gl / 16 + k G / 16), and the passes are uniform: no per-pair-point index
+// stepping or validity tests. The arithmetic of each pair-point is the same in both forms.
+// n: the volume's size (CLAMP only). GRADI: the centre sums are sum S grad I (voxel-coordinate gradient of the interpolant, zero along
 // axes beyond a face) instead of sum -dS/dr I u / h.
 template <int DIM, int G, int U, bool CLAMP, bool GRADI = false, bool FULL = false, typename V>
-__device__ __forceinline__ void lane_sums(const V &vol, const Frame<DIM> &fr, const float4 *pu,
+__device__ __forceinline__ void lane_sums(const V &vol, const int *n, const Frame<DIM> &fr, const float4 *pu,
                                           int P, int L, float invL, int gl, int l0, int m0, int dl, int dm,
                                           float acc[2 + DIM]) {
-    int l = l0, m = m0;
-    const float lf = (float)l0;
+    int l = l0, m = FULL ? gl >> 4 : m0;
+    const float lf = (float)(gl & 15);
+    if constexpr (FULL) invL = 0.0625f;
     for (int q = FULL ? 0 : gl; q < P; q += G * U) {
         Corners<DIM> cp[U], cm[U];
         float fp[U][3], fm[U][3], d1s[U], d2s[U];
@@ -641,7 +755,7 @@ __device__ __forceinline__ void lane_sums(const V &vol, const Frame<DIM> &fr, co
         for (int k = 0; k < U; ++k) {
             if constexpr (FULL) {
                 ok[k] = true;
-                mk[k] = m + k * dm;
+                mk[k] = m + k * (G / 16);
             } else {
                 ok[k] = q + k * G < P;
                 mk[k] = ok[k] ? m : 0;
@@ -661,12 +775,12 @@ __device__ __forceinline__ void lane_sums(const V &vol, const Frame<DIM> &fr, co
                 wm[a] = fmaf(-rad, du[a], fr.off[a]);
             }
             constexpr bool SMALL = V::kSmall;
-            const long ip = locate<DIM, CLAMP, SMALL>(fr, vol.n, vol.nx, vol.nxy, wp, fp[k],
+            const long ip = locate<DIM, CLAMP, SMALL>(fr, n, vol.nx, vol.nxy, wp, fp[k],
                                                       GRADI && CLAMP ? inp[k] : nullptr);
-            const long im = locate<DIM, CLAMP, SMALL>(fr, vol.n, vol.nx, vol.nxy, wm, fm[k],
+            const long im = locate<DIM, CLAMP, SMALL>(fr, n, vol.nx, vol.nxy, wm, fm[k],
                                                       GRADI && CLAMP ? inm[k] : nullptr);
-            vol.load(ip, cp[k]);
-            vol.load(im, cm[k]);
+            vol.load(ip, CLAMP ? 0 : fr.base, cp[k]);
+            vol.load(im, CLAMP ? 0 : fr.base, cm[k]);
             if constexpr (!FULL) {
                 l += dl;
                 m += dm;
@@ -676,7 +790,7 @@ __device__ __forceinline__ void lane_sums(const V &vol, const Frame<DIM> &fr, co
                 }
             }
         }
-        if constexpr (FULL) m += U * dm;
+        if constexpr (FULL) m += U * (G / 16);
         // branch-free: a pair-point past P (it read pair 0, in bounds) gets zero weights, so its
         // gathers are consumed unconditionally and those of all U pair-points stay in flight
         // together
@@ -721,7 +835,7 @@ __device__ __forceinline__ void lane_sums(const V &vol, const Frame<DIM> &fr, co
 // (clamp-to-edge outside the volume when CLAMP). Box points q = gl, gl + G, ..., x fastest; P
 // points are evaluated per pass with their loads issued first.
 template <int DIM, int G, bool CLAMP, int LAYOUT>
-__device__ __forceinline__ void lattice_sums(const Vol<DIM, LAYOUT> &vol, const Frame<DIM> &fr, const float hh[3],
+__device__ __forceinline__ void lattice_sums(const Vol<DIM, LAYOUT> &vol, const int *n, const Frame<DIM> &fr, const float hh[3],
                                              const float inv_h[3], int gl, float acc[2 + DIM]) {
     constexpr int P = 4;
     int lo[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
@@ -764,7 +878,7 @@ __device__ __forceinline__ void lattice_sums(const Vol<DIM, LAYOUT> &vol, const 
                 idx = 0;
                 const long stride[3] = {1, vol.nx, vol.nxy};
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) idx += (long)min(max(fr.anc[a] + j[a], 0), vol.n[a] - 1) * stride[a];
+                for (int a = 0; a < DIM; ++a) idx += (long)min(max(fr.anc[a] + j[a], 0), n[a] - 1) * stride[a];
             } else if constexpr (LAYOUT != kGlobalPlain) {
                 int rel = __mul24(j[1], vol.nx) + j[0];
                 if constexpr (DIM == 3) rel += __mul24(j[2], vol.nxy);
@@ -919,47 +1033,56 @@ __device__ __forceinline__ int uni(int v) {
     else return v;
 }
 
-// Run up to n_iter iterations of the group's contour (slot == nullptr: no contour), stopping early at
-// iteration `target` or when it leaves SNK_ACTIVE. All lanes of the workgroup call this; the loop
-// and its barriers are workgroup-uniform.
-// STAGE (whole-wave groups): iterations whose ball fits a box of tile_cap voxels read their corners
-// from an LDS box at lds_tile, the others from the volume in LAYOUT.
-// Soft repulsion of one contour (kappa > 0): the snapshot of every contour and this contour's
-// neighbour list (cnt indices, ascending).
+// A value that the compiler cannot see through: what is formed from the lane's number would otherwise be
+// formed before the loop and kept in a register of its own for all of it.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Soft repulsion of one contour: its neighbour list holds cnt (ascending) of the contours in a->snap; -1: off.
 struct Repel {
-    const float4 *snap = nullptr;
-    const int *nb = nullptr;
-    int cnt = 0;
-    float kappa = 0.0f;
+    Cold<EvolveArgs> a;
+    int cid, cnt;
 };
 
-template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT = false, bool STAGE = false, bool GRADI = false>
-__device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int target, float *trace_row,
-                          float *lds_draws, float *lds_red, unsigned long long *counter, float *lds_tile = nullptr,
-                          int tile_cap = 0, const Repel rp = Repel{}) {
-    static_assert(!STAGE || (G >= 64 && !EXACT), "LDS boxes are staged by whole-wave Monte-Carlo groups");
+// Per-iteration quantities of the weight for radius R.
+template <int DIM, int G>
+__device__ __forceinline__ void set_frame(Frame<DIM> &fr, const JobParams &p, float smax, float ain, float R) {
+    constexpr float RHO = DIM == 3 ? 0.79370052598409973738f : 0.70710678118654752440f;
+    fr.smax = smax;
+    fr.ain = ain;
+    fr.R = R;
+    fr.hd = uni<G>(0.5f * RHO * p.dR);
+    fr.hD = uni<G>(0.5f * p.dR);
+    fr.is = p.in_slope;
+    fr.os = p.out_slope;
+    fr.rho_is = uni<G>(RHO * p.in_slope);
+}
+
+// Sub-wave groups (G = 16 or 32, several contours per wave64): run up to n_iter iterations of the group's
+// contour (slot == nullptr: no contour), stopping early when it leaves SNK_ACTIVE. All lanes of the
+// workgroup call this; the loop and its barriers are workgroup-uniform. Every lane holds its contour's state.
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT = false>
+__device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, float *trace_row, float *lds_draws,
+                          unsigned long long *counter) {
+    static_assert(G < 64, "whole waves: run_wave");
     constexpr int NR = 2 + DIM;
-    constexpr int WAVES = Grp<G>::WAVES;
     constexpr float RHO = DIM == 3 ? 0.79370052598409973738f : 0.70710678118654752440f;
     constexpr float BALL = DIM == 3 ? 4.18879020478639098462f : 3.14159265358979323846f;
-    const int t = threadIdx.x;
-    const int gl = G < 64 ? (t & (G - 1)) : t;
-    const int lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);  // wave-uniform (scalar branches)
+    const int gl = threadIdx.x & (G - 1);
 
     DevContour s{};
     s.status = SNK_OUT;
-    if (slot) {
-        if constexpr (G >= 64) s = uniform_copy(slot);
-        else s = *slot;
-    }
+    if (slot) s = *slot;
     const int n0 = s.iters;
-    const int budget = ((s.status & 0x0f) == SNK_ACTIVE && slot) ? min(n_iter, target - n0) : 0;
+    const int budget = ((s.status & 0x0f) == SNK_ACTIVE && slot) ? min(n_iter, 0x7fffffff - n0) : 0;
     const int MH = p.M / 2;
     const int P = MH * p.L;
     const Draws dr(lds_draws, G, MH);
     const uint32_t id = s.id;
     const Vol<DIM, LAYOUT> vol(p.g);
+    const int nvol[3] = {p.g.nx, p.g.ny, p.g.nz};
     const float inv_h[3] = {p.g.inv_h[0], p.g.inv_h[1], p.g.inv_h[2]};
     const float hh[3] = {p.g.h[0], p.g.h[1], p.g.h[2]};
 
@@ -973,9 +1096,6 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
     const float invL = 1.0f / (float)L;
     const int l0 = gl % L, m0 = gl / L;
     const int dl = G % L, dm = G / L;
-    // every lane's passes hold only valid pair-points at one radial index (lane_sums FULL; in 2D:
-    // the second copy of the sums loop costs the 3D instances registers they do not have)
-    const bool full = DIM == 2 && dl == 0 && P % (G * U) == 0;
 
     int anc[3] = {s.anc[0], s.anc[1], s.anc[2]};
     float off[3] = {s.off[0], s.off[1], s.off[2]};
@@ -988,15 +1108,10 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
     const float tol2 = p.conv_tol * p.conv_tol;
     int ran = 0;
     int cull_next = p.cull_first;  // this launch's next culling pass point (-1: none)
-    Tile tile;
-    tile.valid = false;
 
     for (int it = 0;; ++it) {
         const bool active = it < budget && (status & 0x0f) == SNK_ACTIVE;
-        bool any;
-        if constexpr (G <= 64) any = __builtin_amdgcn_ballot_w64(active) != 0;
-        else any = active;  // identical in every wave of the workgroup
-        if (!any) break;
+        if (__builtin_amdgcn_ballot_w64(active) == 0) break;
         float acc[NR];
 #pragma unroll
         for (int k = 0; k < NR; ++k) acc[k] = 0.0f;
@@ -1008,14 +1123,7 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
                 draws_phase1<DIM, G>(dr, (blk + 1) & 1, (uint32_t)(n0 + 1 + (blk + 1) * dr.K), id, p, gl);
             if (!EXACT && sl == 1) draws_phase2<DIM, G>(dr, (blk + 1) & 1, p, gl);
 
-            fr.smax = uni<G>(R + 0.5f * p.dR);
-            fr.ain = uni<G>(RHO * R);
-            fr.R = R;
-            fr.hd = 0.5f * RHO * p.dR;
-            fr.hD = 0.5f * p.dR;
-            fr.is = p.in_slope;
-            fr.os = p.out_slope;
-            fr.rho_is = RHO * p.in_slope;
+            set_frame<DIM, G>(fr, p, R + 0.5f * p.dR, RHO * R, R);
             long base = 0;
             const long stride[3] = {1, vol.nx, vol.nxy};
 #pragma unroll
@@ -1030,97 +1138,31 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
                 // interior
                 const float ext = fmaf(fr.smax * inv_h[a], 1.0001f, 1e-3f);
                 interior = interior && (off[a] - ext > (float)(-anc[a])) &&
-                           (off[a] + ext < (float)(vol.n[a] - 1 - anc[a]));
+                           (off[a] + ext < (float)(nvol[a] - 1 - anc[a]));
             }
             fr.base = base;
             if constexpr (EXACT) {
                 if (interior)
-                    lattice_sums<DIM, G, false, LAYOUT>(vol, fr, hh, inv_h, gl, acc);
+                    lattice_sums<DIM, G, false, LAYOUT>(vol, nvol, fr, hh, inv_h, gl, acc);
                 else
-                    lattice_sums<DIM, G, true, LAYOUT>(vol, fr, hh, inv_h, gl, acc);
+                    lattice_sums<DIM, G, true, LAYOUT>(vol, nvol, fr, hh, inv_h, gl, acc);
             } else {
                 const float4 *pu = dr.pu + dr.slot(blk & 1, sl) * MH;
-                bool staged = false;
-                if constexpr (STAGE) {
-                    if (interior && tile_cap > 0) {
-                        int lo[3], hi[3];
-                        ball_range<DIM>(fr, inv_h, lo, hi);
-                        bool covered = tile.valid;
-#pragma unroll
-                        for (int a = 0; a < DIM; ++a)
-                            covered = covered && lo[a] >= tile.lo[a] && hi[a] < tile.lo[a] + tile.n[a];
-                        if (!covered && choose_tile<DIM>(lo, hi, vol.n, tile_cap, tile)) {
-                            // the previous iteration's reads of the box ended at its reduction barrier
-                            stage_tile<G>(lds_tile, p.g.J, vol.nx, vol.nxy, tile, gl);
-                            __syncthreads();
-                        }
-                        staged = tile.valid;
-                    }
-                }
-                if (staged) {
-                    TileVol<DIM> tv;
-                    tv.t = lds_tile;
-                    tv.n[0] = tile.n[0];
-                    tv.n[1] = tile.n[1];
-                    tv.n[2] = tile.n[2];
-                    tv.nx = tile.n[0];
-                    tv.nxy = tile.n[0] * tile.n[1];
-                    Frame<DIM> ft = fr;
-                    ft.base = (anc[0] - tile.lo[0]) + (anc[1] - tile.lo[1]) * tv.nx;
-                    if constexpr (DIM == 3) ft.base += (anc[2] - tile.lo[2]) * tv.nxy;
-                    if (full)
-                        lane_sums<DIM, G, U, false, GRADI, true>(tv, ft, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-                    else
-                        lane_sums<DIM, G, U, false, GRADI>(tv, ft, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-                } else if (interior) {
-                    if (full)
-                        lane_sums<DIM, G, U, false, GRADI, true>(vol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-                    else
-                        lane_sums<DIM, G, U, false, GRADI>(vol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-                } else {
-                    lane_sums<DIM, G, U, true, GRADI>(vol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-                }
+                if (interior)
+                    lane_sums<DIM, G, U, false>(vol, nvol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
+                else
+                    lane_sums<DIM, G, U, true>(vol, nvol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
             }
         }
 
-        // group totals
         float tot[NR];
-        if constexpr (G < 64) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) tot[k] = group_sum_wave<G>(acc[k]);
-        } else if constexpr (G == 64) {
-            wave_sums<NR>(acc, tot);
-        } else {
-            float *red = lds_red + (it & 1) * NR * WAVES;
-            float wt[NR];
-            wave_sums<NR>(acc, wt);
-            if (lane == 0) {
-#pragma unroll
-                for (int k = 0; k < NR; ++k) red[k * WAVES + wave] = wt[k];
-            }
-            __syncthreads();
-            // every wave adds the partials in wave order, so all of them hold the same totals and
-            // take the same step below (no second barrier to hand wave 0's result to the others)
-#pragma unroll
-            for (int k = 0; k < NR; ++k) {
-                float v = red[k * WAVES];
-#pragma unroll
-                for (int w = 1; w < WAVES; ++w) v += red[k * WAVES + w];
-                tot[k] = v;
-            }
-        }
-        // gradient form: sum S dI/dv_a (voxel coordinates) -> the units of the weight form's
-        // sum -dS/dr I u_a / h_a, i.e. the physical force divided by h_a
-        if constexpr (GRADI) {
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) tot[2 + a] *= inv_h[a] * inv_h[a];
-        }
+        for (int k = 0; k < NR; ++k) tot[k] = group_sum<G>(acc[k]);
 
-        // descent step, identical in every lane of the group (multi-wave groups: every wave, from the
-        // same totals)
+        // descent step, identical in every lane of the group
         if (active) {
             // no multiply-add contraction in the step: every instance (with or without the optional
-            // terms below) rounds it operation by operation, so their results agree bit for bit
+            // terms of run_wave) rounds it operation by operation, so their results agree bit for bit
 #pragma clang fp contract(off)
             n += 1;
             const float smax = fr.smax;
@@ -1139,7 +1181,7 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
             const float gR = (BR - (2.0f * DIM) * inv2R * A) * inv_norm;
             const float eps = p.eps0 * __builtin_amdgcn_rsqf((float)n);
             const float half_eps = 0.5f * eps;
-            float dRs = -half_eps * gR;
+            const float dRs = -half_eps * gR;
             const float kc = -half_eps * scale * inv_norm;
             float doff[3] = {0.0f, 0.0f, 0.0f}, dc[3] = {0.0f, 0.0f, 0.0f};
             float dc2 = 0.0f;
@@ -1147,48 +1189,6 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
             for (int i = 0; i < DIM; ++i) {
                 doff[i] = kc * tot[2 + i];   // voxel units (B_c was accumulated against u / h)
                 dc[i] = doff[i] * hh[i];
-            }
-            if constexpr (G >= 64) {
-                if (rp.kappa > 0.0f) {
-                    // repulsion of the neighbours' snapshot: lane k takes neighbour k; with t = |c - c_j| /
-                    // (rho (R + R_j)) < 1 the penalty (1 - t)^2 has dP/dc = -2 (1 - t) (c - c_j) /
-                    // (|c - c_j| rho (R + R_j)) and dP/dR = 2 (1 - t) t / (R + R_j)
-                    float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if (lane < rp.cnt) {
-                        const int j = rp.nb[lane];
-                        const float4 s0 = rp.snap[2 * j], s1 = rp.snap[2 * j + 1];
-                        const int aj[3] = {__float_as_int(s0.x), __float_as_int(s0.y), __float_as_int(s0.z)};
-                        const float oj[3] = {s1.x, s1.y, s1.z};
-                        float dv[3] = {0.0f, 0.0f, 0.0f}, d2 = 0.0f;
-#pragma unroll
-                        for (int a = 0; a < DIM; ++a) {
-                            dv[a] = ((float)(anc[a] - aj[a]) + (off[a] - oj[a])) * hh[a];
-                            d2 = fmaf(dv[a], dv[a], d2);
-                        }
-                        const float d = __builtin_amdgcn_sqrtf(d2);
-                        const float span = RHO * (R + s0.w);
-                        const float t = d / span;
-                        if (t < 1.0f) {
-                            const float om = 1.0f - t;
-                            v[3] = 2.0f * om * t / (R + s0.w);
-                            if (d > 0.0f) {
-                                const float f = -2.0f * om / (d * span);
-#pragma unroll
-                                for (int a = 0; a < DIM; ++a) v[a] = f * dv[a];
-                            }
-                        }
-                    }
-                    float rt[4];
-                    wave_sums<4>(v, rt);
-                    const float kr = -half_eps * rp.kappa;
-                    dRs = dRs + kr * rt[3];
-#pragma unroll
-                    for (int i = 0; i < DIM; ++i) {
-                        const float dcr = kr * rt[i];
-                        dc[i] = dc[i] + dcr;
-                        doff[i] = doff[i] + dcr * inv_h[i];
-                    }
-                }
             }
 #pragma unroll
             for (int i = 0; i < DIM; ++i) dc2 = fmaf(dc[i], dc[i], dc2);
@@ -1236,35 +1236,21 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
                         anc[i] += (int)k;
                         off[i] -= k;
                     }
-                    if (off[i] < (float)(-anc[i]) || off[i] > (float)(vol.n[i] - 1 - anc[i])) st = SNK_OUT;
+                    if (off[i] < (float)(-anc[i]) || off[i] > (float)(nvol[i] - 1 - anc[i])) st = SNK_OUT;
                 }
             }
             if (st == SNK_ACTIVE) {
                 streak = small ? min(streak + 1, 255) : 0;
                 if (p.conv_window > 0 && streak >= p.conv_window) st = SNK_CONVERGED;
             }
-            // a culling pass without competition judges each contour alone: at the run's pass
-            // points an active contour above the threshold retires here and frees its slot at once
-            // (the pass after the evolution treats the others as the passes between chunks would)
             if (it == cull_next) {
-                // kept a branch (an empty volatile statement cannot be executed speculatively):
-                // selects in its place would cost every iteration of every run
-                __asm__ volatile("");
                 if (st == SNK_ACTIVE && !(E <= p.cull_thr)) st = SNK_CULLED;
                 cull_next = cull_next + p.cull_every <= p.cull_last ? cull_next + p.cull_every : -1;
             }
-            status = (uint8_t)uni<G>((int)(st | flag));
-            streak = uni<G>(streak);
-            R = uni<G>(R);
-            e_mc = uni<G>(e_mc);
-#pragma unroll
-            for (int i = 0; i < DIM; ++i) {
-                off[i] = uni<G>(off[i]);
-                anc[i] = uni<G>(anc[i]);
-            }
+            status = (uint8_t)(st | flag);
             ++ran;
         }
-        if constexpr (G <= 64) __syncthreads();  // orders this iteration's LDS draws before later reads
+        __syncthreads();  // orders this iteration's LDS draws before later reads
     }
 
     if (slot && gl == 0 && budget > 0) {
@@ -1283,49 +1269,469 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, int 
     }
 }
 
-// LDS of one workgroup: draws of each contour it holds, then (multi-wave groups) the reduction
-// slots.
-template <int DIM, int G>
-__host__ __device__ __forceinline__ int lds_floats(int MH) {
-    const int per = (draw_floats(G, MH) + 3) & ~3;
-    return Grp<G>::CPB * per + (G > 64 ? 2 * (2 + DIM) * Grp<G>::WAVES : 0);
-}
+// Whole-wave groups (G = 64, 128 or 256 lanes, one contour per workgroup): run up to n_iter iterations of
+// the contour, stopping at iteration `target` or when it leaves SNK_ACTIVE.
+//
+// What bounds an iteration is instruction issue: one contour's iterations are a serial chain, a wave issues
+// one vector instruction per four cycles, and 4 to 8 samples per lane are few against the code around them.
+// So that code is kept short:
+//   - the step works on the axes in parallel: after the quad reduction lane i holds the total of A, x, y, z
+//     (2D: A, x, y, B_R) for i & 3 = 0 .. 3, and the centre's offset, its bounds and the spacing live in the
+//     same lanes, so the step, the interior and box tests and the OUT test each take one instruction for all
+//     axes; only the three offsets the gathers need move to scalar registers;
+//   - what hardly ever happens (a new anchor voxel, OUT, a value that is not finite) is one test of all of it
+//     together and a branch;
+//   - factors that do not depend on the sums are formed before the waves meet;
+//   - FULL instances (L = 16 and whole passes) step no per-pair-point indices;
+//   - the draws: see WaveDraws.
+// Vector instructions per wave and iteration, before -> now, and the evolve's time: slab (3D, two waves, 512
+// pair-points, boxes) 748 -> 546, 2.70 -> 2.34 ms; 8192^2 image (one wave, 128 pair-points) 280 -> 231, 5.1 ->
+// 4.4 ms; 62,500 lattice contours (four waves) 456 -> 323, 10.6 -> 9.1 ms.
+//
+// STAGE: iterations whose ball fits a box of tile_cap voxels read their corners from an LDS box, the others
+// from the volume in LAYOUT. lds: draws, the waves' partial sums, the box.
+// cp: p in constant memory.
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL>
+__device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slot, int n_iter, int target,
+                         float *trace_row, float *lds, int draw_k, int rot_k, unsigned long long *counter,
+                         int tile_cap, const Repel rp) {
+    static_assert(G >= 64, "whole waves");
+    static_assert(!STAGE || !EXACT, "LDS boxes are staged by Monte-Carlo groups");
+    constexpr int NR = 2 + DIM;
+    constexpr int WAVES = G / 64;
+    constexpr float RHO = DIM == 3 ? 0.79370052598409973738f : 0.70710678118654752440f;
+    constexpr float BALL = DIM == 3 ? 4.18879020478639098462f : 3.14159265358979323846f;
+    constexpr uint64_t AXES = DIM == 3 ? 0xE : 0x6;         // lanes 1 .. DIM: the axes
+    constexpr uint64_t LAST = DIM == 3 ? 0x8 : 0x4;         // lane of the last axis
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
 
-// Whole-wave groups with one pair-point in flight fit 64 vector registers: ask for 8 waves per SIMD
-// (a full CU of 4-wave groups holds 8 contours). Two-wave groups with four pair-points in flight
-// ask for 4 waves per SIMD (128 registers), so 8 contours per CU stay resident.
-// STAGE: the workgroup's LDS ends with a box of a.tile_cap voxels. GRADI: centre force in its
-// image-gradient form.
-template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI>
-__global__ __launch_bounds__(Grp<G>::NT, (U == 1 && G >= 64) ? 8 : ((U == 4 && G == 128) ? 4 : 1))
-void evolve_kernel(EvolveArgs a) {
-    extern __shared__ float lds[];
-    const int MH = a.p.M / 2;
-    const int per = (draw_floats(G, MH) + 3) & ~3;
-    const int sub = G < 64 ? (int)threadIdx.x / G : 0;
-    const int k = blockIdx.x * Grp<G>::CPB + sub;
-    const int cid = k < a.n ? (a.idx ? a.idx[k] : k) : k;
-    DevContour *slot = k < a.n ? a.st + cid : nullptr;
-    Repel rp;
-    if (G >= 64 && a.kappa > 0.0f && slot) {
-        rp.snap = a.snap;
-        rp.nb = a.nb + (long)cid * a.nb_cap;
-        rp.cnt = __builtin_amdgcn_readfirstlane(a.nbn[cid]);
-        rp.kappa = a.kappa;
+    const DevContour s = uniform_copy(slot);
+    const int n0 = s.iters;
+    const int budget = (s.status & 0x0f) == SNK_ACTIVE ? min(n_iter, target - n0) : 0;
+    if (budget <= 0) return;   // uniform over the workgroup
+    const int MH = p.M / 2;
+    const int P = MH * p.L;
+    const int L = p.L;
+    const uint32_t id = s.id;
+    const Vol<DIM, LAYOUT> vol(p.g);
+    const WaveDraws<DIM, G> dr(lds, draw_k, rot_k, MH);
+    float *lds_red = lds + (EXACT ? 0 : wave_draw_floats(DIM, draw_k, rot_k, MH));
+    float *lds_axis = lds_red + (WAVES > 1 ? 16 * WAVES : 0);
+    float *lds_tile = lds_axis + 32 * WAVES;
+    const int nb = EXACT ? 1 : dr.KR / dr.K;   // blocks per set of rotations
+    if constexpr (!EXACT) {
+        if (wave == WAVES - 1) dr.rotations((uint32_t)(n0 + 1), id, cp, lane);
+        __syncthreads();
+        for (int r = wave; r < dr.passes; r += WAVES)
+            dr.finish(dr.begin(r, (uint32_t)(n0 + 1), id, cp, lane), 0, 0, cp);
+        __syncthreads();
+        if (nb == 1) {
+            if (wave == WAVES - 1) dr.rotations((uint32_t)(n0 + 1 + dr.K), id, cp, lane);
+            __syncthreads();
+        }
     }
-    run_group<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI>(a.p, slot, a.n_iter, 0x7fffffff,
-                                                      TRACE && slot ? a.trace + (long)cid * SNK_TRACE_W : nullptr,
-                                                      lds + sub * per, lds + Grp<G>::CPB * per, a.counter,
-                                                      lds + lds_floats<DIM, G>(MH), STAGE ? a.tile_cap : 0, rp);
+
+    // general pair-point stepping (not FULL)
+    const float invL = 1.0f / (float)L;
+    const int l0 = FULL ? 0 : tid % L, m0 = FULL ? 0 : tid / L;
+    const int dl = FULL ? 0 : G % L, dm = FULL ? 0 : G / L;
+
+    // Each lane stands for one axis (lanes 1 .. DIM of each four; the others repeat an axis and are never
+    // looked at). What it needs of it, relative to the anchor voxel where it is a place, lies in LDS: the
+    // registers belong to the gathers. rec: 1/h, the volume's faces, h, the range that the box covers, the
+    // axis's last voxel.
+    float *rec = lds_axis + wave * 32 + (lane & 3) * 8;
+    int anc[3] = {s.anc[0], s.anc[1], s.anc[2]};
+    float off_l = (lane & 3) == 3 && DIM == 3 ? s.off[2] : ((lane & 3) == 2 ? s.off[1] : s.off[0]);
+    long base = 0;
+    Tile tile;
+    tile.valid = false;
+    float retry = 3.0e38f;     // no box fitted a ball this large: not tried again until it has shrunk
+    auto axis = [&](int t, int v0, int v1, int v2) {
+        const int l = opaque(t) & 3;
+        return DIM == 3 && l == 3 ? v2 : (l == 2 ? v1 : v0);
+    };
+    auto anchored = [&]() {
+        const int al = axis(lane, anc[0], anc[1], anc[2]);
+        rec[1] = (float)(-al);
+        rec[2] = (float)(__float_as_int(rec[6]) - al);
+        base = anc[0] + (long)anc[1] * vol.nx;
+        if constexpr (DIM == 3) base += (long)anc[2] * vol.nxy;
+        if constexpr (STAGE) {
+            const int tl = axis(lane, tile.lo[0], tile.lo[1], tile.lo[2]);
+            const int tn = axis(lane, tile.n[0], tile.n[1], tile.n[2]);
+            // floor(v) >= lo and floor(v) + 1 < lo + n for whole lo and n
+            rec[4] = tile.valid ? (float)(tl - al) : 3.0e38f;
+            rec[5] = tile.valid ? (float)(tl + tn - 1 - al) : -3.0e38f;
+        }
+    };
+    rec[0] = __int_as_float(axis(lane, __float_as_int(p.g.inv_h[0]), __float_as_int(p.g.inv_h[1]),
+                                 __float_as_int(p.g.inv_h[2])));
+    rec[3] = __int_as_float(axis(lane, __float_as_int(p.g.h[0]), __float_as_int(p.g.h[1]), __float_as_int(p.g.h[2])));
+    rec[6] = __int_as_float(axis(lane, p.g.nx, p.g.ny, p.g.nz) - 1);
+    anchored();
+    float R = s.R;
+    int status = s.status;
+    int streak = s.streak;
+    float e_mc = s.e_mc;
+    const float inv_npts = uni<G>(1.0f / (float)(p.M * p.L));
+    const float tol2 = uni<G>(p.conv_tol * p.conv_tol);
+    int cull_next = p.cull_first;  // this launch's next culling pass point (-1: none)
+    int blk = 0, sl = 0;
+    int rot_next = EXACT || nb == 1 ? 0 : dr.K;   // the next block's entries in the set of rotations
+
+    int it = 0;
+    for (; it < budget && (status & 0x0f) == SNK_ACTIVE; ++it) {
+        // no multiply-add contraction: every instance (with or without the optional terms below) rounds
+        // the step operation by operation, so their results agree bit for bit
+#pragma clang fp contract(off)
+        const int gl = opaque(tid);
+        const int lane = gl & 63;
+        float acc[NR];
+#pragma unroll
+        for (int k = 0; k < NR; ++k) acc[k] = 0.0f;
+        Frame<DIM> fr;
+        const float smax_v = R + 0.5f * p.dR;
+        set_frame<DIM, G>(fr, p, uni<G>(smax_v), RHO * R, R);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            fr.anc[a] = anc[a];
+            fr.off[a] = a < DIM ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(off_l), 1 + a)) : 0.0f;
+        }
+        fr.base = base;
+        // clamping can be skipped when the whole sample ball (with a rounding margin) is interior
+        const float4 r0 = *reinterpret_cast<const float4 *>(rec);
+        const float ext = fmaf(smax_v * r0.x, 1.0001f, 1e-3f);
+        const float below = off_l - ext, above = off_l + ext;
+        const bool interior = (__builtin_amdgcn_ballot_w64(below > r0.y && above < r0.z) & AXES) == AXES;
+        int nvol[3] = {0, 0, 0};
+        if (!interior) {
+            const Cold<JobParams> q = cold(cp);
+            nvol[0] = q->g.nx;
+            nvol[1] = q->g.ny;
+            nvol[2] = q->g.nz;
+        }
+        if constexpr (EXACT) {
+            const float inv_h[3] = {p.g.inv_h[0], p.g.inv_h[1], p.g.inv_h[2]};
+            const float hh[3] = {p.g.h[0], p.g.h[1], p.g.h[2]};
+            if (interior)
+                lattice_sums<DIM, G, false, LAYOUT>(vol, nvol, fr, hh, inv_h, gl, acc);
+            else
+                lattice_sums<DIM, G, true, LAYOUT>(vol, nvol, fr, hh, inv_h, gl, acc);
+        } else {
+            const float4 *pu = dr.pu + ((blk & 1) * dr.K + sl) * MH;
+            bool staged = false;
+            if constexpr (STAGE) {
+                if (interior) {
+                    const float2 r1 = *reinterpret_cast<const float2 *>(rec + 4);
+                    staged = (__builtin_amdgcn_ballot_w64(below >= r1.x && above < r1.y) & AXES) == AXES;
+                    if (!staged && fr.smax < retry) {
+                        const Cold<JobParams> q = cold(cp);
+                        const float inv_h[3] = {q->g.inv_h[0], q->g.inv_h[1], q->g.inv_h[2]};
+                        const int nv[3] = {q->g.nx, q->g.ny, q->g.nz};
+                        int lo[3], hi[3];
+                        ball_range<DIM>(fr, inv_h, lo, hi);
+                        if (choose_tile<DIM>(lo, hi, nv, tile_cap, tile)) {
+                            // the previous iteration's reads of the box ended at its reduction barrier
+                            stage_tile<G>(lds_tile, q->g.J, vol.nx, vol.nxy, tile, gl);
+                            __syncthreads();
+                            staged = true;
+                            retry = 3.0e38f;
+                        } else {
+                            retry = fr.smax - 0.05f;
+                        }
+                        anchored();
+                    }
+                }
+            }
+            if (staged) {
+                TileVol<DIM> tv;
+                tv.t = lds_tile;
+                tv.nx = tile.n[0];
+                tv.nxy = tile.n[0] * tile.n[1];
+                Frame<DIM> ft = fr;
+                ft.base = (anc[0] - tile.lo[0]) + (anc[1] - tile.lo[1]) * tv.nx;
+                if constexpr (DIM == 3) ft.base += (anc[2] - tile.lo[2]) * tv.nxy;
+                lane_sums<DIM, G, U, false, GRADI, FULL>(tv, nvol, ft, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
+            } else if (interior) {
+                lane_sums<DIM, G, U, false, GRADI, FULL>(vol, nvol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
+            } else {
+                lane_sums<DIM, G, U, true, GRADI, FULL>(vol, nvol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
+            }
+        }
+        // draws ahead
+        typename WaveDraws<DIM, G>::Pending pend;
+        pend.on = false;
+        if constexpr (!EXACT) {
+            if (sl == 0 && it + dr.K < budget) {
+                const int r = (wave + blk) & (WAVES - 1);
+                if (r < dr.passes) pend = dr.begin(r, (uint32_t)(n0 + 1 + it + dr.K), id, cp, lane);
+            }
+        }
+
+        // totals: x holds A, x, y, z (2D: A, x, y, B_R) in lanes 0 .. 3 of each four, br B_R in every lane
+        float x, br;
+        {
+            float v[5] = {acc[0], acc[3], acc[2], DIM == 3 ? acc[NR - 1] : acc[1], acc[1]};
+            wave_quads<NR>(v, x, br);
+        }
+        const int n = n0 + it + 1;
+        float smax_d = smax_v;
+#pragma unroll
+        for (int i = 1; i < DIM; ++i) smax_d *= smax_v;
+        // Monte-Carlo: V/N; exact: the voxel measure
+        const float scale = EXACT ? p.g.h[0] * p.g.h[1] * (DIM == 3 ? p.g.h[2] : 1.0f) : BALL * smax_d * inv_npts;
+        const float inv2R = __builtin_amdgcn_rcpf(2.0f * R);
+        float inv_norm = inv2R;
+#pragma unroll
+        for (int i = 1; i < DIM; ++i) inv_norm *= inv2R;
+        const float eps = p.eps0 * __builtin_amdgcn_rsqf((float)n);
+        const float half_eps = 0.5f * eps;
+        const float kc = -half_eps * scale * inv_norm;
+        if constexpr (WAVES > 1) {
+            // per-wave partials, added in wave order by every wave, so all of them hold the same totals
+            // and take the same step (no second barrier to hand one wave's result to the others)
+            float *red = lds_red + (it & 1) * 8 * WAVES;
+            if (lane < 5) red[wave * 8 + lane] = (DIM == 3 && lane == 4) ? br : x;
+            __syncthreads();
+            x = red[lane & 3];
+            if constexpr (DIM == 3) br = red[4];
+#pragma unroll
+            for (int w = 1; w < WAVES; ++w) {
+                x += red[w * 8 + (lane & 3)];
+                if constexpr (DIM == 3) br += red[w * 8 + 4];
+            }
+        }
+        if constexpr (DIM == 2) br = dpp<0xFF>(x);   // quad_perm [3, 3, 3, 3]
+        const float a0 = dpp<0x00>(x);               // quad_perm [0, 0, 0, 0]
+        // gradient form: sum S dI/dv_a (voxel coordinates) -> the units of the weight form's
+        // sum -dS/dr I u_a / h_a, i.e. the physical force divided by h_a
+        const float4 r2 = *reinterpret_cast<const float4 *>(rec);   // 1/h, faces, h
+        if constexpr (GRADI) x *= r2.x * r2.x;
+
+        // descent step: radius and energy in every lane, each axis of the centre in its lanes
+        const float A = scale * a0;
+        const float BR = scale * br;
+        const float E = A * inv_norm;
+        const float gR = (BR - (2.0f * DIM) * inv2R * A) * inv_norm;
+        float dRs = -half_eps * gR;
+        float doff = kc * x;   // voxel units (B_c was accumulated against u / h)
+        float dc = doff * r2.w;
+        if (rp.cnt >= 0) {
+            const Cold<EvolveArgs> ra = cold(rp.a);
+            // repulsion of the neighbours' snapshot: lane k takes neighbour k; with t = |c - c_j| /
+            // (rho (R + R_j)) < 1 the penalty (1 - t)^2 has dP/dc = -2 (1 - t) (c - c_j) /
+            // (|c - c_j| rho (R + R_j)) and dP/dR = 2 (1 - t) t / (R + R_j)
+            float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // R, y, x, z: totals in lanes R, x, y, z
+            if (lane < rp.cnt) {
+                const int j = ra->nb[(long)rp.cid * ra->nb_cap + lane];
+                const float4 s0 = ra->snap[2 * j], s1 = ra->snap[2 * j + 1];
+                const int aj[3] = {__float_as_int(s0.x), __float_as_int(s0.y), __float_as_int(s0.z)};
+                const float oj[3] = {s1.x, s1.y, s1.z};
+                float dv[3] = {0.0f, 0.0f, 0.0f}, d2 = 0.0f;
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) {
+                    dv[a] = ((float)(anc[a] - aj[a]) + (fr.off[a] - oj[a])) * ra->p.g.h[a];
+                    d2 = fmaf(dv[a], dv[a], d2);
+                }
+                const float d = __builtin_amdgcn_sqrtf(d2);
+                const float span = RHO * (R + s0.w);
+                const float t = d / span;
+                if (t < 1.0f) {
+                    const float om = 1.0f - t;
+                    v[0] = 2.0f * om * t / (R + s0.w);
+                    if (d > 0.0f) {
+                        const float f = -2.0f * om / (d * span);
+                        v[2] = f * dv[0];
+                        v[1] = f * dv[1];
+                        v[3] = f * dv[2];
+                    }
+                }
+            }
+            float rt, unused;
+            wave_quads<4>(v, rt, unused);
+            const float kr = -half_eps * ra->kappa;
+            dRs = dRs + kr * dpp<0x00>(rt);
+            const float dcr = kr * rt;
+            dc = dc + dcr;
+            doff = doff + dcr * r2.x;
+        }
+        // |dc|^2 in axis order: lane 1 + i adds its square to lane i's sum
+        const float q1 = dc * dc;
+        float dc2 = fmaf(dc, dc, dpp<0x90>(q1));                        // quad_perm [0, 0, 1, 2]: lane 2 x, y
+        if constexpr (DIM == 3) dc2 = fmaf(dc, dc, dpp<0x90>(dc2));     // lane 3 x, y, z
+        if (TRACE && gl < 4) {
+            float *row = trace_row;
+            if (gl == 0) {
+                row[0] = A;
+                row[1] = BR;
+                row[5] = E;
+                row[6] = dRs;
+                row[10] = (float)n;
+                row[11] = R;
+                row[12] = eps;
+                row[13] = row[14] = row[15] = 0.0f;
+            } else {
+                row[1 + gl] = gl <= DIM ? scale * x * r2.w : 0.0f;
+                row[6 + gl] = gl <= DIM ? dc : 0.0f;
+            }
+        }
+        float Rn = R + dRs;
+        int flag = status & SNK_CLAMPED;
+        if (__builtin_amdgcn_ballot_w64(Rn < p.r_lo || Rn > p.r_hi) != 0) {
+            if (Rn < p.r_lo) Rn = p.r_lo;
+            if (Rn > p.r_hi) Rn = p.r_hi;
+            flag = SNK_CLAMPED;
+        }
+        const float dRe = Rn - R;
+        const bool small = (__builtin_amdgcn_ballot_w64(dRe * dRe < tol2 && dc2 < tol2) & LAST) != 0;
+        R = Rn;
+        e_mc = uni<G>(E);
+        off_l += doff;
+        int st = SNK_ACTIVE;
+        const bool finite_l = isfinite(Rn) && isfinite(E);
+        // a new anchor voxel, beyond a face, or not finite: seldom
+        if ((__builtin_amdgcn_ballot_w64(!(fabsf(off_l) < 0.5f) || off_l < r2.y || off_l > r2.z || !finite_l) & AXES) !=
+            0) {
+            if ((__builtin_amdgcn_ballot_w64(!finite_l || !isfinite(off_l)) & AXES) != 0) {
+                st = SNK_NONFINITE;
+            } else {
+                const bool far = fabsf(off_l) >= 0.5f;
+                const float k = far ? rintf(off_l) : 0.0f;
+                if (far) off_l -= k;
+#pragma unroll
+                for (int i = 0; i < DIM; ++i) anc[i] += __builtin_amdgcn_readlane((int)k, 1 + i);
+                anchored();
+                if ((__builtin_amdgcn_ballot_w64(off_l < rec[1] || off_l > rec[2]) & AXES) != 0) st = SNK_OUT;
+            }
+        }
+        if (st == SNK_ACTIVE) {
+            streak = small ? min(streak + 1, 255) : 0;
+            if (p.conv_window > 0 && streak >= p.conv_window) st = SNK_CONVERGED;
+        }
+        // a culling pass without competition judges each contour alone: at the run's pass points an
+        // active contour above the threshold retires here and frees its slot at once (the pass after
+        // the evolution treats the others as the passes between chunks would)
+        if (it == cull_next) {
+            const Cold<JobParams> q = cold(cp);
+            if (st == SNK_ACTIVE && __builtin_amdgcn_ballot_w64(!(E <= q->cull_thr)) != 0) st = SNK_CULLED;
+            cull_next = cull_next + q->cull_every <= q->cull_last ? cull_next + q->cull_every : -1;
+        }
+        status = st | flag;
+        if constexpr (!EXACT) {
+            if (sl == 0 && it + dr.K < budget) {
+                dr.finish(pend, (blk + 1) & 1, rot_next, cp);
+                // blocks of more passes than waves
+                for (int r = ((wave + blk) & (WAVES - 1)) + WAVES; r < dr.passes; r += WAVES)
+                    dr.finish(dr.begin(r, (uint32_t)(n0 + 1 + it + dr.K), id, cp, lane), (blk + 1) & 1, rot_next, cp);
+            }
+            if (++sl == dr.K) {
+                sl = 0;
+                if ((blk + 2) % nb == 0 && wave == ((blk + 2) / nb & (WAVES - 1)))
+                    dr.rotations((uint32_t)(n0 + 2 + it + dr.K), id, cp, lane);
+                ++blk;
+                rot_next = rot_next + dr.K == dr.KR ? 0 : rot_next + dr.K;
+            }
+        }
+        // one wave's LDS operations complete in order: only the compiler must keep them so
+        if constexpr (WAVES == 1) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+
+    float off_out[3] = {s.off[0], s.off[1], s.off[2]};
+#pragma unroll
+    for (int i = 0; i < DIM; ++i) off_out[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(off_l), 1 + i));
+    if (tid == 0) {
+        DevContour o = s;
+        for (int i = 0; i < 3; ++i) {
+            o.anc[i] = anc[i];
+            o.off[i] = off_out[i];
+        }
+        o.R = R;
+        o.e_mc = e_mc;
+        o.iters = n0 + it;
+        o.status = (uint8_t)status;
+        o.streak = (uint8_t)streak;
+        *slot = o;
+        atomicAdd(counter, (unsigned long long)it);
+    }
 }
 
-template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT = false, bool STAGE = false, bool GRADI = false>
-hipError_t launch_t(const EvolveArgs &a, hipStream_t s) {
-    const size_t lds = sizeof(float) * ((size_t)lds_floats<DIM, G>(a.p.M / 2) + (STAGE ? (size_t)a.tile_cap : 0));
+// LDS of a sub-wave workgroup: the draws of each contour it holds.
+template <int G>
+__host__ __device__ __forceinline__ int sub_lds_floats(int MH) {
+    return Grp<G>::CPB * ((draw_floats(G, MH) + 3) & ~3);
+}
+
+// Waves per SIMD asked of the compiler (1: its choice). One pair-point in flight fits 64 vector registers (8
+// waves: a full CU of 4-wave groups holds 8 contours). FULL 3D instances with two in flight and no box: 93
+// registers, 5 waves (98 and 4 waves unasked; lattice 10.6 ms against 10.9). In 2D the compiler's 86 registers
+// (5 waves) are the best: 6 or 7 waves spill nothing but put more contours' footprints in the L2 than it
+// holds (8192^2 image 5.1 ms; 7 waves 5.3, 8 waves 6.2; 4 waves, held by LDS, 5.4). Two-wave groups with four
+// in flight: 128 registers, so 8 contours per CU stay resident. With a box the LDS holds 8 contours of
+// two waves per CU, so registers are left alone (109).
+template <int DIM, int G, int U, bool STAGE, bool GRADI, bool FULL>
+constexpr int waves_asked() {
+    if (G < 64) return 1;
+    if (U == 1) return 8;
+    if (U == 4) return G == 128 ? 4 : 1;
+    return DIM == 3 && FULL && !STAGE && !GRADI ? 5 : 1;
+}
+
+// STAGE: the workgroup's LDS ends with a box of a.tile_cap voxels. GRADI: centre force in its
+// image-gradient form. FULL: L = 16 and whole passes (full_passes).
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL>
+__global__ __launch_bounds__(Grp<G>::NT, (waves_asked<DIM, G, U, STAGE, GRADI, FULL>()))
+void evolve_kernel(EvolveArgs a) {
+    extern __shared__ __align__(16) float lds[];
+    if constexpr (G < 64) {
+        const int per = (draw_floats(G, a.p.M / 2) + 3) & ~3;
+        const int sub = (int)threadIdx.x / G;
+        const int k = blockIdx.x * Grp<G>::CPB + sub;
+        const int cid = k < a.n ? (a.idx ? a.idx[k] : k) : k;
+        DevContour *slot = k < a.n ? a.st + cid : nullptr;
+        run_group<DIM, G, U, TRACE, LAYOUT, EXACT>(a.p, slot, a.n_iter,
+                                                   TRACE && slot ? a.trace + (long)cid * SNK_TRACE_W : nullptr,
+                                                   lds + sub * per, a.counter);
+    } else {
+        const int cid = a.idx ? __builtin_amdgcn_readfirstlane(a.idx[blockIdx.x]) : (int)blockIdx.x;
+        // the arguments where the launch put them (EvolveArgs is the kernel's only argument, p its first member)
+        const Cold<EvolveArgs> ca = (Cold<EvolveArgs>)__builtin_amdgcn_kernarg_segment_ptr();
+        Repel rp{ca, cid, -1};
+        if (a.kappa > 0.0f) rp.cnt = __builtin_amdgcn_readfirstlane(a.nbn[cid]);
+        run_wave<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, FULL>(
+            a.p, (Cold<JobParams>)ca, a.st + cid, a.n_iter, 0x7fffffff,
+            TRACE ? a.trace + (long)cid * SNK_TRACE_W : nullptr, lds, a.draw_k, a.rot_k, a.counter,
+            STAGE ? a.tile_cap : 0, rp);
+    }
+}
+
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL>
+hipError_t launch_f(EvolveArgs a, hipStream_t s) {
+    size_t lds;
+    if constexpr (G >= 64) {
+        const DrawPlan d = draw_plan(DIM, a.p.M / 2);
+        a.draw_k = d.K;
+        a.rot_k = d.KR;
+        lds = wave_lds_bytes(G, EXACT ? 0 : wave_draw_floats(DIM, d.K, d.KR, a.p.M / 2), STAGE ? a.tile_cap : 0);
+    } else {
+        lds = sizeof(float) * (size_t)sub_lds_floats<G>(a.p.M / 2);
+    }
     const int blocks = (a.n + Grp<G>::CPB - 1) / Grp<G>::CPB;
-    hipLaunchKernelGGL((evolve_kernel<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI>), dim3(blocks),
+    hipLaunchKernelGGL((evolve_kernel<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, FULL>), dim3(blocks),
                        dim3(Grp<G>::NT), lds, s, a);
     return hipGetLastError();
+}
+
+// FULL instances where the sampling allows (they exist outside the per-iteration trace, whose sums have the
+// same order).
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT = false, bool STAGE = false, bool GRADI = false>
+hipError_t launch_t(const EvolveArgs &a, hipStream_t s) {
+    if constexpr (G >= 64 && U >= 2 && !TRACE && !EXACT)
+        if (full_passes(G, U, a.p.M, a.p.L))
+            return launch_f<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, true>(a, s);
+    return launch_f<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, false>(a, s);
 }
 
 }  // namespace

@@ -56,14 +56,14 @@ int stage_blocks_t(int layout) {
     hipError_t e;
     if (layout == kBufferQuad)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, evolve_kernel<DIM, G, U, false, kBufferQuad, false, true, false>, Grp<G>::NT, 0);
+            &nb, evolve_kernel<DIM, G, U, false, kBufferQuad, false, true, false, false>, Grp<G>::NT, 0);
     else if (DIM == 3 && layout == kBufferPair)
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, evolve_kernel<DIM, G, U, false, DIM == 3 ? kBufferPair : kBufferPlain, false, true, false>,
+            &nb, evolve_kernel<DIM, G, U, false, DIM == 3 ? kBufferPair : kBufferPlain, false, true, false, false>,
             Grp<G>::NT, 0);
     else
         e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, evolve_kernel<DIM, G, U, false, kBufferPlain, false, true, false>, Grp<G>::NT, 0);
+            &nb, evolve_kernel<DIM, G, U, false, kBufferPlain, false, true, false, false>, Grp<G>::NT, 0);
     return e == hipSuccess ? nb : 0;
 }
 

@@ -108,7 +108,46 @@ struct EvolveArgs {
     const int *nb, *nbn;         // nb_cap neighbour indices per contour (ascending), their counts
     int nb_cap;
     float kappa;
+    int draw_k, rot_k;           // draw plan of a whole-wave launch (set by the launcher)
 };
+
+// Draws of a whole-wave group held in LDS: pairs of two blocks of K iterations (4 floats each) and the
+// rotations of KR iterations, a multiple of K (9 floats each in 3D, 2 in 2D).
+struct DrawPlan {
+    int K, KR;
+};
+__host__ __device__ inline int wave_draw_floats(int dim, int K, int KR, int MH) {
+    return (8 * K * MH + KR * (dim == 3 ? 9 : 2) + 3) & ~3;
+}
+// LDS of a whole-wave workgroup: draws, the waves' partial sums (two sets of 8 floats per wave) and axis
+// records (32 floats per wave), the box. Up to a few hundred bytes over 64 KiB with the largest box that
+// evolve_lds_accepts takes; a workgroup may have 160 KiB.
+inline size_t wave_lds_bytes(int G, int draw_floats, int tile_cap) {
+    return sizeof(float) * ((size_t)draw_floats + (G > 64 ? G / 64 * 16 : 0) + G / 64 * 32 + (size_t)tile_cap);
+}
+// K: the smallest block (two iterations at least) whose passes of 64 draws are nearly full (within 15% of
+// MH / 64 per iteration), of those that take 8 KiB at most; KR: as many iterations as 32 (3D; 1.1 KiB) or 64
+// (2D) lanes draw in one pass.
+inline DrawPlan draw_plan(int dim, int MH) {
+    DrawPlan d{2, 2};
+    double best = 1e30;
+    for (int K = 2; K <= 16 && (K == 2 || 8 * K * MH <= 2048); ++K) {
+        const double cost = (double)((K * MH + 63) / 64) / K;
+        if (cost < best - 1e-9) {
+            best = cost;
+            d.K = K;
+        }
+        if (cost * 64.0 <= 1.15 * MH) {
+            d.K = K;
+            break;
+        }
+    }
+    const int r = dim == 3 ? 32 : 64;
+    d.KR = d.K * (r / d.K > 1 ? r / d.K : 1);
+    return d;
+}
+// Whether every pass of every lane holds U valid pair-points at one radial index.
+inline bool full_passes(int G, int U, int M, int L) { return L == 16 && (M / 2 * L) % (G * U) == 0; }
 
 // Neighbour lists of the soft repulsion (neighbours.hip): a grid of cell >= 2 rho r_max over the live
 // contours, then per ACTIVE contour the live contours whose inner sphere overlaps its own.
@@ -151,7 +190,8 @@ struct BatchArgs {
     int *queue;                  // work-queue head (persistent launch)
     int chunk;                   // iterations per contour in this launch
     unsigned long long *counter;
-    int max_D, max_M;
+    int max_D, max_M, L;
+    int draw_k, rot_k;           // draw plan (set by the launcher)
     int tile_cap;                // voxels of each workgroup's LDS box (0: corners read from the volumes)
 };
 
@@ -194,6 +234,9 @@ hipError_t launch_evolve_batch(const BatchArgs &a, int dim, int lanes, int unrol
 // Workgroups per CU of a batched launch shape (registers and LDS, including a box of tile_cap voxels).
 int evolve_batch_max_blocks(int dim, int lanes, int unroll, int layout, int max_M, int tile_cap);
 size_t evolve_lds_bytes(int dim, int lanes, int M, int tile_cap);
+// Whether a launch of that many rays and box voxels is accepted (64 KiB of LDS per workgroup by the
+// draw buffers' general size; the kernels take no more than that).
+bool evolve_lds_accepts(int dim, int lanes, int M, int tile_cap);
 // Star-shaped contours (one wave per contour, n_radial 16).
 hipError_t launch_star(const EvolveArgs &a, const StarArgs &sa, int dim, int lanes, int layout, hipStream_t s);
 size_t star_lds_bytes(int dim, int D, int M, int lanes);

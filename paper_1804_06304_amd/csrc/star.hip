@@ -65,10 +65,11 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
         Rb[D] = 0.0f;
     }
     const Vol<DIM, LAYOUT> vol(p.g);
+    const int nvol[3] = {p.g.nx, p.g.ny, p.g.nz};
     const float inv_h[3] = {p.g.inv_h[0], p.g.inv_h[1], p.g.inv_h[2]};
     const float hh[3] = {p.g.h[0], p.g.h[1], p.g.h[2]};
     const uint32_t id = s.id;
-    if (budget > 0) draws_phase1<DIM, NT>(dr, 0, (uint32_t)(n0 + 1), id, p, t);
+    if (budget > 0) draws_phase1<DIM, NT, false>(dr, 0, (uint32_t)(n0 + 1), id, p, t);
     __syncthreads();
     // largest radius (interior test) and the clamp flag of the radii
     float rmax = 0.0f;
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
 
     for (int it = 0; it < budget && (status & 0x0f) == SNK_ACTIVE; ++it) {
         const int blk = it / dr.K, sl = it - blk * dr.K;
-        if (sl == 0) draws_phase1<DIM, NT>(dr, (blk + 1) & 1, (uint32_t)(n0 + 1 + (blk + 1) * dr.K), id, p, t);
+        if (sl == 0) draws_phase1<DIM, NT, false>(dr, (blk + 1) & 1, (uint32_t)(n0 + 1 + (blk + 1) * dr.K), id, p, t);
         const float4 *pu = dr.pu + dr.slot(blk & 1, sl) * MH;
         Frame<DIM> fr;
         long base = 0;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
         for (int ax = 0; ax < DIM; ++ax) {
             base += (long)anc[ax] * stride[ax];
             const float ext = fmaf(ext_r * inv_h[ax], 1.0001f, 1e-3f);
-            interior = interior && (off[ax] - ext > (float)(-anc[ax])) && (off[ax] + ext < (float)(vol.n[ax] - 1 - anc[ax]));
+            interior = interior && (off[ax] - ext > (float)(-anc[ax])) && (off[ax] + ext < (float)(nvol[ax] - 1 - anc[ax]));
         }
         fr.base = base;
         // the ray pairs' tables entries, once per iteration (the pair-points below read them from LDS)
@@ -166,11 +167,11 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
                     for (int ax = 0; ax < DIM; ++ax) w[ax] = fmaf(sg ? -rad : rad, du[ax], off[ax]);
                     Rv[h][sg] = R;
                     if (interior)
-                        vol.load(locate<DIM, false, Vol<DIM, LAYOUT>::kSmall>(fr, vol.n, vol.nx, vol.nxy, w, fv[h][sg]),
-                                 cr[h][sg]);
+                        vol.load(locate<DIM, false, Vol<DIM, LAYOUT>::kSmall>(fr, nvol, vol.nx, vol.nxy, w, fv[h][sg]),
+                                 fr.base, cr[h][sg]);
                     else
-                        vol.load(locate<DIM, true, Vol<DIM, LAYOUT>::kSmall>(fr, vol.n, vol.nx, vol.nxy, w, fv[h][sg]),
-                                 cr[h][sg]);
+                        vol.load(locate<DIM, true, Vol<DIM, LAYOUT>::kSmall>(fr, nvol, vol.nx, vol.nxy, w, fv[h][sg]),
+                                 0, cr[h][sg]);
                 }
             }
 #pragma unroll
@@ -224,9 +225,9 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
         }
         float E = 0.0f, gc[3] = {0.0f, 0.0f, 0.0f};
         if constexpr (NW == 1) {
-            E = group_sum_wave<64>(accE);
+            E = wave_sum(accE);
 #pragma unroll
-            for (int ax = 0; ax < DIM; ++ax) gc[ax] = group_sum_wave<64>(accc[ax]);
+            for (int ax = 0; ax < DIM; ++ax) gc[ax] = wave_sum(accc[ax]);
         } else {
             const float wE = wave_sum_to_63(accE);
             float wc[3] = {0.0f, 0.0f, 0.0f};
@@ -366,7 +367,7 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
         clamped = __builtin_amdgcn_ballot_w64(clamped != 0) != 0;
         bool fin_r = __builtin_amdgcn_ballot_w64(!finite_r) == 0;
         if constexpr (NW == 1) {
-            sum = group_sum_wave<64>(sum);
+            sum = wave_sum(sum);
         } else {
             const float ws = wave_sum_to_63(sum);
             if (lane == 63) {
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
                     anc[ax] += (int)kk;
                     off[ax] -= kk;
                 }
-                if (off[ax] < (float)(-anc[ax]) || off[ax] > (float)(vol.n[ax] - 1 - anc[ax])) st = SNK_OUT;
+                if (off[ax] < (float)(-anc[ax]) || off[ax] > (float)(nvol[ax] - 1 - anc[ax])) st = SNK_OUT;
             }
         }
         if (st == SNK_ACTIVE) {
