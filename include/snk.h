@@ -230,8 +230,8 @@ snk_status snk_finalize(snk_ctx *ctx);
 
 /* snk_finalize for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc. Same kernels, same results as snk_finalize, but
- * the selection's scratch (grid cells, per-contour items, cells and decisions, counters) lives in a
- * static device array of the library, about 6 MB, that each GPU the library runs on holds until the
+ * the selection's scratch (grid cells, per-contour chains, cells, decisions and lists, counters) lives
+ * in a static device array of the library, about 8 MB, that each GPU the library runs on holds until the
  * process ends; the call itself calls no hipMalloc, hipFree or allocating library routine. Limits:
  * at most 131072 contours and 524288 cells of the selection grid (cell edge rho * r_max * 1.01 + 0.01
  * physical, widened until the grid has at most 4,194,304 cells); beyond them SNK_EINVAL and nothing

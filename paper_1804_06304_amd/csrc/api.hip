@@ -79,11 +79,11 @@ struct snk_ctx {
     float *d_trace = nullptr;
     size_t trace_cap = 0;
 
-    int *d_cell_start = nullptr, *d_cell_fill = nullptr, *d_items = nullptr, *d_cell_of = nullptr,
-        *d_dec = nullptr;
-    size_t grid_cap = 0, grid_fill_cap = 0, sel_cap = 0;
+    int *d_cell_start = nullptr, *d_items = nullptr, *d_cell_of = nullptr, *d_dec = nullptr, *d_sel_list = nullptr,
+        *d_sel_work = nullptr;
+    size_t grid_cap = 0, sel_cap = 0;
 
-    unsigned long long *d_counters = nullptr;  // [0] evolved, [1] kept, [2..3] selection round counters
+    unsigned long long *d_counters = nullptr;  // [0] evolved, [1] kept, [2..4] counters of the selection
     unsigned char *scratch = nullptr;  // this device's copy of the static selection scratch (no-alloc finalize)
     int *d_live = nullptr;             // snk_evolve_cull: indices of the active contours, then their count
     size_t live_cap = 0;
@@ -101,8 +101,8 @@ struct snk_ctx {
 };
 
 // Scratch of snk_finalize_noalloc, a static device array so that the call allocates nothing: the
-// selection counters (kept count and the grid-wide round counters), the cell starts and fills of
-// the uniform grid, and the per-contour item, cell and decision arrays. Every device the library
+// selection counters (kept count and those of the rounds), the chain heads of the uniform grid's cells, and
+// the per-contour chain, cell, decision, work and neighbour-list arrays. Every device the library
 // runs on holds one copy until the process ends; host code reaches it only through the address
 // hipGetSymbolAddress returns for that device (the array's name is a host-side stand-in).
 namespace {
@@ -110,12 +110,13 @@ constexpr int64_t kNoAllocMaxContours = (int64_t)1 << 17;
 constexpr int64_t kNoAllocMaxCells = (int64_t)1 << 19;
 constexpr size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 constexpr size_t kNaCounters = 0;                                                   // 4 x u64
-constexpr size_t kNaCellStart = 256;                                                // cells + 1 ints
-constexpr size_t kNaCellFill = kNaCellStart + align256((kNoAllocMaxCells + 1) * 4); // cells + 1 ints
-constexpr size_t kNaItems = kNaCellFill + align256((kNoAllocMaxCells + 1) * 4);     // contours ints
+constexpr size_t kNaCellStart = 256;                                                // a chain head per cell
+constexpr size_t kNaItems = kNaCellStart + align256((kNoAllocMaxCells + 1) * 4);    // contours ints
 constexpr size_t kNaCellOf = kNaItems + align256(kNoAllocMaxContours * 4);
 constexpr size_t kNaDec = kNaCellOf + align256(kNoAllocMaxContours * 4);
-constexpr size_t kNoAllocScratchBytes = kNaDec + align256(kNoAllocMaxContours * 4);
+constexpr size_t kNaWork = kNaDec + align256(kNoAllocMaxContours * 4);
+constexpr size_t kNaList = kNaWork + align256(kNoAllocMaxContours * 4);             // 8 ints per contour
+constexpr size_t kNoAllocScratchBytes = kNaList + align256(kNoAllocMaxContours * 32);
 constexpr int kMaxDevices = 64;
 }  // namespace
 
@@ -817,45 +818,37 @@ snk_status run_select(snk_ctx *c, int mode, int grace, bool noalloc = false) {
             return fail(c, SNK_EINVAL, "snk_finalize_noalloc: more than its maximum contours or grid cells");
         unsigned char *base = c->scratch;
         a.cell_start = reinterpret_cast<int *>(base + kNaCellStart);
-        a.cell_fill = reinterpret_cast<int *>(base + kNaCellFill);
         a.items = reinterpret_cast<int *>(base + kNaItems);
         a.cell_of = reinterpret_cast<int *>(base + kNaCellOf);
         a.dec = reinterpret_cast<int *>(base + kNaDec);
-        unsigned long long *counters = reinterpret_cast<unsigned long long *>(base + kNaCounters);
-        a.kept = counters;
-        // a fill kernel, not a memset node, so the call can also be captured in a graph
-        HIPTRY(c, snk::launch_zero(counters, 4, c->stream));
-        if (mode == 0) HIPTRY(c, snk::launch_energy_vox(a.p, a.st, a.e_vox, a.n, c->P.dim, true, c->stream));
-        if (mode == 2) HIPTRY(c, snk::launch_mark_maxiter(a.st, a.n, c->stream));
-        HIPTRY(c, snk::launch_select(a, c->P.dim, reinterpret_cast<int *>(counters + 2), c->stream));
+        a.kept = reinterpret_cast<unsigned long long *>(base + kNaCounters);
+        // every step a kernel, no memset, so the call can also be captured in a graph
+        HIPTRY(c, snk::launch_select(a, c->P.dim, reinterpret_cast<int *>(base + kNaList),
+                                     reinterpret_cast<int *>(base + kNaWork), c->stream));
         return SNK_OK;
     }
     st = ensure(c, &c->d_cell_start, &c->grid_cap, (size_t)G + 1);
     if (st != SNK_OK) return st;
-    st = ensure(c, &c->d_cell_fill, &c->grid_fill_cap, (size_t)G + 1);
-    if (st != SNK_OK) return st;
     if (c->sel_cap < (size_t)c->n) {
-        for (int **p : {&c->d_items, &c->d_cell_of, &c->d_dec}) {
+        for (int **p : {&c->d_items, &c->d_cell_of, &c->d_dec, &c->d_sel_list, &c->d_sel_work}) {
             if (*p) (void)hipFree(*p);
             *p = nullptr;
         }
-        size_t k1 = 0, k2 = 0, k3 = 0;
+        c->sel_cap = 0;
+        size_t k1 = 0, k2 = 0, k3 = 0, k4 = 0, k5 = 0;
         if ((st = ensure(c, &c->d_items, &k1, (size_t)c->n)) != SNK_OK) return st;
         if ((st = ensure(c, &c->d_cell_of, &k2, (size_t)c->n)) != SNK_OK) return st;
         if ((st = ensure(c, &c->d_dec, &k3, (size_t)c->n)) != SNK_OK) return st;
+        if ((st = ensure(c, &c->d_sel_list, &k4, snk::select_list_ints(c->n))) != SNK_OK) return st;
+        if ((st = ensure(c, &c->d_sel_work, &k5, (size_t)c->n)) != SNK_OK) return st;
         c->sel_cap = (size_t)c->n;
     }
     a.cell_start = c->d_cell_start;
-    a.cell_fill = c->d_cell_fill;
     a.items = c->d_items;
     a.cell_of = c->d_cell_of;
     a.dec = c->d_dec;
     a.kept = c->d_counters + 1;
-    HIPTRY(c, hipMemsetAsync(c->d_counters + 1, 0, sizeof(unsigned long long), c->stream));
-    // a culling pass ranks by the Monte-Carlo energy the last iteration left in the state
-    if (mode == 0) HIPTRY(c, snk::launch_energy_vox(a.p, a.st, a.e_vox, a.n, c->P.dim, true, c->stream));
-    if (mode == 2) HIPTRY(c, snk::launch_mark_maxiter(a.st, a.n, c->stream));
-    HIPTRY(c, snk::launch_select(a, c->P.dim, reinterpret_cast<int *>(c->d_counters + 2), c->stream));
+    HIPTRY(c, snk::launch_select(a, c->P.dim, c->d_sel_list, c->d_sel_work, c->stream));
     return SNK_OK;
 }
 
@@ -896,7 +889,7 @@ snk_status snk_create(snk_ctx **out, int device, void *hip_stream) {
         snk_destroy(c);
         return fail(nullptr, SNK_EDEVICE, std::string("hipEventCreate: ") + hipGetErrorString(e));
     }
-    e = hipMalloc(&c->d_counters, 4 * sizeof(unsigned long long));
+    e = hipMalloc(&c->d_counters, 8 * sizeof(unsigned long long));
     if (e != hipSuccess) {
         snk_destroy(c);
         return fail(nullptr, SNK_ENOMEM, "hipMalloc counters");
@@ -915,7 +908,7 @@ snk_status snk_destroy(snk_ctx *c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     void *bufs[] = {c->d_dirs, c->raw_owned, c->J, c->Jq, c->d_st, c->d_evox, c->d_trace, c->d_cell_start,
-                    c->d_cell_fill, c->d_items, c->d_cell_of, c->d_dec, c->d_counters, c->d_anti, c->d_nb,
+                    c->d_sel_list, c->d_sel_work, c->d_items, c->d_cell_of, c->d_dec, c->d_counters, c->d_anti, c->d_nb,
                     c->d_Rk, c->d_live, c->d_snap, c->d_nbgrid, c->d_nbitems, c->d_rnb};
     for (void *b : bufs)
         if (b) (void)hipFree(b);

@@ -5,15 +5,18 @@
 // divided by (2R)^d. FP32 terms, FP64 accumulation, fixed-order reduction. Contours still ACTIVE
 // become MAXITER here.
 //
-// Selection: one workgroup per job. Candidates (CONVERGED or MAXITER, E_vox <= E0) are binned on a
-// uniform grid with cell >= rho * r_max, so every overlapping pair (|c' - c''| < rho max(R', R''))
-// lies in neighbouring cells. Rounds of "accept a candidate whose (E_vox, id) is the smallest among
-// its undecided overlapping neighbours and that has no accepted overlapping neighbour; reject a
-// candidate with an accepted overlapping neighbour" run until nothing is undecided. An accepted
-// neighbour always has the smaller key, and the undecided candidate with the globally smallest key
-// is decided in every round, so the result equals the sequential greedy of the paper's competition
-// (lower energy survives) taken in ascending (E_vox, id) order.
+// Selection. Candidates (CONVERGED or MAXITER, E_vox <= E0) are binned on a uniform grid with cell
+// >= rho * r_max, so every overlapping pair (|c' - c''| < rho max(R', R'')) lies in neighbouring cells. A
+// candidate is accepted once every overlapping candidate with a smaller (E_vox, id) is rejected, and
+// rejected once one of them is accepted; that decides the smallest undecided candidate at every step, so the
+// result equals the sequential greedy of the paper's competition (lower energy survives) taken in ascending
+// (E_vox, id) order.
+//   One volume (select_plain): chains of contours per cell, each candidate's overlapping smaller candidates
+//   listed once, then rounds over the lists of those that have any.
+//   Batch (select_job): one workgroup per job, items sorted by cell, rounds that walk the cells again.
 #include <math.h>
+
+#include <algorithm>
 
 #include "snk_internal.h"
 
@@ -22,8 +25,6 @@ namespace snk {
 namespace {
 
 constexpr int SEL_T = 1024;
-constexpr int kSelectGridMin = 1024;   // contours above which the plain path bins and decides grid-wide
-constexpr int kSelectGridRounds = 6;   // grid-wide decision rounds before the single-workgroup finish
 
 // Threads per contour of the exact energy: a 3D ball holds thousands of lattice points, a disk
 // hundreds.
@@ -126,13 +127,6 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
 }
 
 template <int DIM>
-__global__ __launch_bounds__(ev_threads<DIM>()) void energy_vox_kernel(JobParams p, DevContour *st, double *e_vox,
-                                                                      int n, int finalize) {
-    const int cid = blockIdx.x;
-    if (cid < n) energy_one<DIM>(p, st + cid, e_vox + cid, finalize != 0);
-}
-
-template <int DIM>
 __global__ __launch_bounds__(ev_threads<DIM>()) void energy_vox_batch_kernel(const JobDev *jobs, const int2 *items,
                                                                             int n_items) {
     const int item = blockIdx.x;
@@ -206,29 +200,37 @@ __device__ int decide(const JobDev &a, int i) {
     return d;
 }
 
+// Whether contour i is a candidate of the selection (final: stopped contours at or below E0; culling
+// pass: live contours below its threshold, or all of them during the run's grace period, for which the host
+// passes a grace above every count, else 0).
+__device__ __forceinline__ bool is_candidate(const JobDev &a, const DevContour &s, double e) {
+    const int st = s.status & 0x0f;
+    return a.mode != 1 ? (st == SNK_CONVERGED || st == SNK_MAXITER) && isfinite(e) && e <= (double)a.e0
+                       : (st == SNK_ACTIVE || st == SNK_CONVERGED) && isfinite(e) &&
+                             (s.iters < a.grace || e <= (double)a.e_cull);
+}
+
+template <int DIM>
+__device__ __forceinline__ int grid_cell(const JobDev &a, const DevContour &s) {
+    int gi[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) {
+        const float pk = ((float)s.anc[k] + s.off[k]) * a.p.g.h[k];
+        gi[k] = min(max((int)floorf(pk / a.cell), 0), a.G[k] - 1);
+    }
+    return (gi[2] * a.G[1] + gi[1]) * a.G[0] + gi[0];
+}
+
 // Candidate flag and grid cell of contour i; counts the cell's members in cell_start[cell + 1].
 template <int DIM>
 __device__ __forceinline__ void bin_one(const JobDev &a, int i) {
-    const Geometry &g = a.p.g;
     const DevContour s = a.st[i];
-    const int st = s.status & 0x0f;
-    const double e = rank_energy(a, i, s);
-    // final selection: stopped contours at or below E0; culling pass: live contours below E0, or all
-    // of them during the run's grace period (the host passes a grace above every count then, else 0)
-    const bool cand = a.mode != 1 ? (st == SNK_CONVERGED || st == SNK_MAXITER) && isfinite(e) && e <= (double)a.e0
-                                  : (st == SNK_ACTIVE || st == SNK_CONVERGED) && isfinite(e) &&
-                                        (s.iters < a.grace || e <= (double)a.e_cull);
+    const bool cand = is_candidate(a, s, rank_energy(a, i, s));
     // a culling pass without competition keeps every candidate
     a.dec[i] = cand ? (a.mode == 1 && !a.compete ? DEC_ACCEPT : DEC_UNDECIDED) : DEC_NONE;
     int cell = -1;
     if (cand) {
-        int gi[3] = {0, 0, 0};
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-            const float pk = ((float)s.anc[k] + s.off[k]) * g.h[k];
-            gi[k] = min(max((int)floorf(pk / a.cell), 0), a.G[k] - 1);
-        }
-        cell = (gi[2] * a.G[1] + gi[1]) * a.G[0] + gi[0];
+        cell = grid_cell<DIM>(a, s);
         atomicAdd(&a.cell_start[cell + 1], 1);
     }
     a.cell_of[i] = cell;
@@ -314,135 +316,222 @@ __device__ __forceinline__ int apply_one(const JobDev &a, int i, int d) {
     return 0;
 }
 
-// Whole selection of one job by one workgroup. binned: the grid (cell_start, items, cell_of, dec)
-// was already built and some decisions may already be taken; then a scan of the decisions decides
-// whether the decision loop is needed at all. apply = false leaves the outcome to sel_apply_kernel.
+// Whole selection of one job by one workgroup.
 template <int DIM>
-__device__ void select_job(const JobDev &a, bool binned, bool apply = true) {
-    __shared__ int chunk_sum[SEL_T];
+__device__ void select_job(const JobDev &a) {
+    __shared__ int ws[SEL_T / 64 + 1];
     const int t = threadIdx.x;
     const int n = a.n;
     const int G = a.G[0] * a.G[1] * a.G[2];
     volatile int *dec = a.dec;
-    if (!binned) {
-        for (int c = t; c <= G; c += SEL_T) a.cell_start[c] = 0;
-        for (int c = t; c < G; c += SEL_T) a.cell_fill[c] = 0;
-        __syncthreads();
-        for (int i = t; i < n; i += SEL_T) bin_one<DIM>(a, i);
-        __syncthreads();
-        scan_cells(a, G, chunk_sum);
-        __syncthreads();
-        for (int i = t; i < n; i += SEL_T) scatter_one(a, i);
-        __syncthreads();
-    }
+    for (int c = t; c <= G; c += SEL_T) a.cell_start[c] = 0;
+    for (int c = t; c < G; c += SEL_T) a.cell_fill[c] = 0;
+    __syncthreads();
+    for (int i = t; i < n; i += SEL_T) bin_one<DIM>(a, i);
+    __syncthreads();
+    scan_cells(a, G, ws);
+    __syncthreads();
+    for (int i = t; i < n; i += SEL_T) scatter_one(a, i);
+    __syncthreads();
     bool any = true;
-    if (binned) {
-        // no decision is written while this scan runs, so plain loads (issued back to back) serve
-        const int *dn = a.dec;
-        int local = 0;
-#pragma unroll 8
-        for (int i = t; i < n; i += SEL_T) local |= dn[i] == DEC_UNDECIDED ? 1 : 0;
-        any = __syncthreads_or(local) != 0;
-    }
     while (any) {
         int local = 0;
         for (int i = t; i < n; i += SEL_T) local |= decide<DIM>(a, i) == DEC_UNDECIDED ? 1 : 0;
         __threadfence_block();
         any = __syncthreads_or(local) != 0;
     }
-    if (!apply) return;
     unsigned long long count = 0;
     for (int i = t; i < n; i += SEL_T) count += apply_one(a, i, dec[i]);
     if (count) atomicAdd(a.kept, count);
 }
 
 template <int DIM>
-__global__ __launch_bounds__(SEL_T) void select_kernel(JobDev j, int binned, int apply) {
-    if (j.n > 0) select_job<DIM>(j, binned != 0, apply != 0);
-}
-
-template <int DIM>
 __global__ __launch_bounds__(SEL_T) void select_batch_kernel(const JobDev *jobs, const int *job_list, int n_jobs) {
     if ((int)blockIdx.x >= n_jobs) return;
     const JobDev &j = jobs[__builtin_amdgcn_readfirstlane(job_list[blockIdx.x])];
-    if (j.n > 0) select_job<DIM>(j, false);
+    if (j.n > 0) select_job<DIM>(j);
 }
 
-// Grid-wide selection steps for one job with many contours (the single-workgroup loop above then
-// finishes whatever the rounds left undecided).
+// ---------------------------------------------------------------------------------------------
+// Selection of one volume
+// ---------------------------------------------------------------------------------------------
+//
+// Bound by latency: a few thousand contours are a few hundred waves, and each step waits for the one before.
+// So the steps are few and wide: (1) clear the cells' chain heads; (2) link every candidate into its cell's
+// chain, at the end of the kernel that finishes it (exact energy, or the end of evolution); (3) a group
+// of lanes per candidate, one per neighbouring cell, walks the chains and lists the overlapping candidates
+// with a smaller key: none, as for most, accepts at once, the others join the work list; (4) rounds over the
+// work list, which read only the listed candidates' decisions; (5) the outcome. With up to kOneGroup
+// contours one workgroup does (4) and (5). Finalize, before -> now (the exact energy of 55 us in the first,
+// none in the second, 715 in the third): 2,000 contours 147 -> 71 us, 600 star contours 59 -> 17, 62,500 lattice
+// contours 808 -> 754 (one workgroup, above 1,024 contours 14 launches, sorted the cells and re-walked them
+// every round); 9,000 contours with hundreds of overlaps each 2.5 -> 0.49 ms.
 constexpr int SG_T = 256;
+// Contours whose outcome one workgroup writes: 8 per thread; a launch more costs about as much as 8 more.
+constexpr int kOneGroup = 8192;
+// A candidate's list: its length, then up to 7 indices (two 16-byte loads); a longer one walks its cells again.
+constexpr int kSelList = 8;
+// Contours above which grid-wide rounds come before the one-workgroup rounds: 32 candidates a step, one
+// workgroup takes a thousand in the time of a few launches.
+constexpr int kSelRounds = 1024;
 
-__global__ __launch_bounds__(SG_T) void sel_zero_kernel(JobDev a, int G, int *rounds) {
+__global__ __launch_bounds__(SG_T) void sel_clear_kernel(JobDev a, int G) {
     const int i = blockIdx.x * SG_T + threadIdx.x;
-    if (i <= G) a.cell_start[i] = 0;
-    if (i < G) a.cell_fill[i] = 0;
-    if (i < 3) rounds[i] = 0;
+    if (i < G) a.cell_start[i] = 0;
+    if (i < 4) a.kept[i] = 0;   // kept, work-list length and the rounds' counters (launch_select)
 }
 
+// Links contour i (its final state s, ranking energy e) into its cell's chain if it competes.
 template <int DIM>
-__global__ __launch_bounds__(SG_T) void sel_bin_kernel(JobDev a) {
-    const int i = blockIdx.x * SG_T + threadIdx.x;
-    if (i < a.n) bin_one<DIM>(a, i);
-}
-
-__global__ __launch_bounds__(SEL_T) void sel_scan_kernel(JobDev a, int G) {
-    __shared__ int chunk_sum[SEL_T];
-    scan_cells(a, G, chunk_sum);
-}
-
-// The same running sum by one workgroup per tile, for grids of several tiles: (1) each tile's own
-// running sum, its total parked in cell_fill[tile] (zero until the scatter counts in it); (2) one
-// workgroup turns the totals into each tile's offset; (3) each tile adds its offset and puts the
-// zero back in cell_fill[tile].
-__global__ __launch_bounds__(SEL_T) void sel_scan_tiles_kernel(JobDev a, int G) {
-    __shared__ int ws[SEL_T / 64 + 1];
-    const int total = scan_tile(a.cell_start + 1, G, blockIdx.x * SCAN_TILE, 0, ws);
-    if (threadIdx.x == 0) a.cell_fill[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(SEL_T) void sel_scan_totals_kernel(JobDev a, int ntiles) {
-    __shared__ int ws[SEL_T / 64 + 1];
-    // ntiles <= SEL_T * 8: one tile of totals; inclusive, then shifted to the exclusive offsets
-    const int t = threadIdx.x;
-    int own[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) own[k] = t * 8 + k < ntiles ? a.cell_fill[t * 8 + k] : 0;
-    __syncthreads();
-    scan_tile(a.cell_fill, ntiles, 0, 0, ws);
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        if (t * 8 + k < ntiles) a.cell_fill[t * 8 + k] -= own[k];
-}
-
-__global__ __launch_bounds__(SEL_T) void sel_scan_add_kernel(JobDev a, int G) {
-    __shared__ int off_sh;
-    if (threadIdx.x == 0) {
-        off_sh = a.cell_fill[blockIdx.x];
-        a.cell_fill[blockIdx.x] = 0;
+__device__ __forceinline__ void link_one(const JobDev &a, int i, const DevContour &s, double e) {
+    const bool cand = is_candidate(a, s, e);
+    a.dec[i] = cand ? DEC_UNDECIDED : DEC_NONE;
+    if (cand) {
+        const int cell = grid_cell<DIM>(a, s);
+        a.cell_of[i] = cell;
+        a.items[i] = atomicExch(&a.cell_start[cell], i + 1);   // chain heads hold index + 1
     }
-    __syncthreads();
-    const int off = off_sh;
-    if (off == 0) return;
-    int *cs = a.cell_start + 1;
-    const int base = blockIdx.x * SCAN_TILE;
-    for (int i = base + (int)threadIdx.x; i < min(base + SCAN_TILE, G); i += SEL_T) cs[i] += off;
 }
 
-__global__ __launch_bounds__(SG_T) void sel_scatter_kernel(JobDev a) {
-    const int i = blockIdx.x * SG_T + threadIdx.x;
-    if (i < a.n) scatter_one(a, i);
-}
-
-// Round r: skipped when round r-1 left nothing undecided; counts what it leaves undecided in
-// rounds[r % 3] and clears rounds[(r + 1) % 3] for the next round.
 template <int DIM>
-__global__ __launch_bounds__(SG_T) void sel_round_kernel(JobDev a, int r, int *rounds) {
-    if (r > 0 && *(volatile int *)&rounds[(r + 2) % 3] == 0) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) rounds[(r + 1) % 3] = 0;
-    const int i = blockIdx.x * SG_T + threadIdx.x;
-    int left = 0;
-    if (i < a.n) left = decide<DIM>(a, i) == DEC_UNDECIDED ? 1 : 0;
-    if (__builtin_amdgcn_ballot_w64(left != 0) != 0 && (threadIdx.x & 63) == 0) atomicAdd(&rounds[r % 3], 1);
+constexpr int sel_lanes() {
+    return DIM == 3 ? 32 : 16;   // at least 3^DIM
+}
+
+// Lanes per candidate walk the cells around it in step. Each overlapping candidate with a smaller key is
+// handed to visit(j, hit) by every lane of the group together (hit false where a lane has none); the walk
+// ends when visit returns true.
+template <int DIM, typename F>
+__device__ __forceinline__ void walk_smaller(const JobDev &a, int i, int sub, F visit) {
+    const DevContour si = a.st[i];
+    const double ei = rank_energy(a, i, si);
+    const int cell = a.cell_of[i];
+    int next = 0;
+    if (sub < (DIM == 3 ? 27 : 9)) {
+        const int cx = cell % a.G[0] + sub % 3 - 1, cy = (cell / a.G[0]) % a.G[1] + sub / 3 % 3 - 1,
+                  cz = DIM == 3 ? cell / (a.G[0] * a.G[1]) + sub / 9 - 1 : 0;
+        if (cx >= 0 && cy >= 0 && cz >= 0 && cx < a.G[0] && cy < a.G[1] && cz < a.G[2])
+            next = a.cell_start[(cz * a.G[1] + cy) * a.G[0] + cx];
+    }
+    constexpr int LN = sel_lanes<DIM>();
+    const int lane = threadIdx.x & 63;
+    const uint64_t group = ((1ull << LN) - 1) << (lane & ~(LN - 1));
+    while ((__builtin_amdgcn_ballot_w64(next != 0) & group) != 0) {
+        const int j = next - 1;
+        bool hit = false;
+        if (next != 0) {
+            next = a.items[j];
+            if (j != i) {
+                const DevContour sj = a.st[j];
+                if (overlaps<DIM>(si, sj, a.p.g.h)) {
+                    const double ej = rank_energy(a, j, sj);
+                    hit = ej < ei || (ej == ei && sj.id < si.id);
+                }
+            }
+        }
+        if (visit(j, hit, group)) break;
+    }
+}
+
+// Step 3.
+template <int DIM>
+__global__ __launch_bounds__(SG_T) void sel_list_kernel(JobDev a, int *list, int *work, int *m) {
+    constexpr int LN = sel_lanes<DIM>();
+    const int i = (int)(((long)blockIdx.x * SG_T + threadIdx.x) / LN), sub = threadIdx.x & (LN - 1);
+    if (i >= a.n || a.dec[i] != DEC_UNDECIDED) return;   // whole groups
+    int *mine = list + (long)i * kSelList;
+    int total = 0;
+    const int lane = threadIdx.x & 63;
+    walk_smaller<DIM>(a, i, sub, [&](int j, bool hit, uint64_t group) {
+        const uint64_t h = __builtin_amdgcn_ballot_w64(hit) & group;
+        const int pos = total + __builtin_popcountll(h & ((1ull << lane) - 1ull));
+        if (hit && pos + 1 < kSelList) mine[1 + pos] = j;
+        total += __builtin_popcountll(h);
+        return false;
+    });
+    if (sub == 0) {
+        if (total == 0) {
+            // no other lane reads this decision in this launch
+            a.dec[i] = DEC_ACCEPT;
+        } else {
+            mine[0] = total;
+            work[atomicAdd(m, 1)] = i;
+        }
+    }
+}
+
+// A decision that other waves may be taking: a value read early only delays the reader's own decision.
+template <int SCOPE>
+__device__ __forceinline__ int decision(const JobDev &a, int i) {
+    return __hip_atomic_load(a.dec + i, __ATOMIC_RELAXED, SCOPE);
+}
+
+// One decision step of candidate i by a group of lanes (every decision taken is final and correct whatever
+// the others do meanwhile): accepted neighbour -> reject; none undecided -> accept. Returns whether it
+// stays undecided. SCOPE: of the waves that decide concurrently.
+template <int DIM, int SCOPE>
+__device__ __forceinline__ bool decide_group(const JobDev &a, const int *list, int i, int sub) {
+    const int *mine = list + (long)i * kSelList;
+    const int cnt = mine[0];
+    bool accepted = false, open = false;
+    if (cnt < kSelList) {
+        const int d = sub < cnt ? decision<SCOPE>(a, mine[1 + sub]) : (int)DEC_REJECT;
+        const uint64_t group = ((1ull << sel_lanes<DIM>()) - 1) << ((threadIdx.x & 63) & ~(sel_lanes<DIM>() - 1));
+        accepted = (__builtin_amdgcn_ballot_w64(d == DEC_ACCEPT) & group) != 0;
+        open = (__builtin_amdgcn_ballot_w64(d == DEC_UNDECIDED) & group) != 0;
+    } else {
+        walk_smaller<DIM>(a, i, sub, [&](int j, bool hit, uint64_t group) {
+            const int d = hit ? decision<SCOPE>(a, j) : (int)DEC_REJECT;
+            accepted = accepted || (__builtin_amdgcn_ballot_w64(d == DEC_ACCEPT) & group) != 0;
+            open = open || (__builtin_amdgcn_ballot_w64(d == DEC_UNDECIDED) & group) != 0;
+            return accepted;
+        });
+    }
+    if (sub == 0 && (accepted || !open))
+        __hip_atomic_store(a.dec + i, accepted ? (int)DEC_REJECT : (int)DEC_ACCEPT, __ATOMIC_RELAXED, SCOPE);
+    return !accepted && open;
+}
+
+// Step 4, grid-wide. Round r: skipped when round r - 1 left nothing undecided; counts what it leaves
+// undecided in left[r % 3] and clears left[(r + 1) % 3] for the next round.
+template <int DIM>
+__global__ __launch_bounds__(SG_T) void sel_round_kernel(JobDev a, const int *list, const int *work, const int *m, int r,
+                                                         int *left) {
+    if (r > 0 && *(volatile int *)&left[(r + 2) % 3] == 0) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) left[(r + 1) % 3] = 0;
+    constexpr int LN = sel_lanes<DIM>();
+    const int k = (int)(((long)blockIdx.x * SG_T + threadIdx.x) / LN), sub = threadIdx.x & (LN - 1);
+    if (k >= *m) return;   // whole groups
+    const int i = work[k];
+    if (__shfl(decision<__HIP_MEMORY_SCOPE_AGENT>(a, i), 0, LN) != DEC_UNDECIDED) return;
+    if (decide_group<DIM, __HIP_MEMORY_SCOPE_AGENT>(a, list, i, sub) && sub == 0) atomicAdd(&left[r % 3], 1);
+}
+
+// Steps 4 and 5 by one workgroup: rounds until nothing on the work list is undecided, then (apply) the outcome
+// of every contour.
+template <int DIM>
+__global__ __launch_bounds__(SEL_T) void sel_finish_kernel(JobDev a, const int *list, const int *work, const int *mp,
+                                                           int apply) {
+    constexpr int LN = sel_lanes<DIM>();
+    const int t = threadIdx.x, sub = t & (LN - 1);
+    const int m = *mp;
+    constexpr int SCOPE = __HIP_MEMORY_SCOPE_WORKGROUP;
+    bool any = m > 0;
+    while (any) {
+        int local = 0;
+        for (int k = t / LN; k < m; k += SEL_T / LN) {
+            const int i = work[k];
+            if (__shfl(decision<SCOPE>(a, i), 0, LN) == DEC_UNDECIDED)
+                local |= decide_group<DIM, SCOPE>(a, list, i, sub) ? 1 : 0;
+        }
+        __threadfence_block();
+        any = __syncthreads_or(local) != 0;
+    }
+    if (!apply) return;
+    int count = 0;
+    for (int i = t; i < a.n; i += SEL_T) count += apply_one(a, i, decision<SCOPE>(a, i));
+    for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, 64);
+    if ((t & 63) == 0 && count) atomicAdd(a.kept, (unsigned long long)count);
 }
 
 // The outcome of every decision, grid-wide (after the decisions are complete).
@@ -453,37 +542,72 @@ __global__ __launch_bounds__(SG_T) void sel_apply_kernel(JobDev a) {
     if (threadIdx.x == 0 && total) atomicAdd(a.kept, (unsigned long long)total);
 }
 
+// Step 2 where no exact energy is formed: contours still ACTIVE become MAXITER (mode 2), candidates are linked.
 template <int DIM>
-hipError_t select_grid(const JobDev &j, int *rounds, hipStream_t s) {
+__global__ __launch_bounds__(SG_T) void sel_link_kernel(JobDev a) {
+    const int i = blockIdx.x * SG_T + threadIdx.x;
+    if (i >= a.n) return;
+    DevContour s = a.st[i];
+    if (a.mode == 2 && (s.status & 0x0f) == SNK_ACTIVE) {
+        s.status = (uint8_t)((s.status & SNK_CLAMPED) | SNK_MAXITER);
+        a.st[i].status = s.status;
+    }
+    link_one<DIM>(a, i, s, rank_energy(a, i, s));
+}
+
+// A culling pass without competition judges each contour alone.
+__global__ __launch_bounds__(SG_T) void cull_alone_kernel(JobDev a) {
+    const int i = blockIdx.x * SG_T + threadIdx.x;
+    int c = 0;
+    if (i < a.n) {
+        const DevContour s = a.st[i];
+        c = apply_one(a, i, is_candidate(a, s, (double)s.e_mc) ? DEC_ACCEPT : DEC_NONE);
+    }
+    const int total = __syncthreads_count(c);
+    if (threadIdx.x == 0 && total) atomicAdd(a.kept, (unsigned long long)total);
+}
+
+template <int DIM>
+__global__ __launch_bounds__(ev_threads<DIM>()) void energy_link_kernel(JobDev a) {
+    const int cid = blockIdx.x;
+    energy_one<DIM>(a.p, a.st + cid, a.e_vox + cid, true);
+    if (threadIdx.x == 0) {
+        // this thread wrote the state and energy it reads here
+        const DevContour s = a.st[cid];
+        link_one<DIM>(a, cid, s, a.e_vox[cid]);
+    }
+}
+
+template <int DIM>
+hipError_t select_plain(const JobDev &j, int *list, int *work, hipStream_t s) {
     const int G = j.G[0] * j.G[1] * j.G[2];
     const int bn = (j.n + SG_T - 1) / SG_T;
-    hipLaunchKernelGGL(sel_zero_kernel, dim3((G + 1 + SG_T - 1) / SG_T), dim3(SG_T), 0, s, j, G, rounds);
-    hipLaunchKernelGGL(sel_bin_kernel<DIM>, dim3(bn), dim3(SG_T), 0, s, j);
-    // one workgroup walks up to three tiles faster than three launches take (about 8 us per tile
-    // against about 20 us for the tile, totals and add kernels together)
-    const int ntiles = (G + SCAN_TILE - 1) / SCAN_TILE;
-    if (ntiles <= 3) {
-        hipLaunchKernelGGL(sel_scan_kernel, dim3(1), dim3(SEL_T), 0, s, j, G);
-    } else {
-        hipLaunchKernelGGL(sel_scan_tiles_kernel, dim3(ntiles), dim3(SEL_T), 0, s, j, G);
-        hipLaunchKernelGGL(sel_scan_totals_kernel, dim3(1), dim3(SEL_T), 0, s, j, ntiles);
-        hipLaunchKernelGGL(sel_scan_add_kernel, dim3(ntiles), dim3(SEL_T), 0, s, j, G);
+    // kept counter, then three more 64-bit words: work-list length and the rounds' three counters
+    int *m = reinterpret_cast<int *>(j.kept + 1);
+    int *left = m + 1;
+    const bool alone = j.mode == 1 && !j.compete;
+    hipLaunchKernelGGL(sel_clear_kernel, dim3(alone ? 1 : (std::max(G, 4) + SG_T - 1) / SG_T), dim3(SG_T), 0, s, j,
+                       alone ? 0 : G);
+    if (alone) {
+        hipLaunchKernelGGL(cull_alone_kernel, dim3(bn), dim3(SG_T), 0, s, j);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(sel_scatter_kernel, dim3(bn), dim3(SG_T), 0, s, j);
-    for (int r = 0; r < kSelectGridRounds; ++r)
-        hipLaunchKernelGGL(sel_round_kernel<DIM>, dim3(bn), dim3(SG_T), 0, s, j, r, rounds);
-    hipLaunchKernelGGL(select_kernel<DIM>, dim3(1), dim3(SEL_T), 0, s, j, 1, 0);
-    hipLaunchKernelGGL(sel_apply_kernel, dim3(bn), dim3(SG_T), 0, s, j);
+    if (j.mode == 0)
+        hipLaunchKernelGGL(energy_link_kernel<DIM>, dim3(j.n), dim3(ev_threads<DIM>()), 0, s, j);
+    else
+        hipLaunchKernelGGL(sel_link_kernel<DIM>, dim3(bn), dim3(SG_T), 0, s, j);
+    constexpr int per = SG_T / sel_lanes<DIM>();
+    const int bg = (j.n + per - 1) / per;
+    hipLaunchKernelGGL(sel_list_kernel<DIM>, dim3(bg), dim3(SG_T), 0, s, j, list, work, m);
+    const int rounds = j.n > kOneGroup ? 6 : (j.n > kSelRounds ? 2 : 0);
+    for (int r = 0; r < rounds; ++r)
+        hipLaunchKernelGGL(sel_round_kernel<DIM>, dim3(bg), dim3(SG_T), 0, s, j, list, work, m, r, left);
+    const bool apply = j.n <= kOneGroup;
+    hipLaunchKernelGGL(sel_finish_kernel<DIM>, dim3(1), dim3(SEL_T), 0, s, j, list, work, m, apply ? 1 : 0);
+    if (!apply) hipLaunchKernelGGL(sel_apply_kernel, dim3(bn), dim3(SG_T), 0, s, j);
     return hipGetLastError();
 }
 
-}  // namespace
-
-namespace {
-__global__ __launch_bounds__(256) void mark_maxiter_kernel(DevContour *st, int n) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n && (st[i].status & 0x0f) == SNK_ACTIVE) st[i].status = (uint8_t)((st[i].status & SNK_CLAMPED) | SNK_MAXITER);
-}
 }  // namespace
 
 namespace {
@@ -506,28 +630,12 @@ hipError_t launch_compact_active(const DevContour *st, int n, int *idx, int *cou
     return hipGetLastError();
 }
 
-hipError_t launch_mark_maxiter(DevContour *st, int n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(mark_maxiter_kernel, dim3((n + 255) / 256), dim3(256), 0, s, st, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_energy_vox(const JobParams &p, DevContour *st, double *e_vox, int n, int dim, bool finalize,
-                             hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int f = finalize ? 1 : 0;
-    if (dim == 2) hipLaunchKernelGGL(energy_vox_kernel<2>, dim3(n), dim3(ev_threads<2>()), 0, s, p, st, e_vox, n, f);
-    else hipLaunchKernelGGL(energy_vox_kernel<3>, dim3(n), dim3(ev_threads<3>()), 0, s, p, st, e_vox, n, f);
-    return hipGetLastError();
-}
-
-hipError_t launch_select(const JobDev &j, int dim, int *rounds, hipStream_t s) {
+hipError_t launch_select(const JobDev &j, int dim, int *list, int *work, hipStream_t s) {
     if (j.n <= 0) return hipSuccess;
-    if (j.n > kSelectGridMin && rounds) return dim == 2 ? select_grid<2>(j, rounds, s) : select_grid<3>(j, rounds, s);
-    if (dim == 2) hipLaunchKernelGGL(select_kernel<2>, dim3(1), dim3(SEL_T), 0, s, j, 0, 1);
-    else hipLaunchKernelGGL(select_kernel<3>, dim3(1), dim3(SEL_T), 0, s, j, 0, 1);
-    return hipGetLastError();
+    return dim == 2 ? select_plain<2>(j, list, work, s) : select_plain<3>(j, list, work, s);
 }
+
+size_t select_list_ints(int64_t n) { return (size_t)n * kSelList; }
 
 hipError_t launch_energy_vox_batch(const JobDev *jobs, const int2 *items, int n_items, int dim, hipStream_t s) {
     if (n_items <= 0) return hipSuccess;

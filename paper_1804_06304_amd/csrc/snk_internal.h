@@ -250,17 +250,15 @@ hipError_t launch_reset_items(const JobDev *jobs, const int2 *items, int n_items
                               hipStream_t s);
 hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s);
 hipError_t launch_count_unfinished(const JobDev *jobs, const int2 *items, int n_items, int *unfinished, hipStream_t s);
-// finalize: contours still ACTIVE become MAXITER and E_vox is stored in the state (else only in
-// e_vox).
-hipError_t launch_energy_vox(const JobParams &p, DevContour *st, double *e_vox, int n, int dim, bool finalize,
-                             hipStream_t s);
-// Contours still ACTIVE become MAXITER (the end of evolution without the exact energy).
-hipError_t launch_mark_maxiter(DevContour *st, int n, hipStream_t s);
 // Indices of the ACTIVE contours among st[0..n-1] into idx, their number into *count (which must be
 // zero beforehand); the order of the indices is unspecified.
 hipError_t launch_compact_active(const DevContour *st, int n, int *idx, int *count, hipStream_t s);
-// rounds: 3 ints of device scratch for the grid-wide rounds (null: one workgroup does everything).
-hipError_t launch_select(const JobDev &j, int dim, int *rounds, hipStream_t s);
+// Selection of one volume: the end of evolution (mode 0: exact energies, ACTIVE contours become MAXITER; mode
+// 2: MAXITER only) or a culling pass (mode 1), and its outcome. Device scratch: j.cell_start one int per grid
+// cell, j.items, j.cell_of and j.dec one per contour, list select_list_ints(n), work one per contour;
+// j.kept is the first of four 64-bit words, all written (kept, then counters).
+hipError_t launch_select(const JobDev &j, int dim, int *list, int *work, hipStream_t s);
+size_t select_list_ints(int64_t n);
 hipError_t launch_energy_vox_batch(const JobDev *jobs, const int2 *items, int n_items, int dim, hipStream_t s);
 hipError_t launch_select_batch(const JobDev *jobs, const int *job_list, int n_jobs, int dim, hipStream_t s);
 

@@ -1,0 +1,75 @@
+"""Selection of one volume: the outcome of the competition at the edges of its kernels' sizes.
+
+The paper's competition taken in ascending (E_vox, id) order is characterised by two properties, checked
+here in FP64 on what the call returns: no two kept contours overlap, and every candidate that is not kept
+overlaps a kept one of smaller or equal energy. Pairs within 1e-4 of touching are left out (the kernels
+measure distances in FP32: coordinates below 1,024 with offsets below 1 and radii below 10 err by less
+than 1e-5), and energies compare with the FP32 rounding of the readback (2^-23 relative).
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(dim, n, shape, r, noalloc=False):
+    from paper_1804_06304_amd import snk
+    rng = np.random.default_rng(n + dim)
+    raw = rng.integers(0, 200, shape).astype(np.uint8)
+    D = 64 if dim == 2 else 162
+    p = synth.Params(dim=dim, r_max=10.0, r_init=r[0], n_dirs=D, i_scale=1 / 160.0, e0=1.0)
+    ctx = snk.Context(0)
+    ctx.set_params(p)
+    ctx.set_directions(synth.directions_for(dim, D))
+    ctx.load_volume(raw)
+    top = np.array(shape[::-1]) - 1.0
+    cen = rng.uniform(0, 1, (n, 3)) * top
+    cen[:, dim:] = 0.0
+    status = np.full(n, 2, np.uint8)
+    status[5::19] = 3           # OUT: never a candidate
+    status[7::23] = 0           # ACTIVE: becomes MAXITER
+    ctx.load_seeds(cen)
+    ctx.set_state(cen, rng.uniform(*r, n).astype(np.float32), np.full(n, 3, np.int32), status)
+    ctx.prepass()
+    (ctx.finalize_noalloc if noalloc else ctx.finalize)()
+    out = ctx.read()
+    ctx.close()
+    return out, status
+
+
+def _check(dim, out, status):
+    rho = 2.0 ** (-1.0 / dim)
+    c, R, e = out["centers"], out["radii"].astype(np.float64), out["e_vox"].astype(np.float64)
+    cand = status != 3
+    assert np.all(out["status"][status == 0] == 2)
+    kept = out["keep"] == 1
+    assert not np.any(kept & ~cand)
+    k = np.where(kept)[0]
+    assert len(k) > 0
+    beaten = np.zeros(len(c), bool)
+    for i in range(0, len(c), 512):
+        d = np.linalg.norm(c[i:i + 512, None] - c[None, k], axis=-1)
+        thr = rho * np.maximum(R[i:i + 512, None], R[None, k])
+        same = np.arange(i, min(i + 512, len(c)))[:, None] == k[None]
+        clash = (d < thr - 1e-4) & ~same
+        assert not np.any(clash[kept[i:i + 512]]), "two kept contours overlap"
+        near = (d < thr + 1e-4) & ~same
+        beaten[i:i + 512] = np.any(near & (e[None, k] <= e[i:i + 512, None] + 2.0 ** -22 * np.abs(e[i:i + 512, None])), axis=1)
+    assert np.all(beaten[cand & ~kept]), "a contour lost to nobody"
+
+
+# one workgroup writes the outcome up to 8,192 contours; grid-wide rounds from 1,025; the dense volumes give
+# every contour more overlapping neighbours than its list holds
+@pytest.mark.parametrize("dim,n,shape,r", [
+    (3, 1, (40, 40, 40), (5, 9)), (3, 33, (40, 40, 40), (5, 9)), (3, 1024, (60, 64, 70), (5, 9)),
+    (3, 1025, (100, 120, 128), (4, 6)), (3, 3000, (40, 44, 50), (5, 9)), (3, 8193, (160, 200, 210), (4, 6)),
+    (2, 40, (1, 90, 101), (5, 9)), (2, 2000, (1, 300, 310), (4, 9)), (2, 8192, (1, 512, 640), (4, 6)),
+    (2, 8193, (1, 600, 900), (4, 9))])
+def test_competition_outcome(dim, n, shape, r):
+    out, status = _run(dim, n, shape, r)
+    _check(dim, out, status)
+    again, _ = _run(dim, n, shape, r, noalloc=True)
+    for k in out:
+        assert np.array_equal(out[k], again[k]), k
