@@ -601,7 +601,7 @@ snk_status neighbour_args(snk_ctx *c, snk::NeighbourArgs &b) {
     if (st != SNK_OK) return st;
     b.snap = c->d_snap;
     b.cell_start = c->d_nbgrid;
-    b.cell_fill = c->d_nbgrid + total + 1;
+    b.cell_next = c->d_nbgrid + total + 1;
     b.overflow = c->d_nbgrid + 2 * (total + 1);
     b.items = c->d_nbitems;
     b.cell_of = c->d_nbitems + n;
@@ -714,7 +714,9 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
         for (int done = 0; done < n_iter; ++parts) {
             a.n_iter = std::min(c->repel_every, n_iter - done);
             done += a.n_iter;
-            HIPTRY(c, snk::launch_neighbours(c->d_st, (int)c->n, geometry(c), c->P.dim, rho, nbargs, c->stream));
+            HIPTRY(c, snk::launch_neighbours(c->d_st, (int)c->n, geometry(c), c->P.dim, rho, nbargs, parts == 0,
+                                             c->stream));
+            std::swap(nbargs.cell_start, nbargs.cell_next);
             HIPTRY(c, snk::launch_evolve(a, c->P.dim, lanes, unroll, layout, trace, c->stream));
         }
         parts = std::max(parts, 1);

@@ -1322,9 +1322,13 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
     float *lds_tile = lds_axis + 32 * WAVES;
     const int nb = EXACT ? 1 : dr.KR / dr.K;   // blocks per set of rotations
     if constexpr (!EXACT) {
+        // the last wave draws the rotations while the others' first passes draw and fetch their table rows
+        typename WaveDraws<DIM, G>::Pending pend;
+        if (wave < dr.passes) pend = dr.begin(wave, (uint32_t)(n0 + 1), id, cp, lane);
         if (wave == WAVES - 1) dr.rotations((uint32_t)(n0 + 1), id, cp, lane);
         __syncthreads();
-        for (int r = wave; r < dr.passes; r += WAVES)
+        if (wave < dr.passes) dr.finish(pend, 0, 0, cp);
+        for (int r = wave + WAVES; r < dr.passes; r += WAVES)
             dr.finish(dr.begin(r, (uint32_t)(n0 + 1), id, cp, lane), 0, 0, cp);
         __syncthreads();
         if (nb == 1) {

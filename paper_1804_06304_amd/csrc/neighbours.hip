@@ -31,18 +31,23 @@ __device__ __forceinline__ bool is_live(uint8_t status) {
     return st == SNK_ACTIVE || st == SNK_CONVERGED;
 }
 
-__global__ __launch_bounds__(NB_T) void nb_zero_kernel(NeighbourArgs b) {
+// A rebuild is three dependent launches (four above kNbOneGroup contours): snapshot and count, running sum and
+// items, lists. Each takes a few microseconds whatever it does, and a run rebuilds before every chunk, so
+// the steps are merged (1,200 doubled seeds: 33 us in five launches before, 15 us now): the count gives each
+// contour its place in its cell, so the items need no counters of their own, and the running sum clears the
+// counts of the next rebuild (two sets in turn).
+constexpr int kNbOneGroup = 8192;   // contours whose items one workgroup places (8 per thread)
+
+__global__ __launch_bounds__(NB_T) void nb_clear_kernel(NeighbourArgs b) {
     const int i = blockIdx.x * NB_T + threadIdx.x;
-    const int G = b.G[0] * b.G[1] * b.G[2];
-    if (i <= G) b.cell_start[i] = 0;
-    if (i < G) b.cell_fill[i] = 0;
-    if (i == 0) *b.overflow = 0;
+    if (i <= b.G[0] * b.G[1] * b.G[2]) b.cell_start[i] = 0;
 }
 
-// Snapshot record of contour i (anchor bits and R; offset and live flag) and its grid cell.
+// Snapshot record of contour i (anchor bits and R; offset and live flag), its grid cell and place in it.
 template <int DIM>
 __global__ __launch_bounds__(NB_T) void nb_snap_kernel(const DevContour *st, int n, Geometry g, NeighbourArgs b) {
     const int i = blockIdx.x * NB_T + threadIdx.x;
+    if (i == 0) *b.overflow = 0;
     if (i >= n) return;
     const DevContour s = st[i];
     const bool live = is_live(s.status);
@@ -51,13 +56,19 @@ __global__ __launch_bounds__(NB_T) void nb_snap_kernel(const DevContour *st, int
     int cell = -1;
     if (live) {
         cell = cell_of_point<DIM>(s, g, b.cell, b.G);
-        atomicAdd(&b.cell_start[cell + 1], 1);
+        b.nbn[i] = atomicAdd(&b.cell_start[cell + 1], 1);
     }
     b.cell_of[i] = cell;
 }
 
-// Running sum of the cell counts, in place, by one workgroup (grids here hold at most 2^20 cells).
-__global__ __launch_bounds__(1024) void nb_scan_kernel(NeighbourArgs b) {
+__device__ __forceinline__ void place_one(int i, const NeighbourArgs &b) {
+    const int cell = b.cell_of[i];
+    if (cell >= 0) b.items[b.cell_start[cell] + b.nbn[i]] = i;
+}
+
+// Running sum of the cell counts, in place, by one workgroup (grids here hold at most 2^20 cells); clears the
+// next rebuild's counts; place: the items of all n contours too.
+__global__ __launch_bounds__(1024) void nb_scan_kernel(int n, int place, NeighbourArgs b) {
     __shared__ int part[1024];
     const int G = b.G[0] * b.G[1] * b.G[2];
     const int t = threadIdx.x;
@@ -65,6 +76,7 @@ __global__ __launch_bounds__(1024) void nb_scan_kernel(NeighbourArgs b) {
     const int lo = 1 + t * per, hi = min(lo + per, G + 1);
     int sum = 0;
     for (int c = lo; c < hi; ++c) sum += b.cell_start[c];
+    for (int c = t; c <= G; c += 1024) b.cell_next[c] = 0;
     part[t] = sum;
     __syncthreads();
     for (int d = 1; d < 1024; d <<= 1) {
@@ -78,13 +90,14 @@ __global__ __launch_bounds__(1024) void nb_scan_kernel(NeighbourArgs b) {
         run += b.cell_start[c];
         b.cell_start[c] = run;
     }
+    if (!place) return;
+    __syncthreads();
+    for (int i = t; i < n; i += 1024) place_one(i, b);
 }
 
-__global__ __launch_bounds__(NB_T) void nb_scatter_kernel(int n, NeighbourArgs b) {
+__global__ __launch_bounds__(NB_T) void nb_place_kernel(int n, NeighbourArgs b) {
     const int i = blockIdx.x * NB_T + threadIdx.x;
-    if (i >= n) return;
-    const int cell = b.cell_of[i];
-    if (cell >= 0) b.items[b.cell_start[cell] + atomicAdd(&b.cell_fill[cell], 1)] = i;
+    if (i < n) place_one(i, b);
 }
 
 // Whether live contour j (snapshot records sj0, sj1) overlaps contour i: |c_i - c_j| < rho (R_i + R_j).
@@ -140,8 +153,9 @@ constexpr int NB_BUF = 256;        // matches a wave collects before ranking the
 
 // The list of contour i (ACTIVE only; others get none): live contours j != i with
 // |c_i - c_j| < rho (R_i + R_j), ascending j, at most b.cap (more sets the overflow flag). One wave
-// per contour: the lanes test a cell's candidates 64 at a time and append the matches to an LDS
-// buffer (in whatever order the grid holds them), then each match's rank among all of them gives
+// per contour: three cells along x hold their items side by side, so 9 ranges (3 in 2D), loaded together, hold
+// the candidates; the lanes test 64 of them at a time and append the matches to an LDS buffer (in
+// whatever order the grid holds them), then each match's rank among all of them gives
 // its place, so the list does not depend on that order. A contour with more matches than the buffer
 // holds falls back to one lane inserting them one by one (same list).
 template <int DIM>
@@ -163,29 +177,42 @@ __global__ __launch_bounds__(64 * NB_LIST_WAVES) void nb_list_kernel(int n, Geom
     const int ai[3] = {__float_as_int(si0.x), __float_as_int(si0.y), __float_as_int(si0.z)};
     const float oi[3] = {si1.x, si1.y, si1.z};
     int *mine = buf[w];
+    constexpr int ROWS = DIM == 3 ? 9 : 3;
+    int first = 0, len = 0;   // lane r < ROWS: the range of row r
+    if (lane < ROWS) {
+        const int cy = gi[1] + lane % 3 - 1, cz = DIM == 3 ? gi[2] + lane / 3 - 1 : 0;
+        if (cy >= 0 && cz >= 0 && cy < b.G[1] && cz < b.G[2]) {
+            const int row = (cz * b.G[1] + cy) * b.G[0];
+            first = b.cell_start[row + max(gi[0] - 1, 0)];
+            len = b.cell_start[row + min(gi[0] + 1, b.G[0] - 1) + 1] - first;
+        }
+    }
+    int shift[ROWS], end[ROWS];   // candidate k of row r is item shift[r] + k, for k < end[r]
+    int cand = 0;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        shift[r] = __builtin_amdgcn_readlane(first, r) - cand;
+        cand += __builtin_amdgcn_readlane(len, r);
+        end[r] = cand;
+    }
     int total = 0;
-    for (int dz = (DIM == 3 ? -1 : 0); dz <= (DIM == 3 ? 1 : 0); ++dz)
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int cx = gi[0] + dx, cy = gi[1] + dy, cz = gi[2] + dz;
-                if (cx < 0 || cy < 0 || cz < 0 || cx >= b.G[0] || cy >= b.G[1] || cz >= b.G[2]) continue;
-                const int c = (cz * b.G[1] + cy) * b.G[0] + cx;
-                const int q1 = b.cell_start[c + 1];
-                for (int q0 = b.cell_start[c]; q0 < q1; q0 += 64) {
-                    const int q = q0 + lane;
-                    bool hit = false;
-                    int j = -1;
-                    if (q < q1) {
-                        j = b.items[q];
-                        hit = j != i && overlaps<DIM>(ai, oi, si0.w, b.snap[2 * j], b.snap[2 * j + 1], g, rho);
-                    }
-                    const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
-                    const int pos = total + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                    if (hit && pos < NB_BUF) mine[pos] = j;
-                    total += __builtin_popcountll(m);
-                }
-            }
+    for (int k0 = 0; k0 < cand; k0 += 64) {
+        const int k = k0 + lane;
+        bool hit = false;
+        int j = -1;
+        if (k < cand) {
+            int q = k + shift[ROWS - 1];
+#pragma unroll
+            for (int r = ROWS - 2; r >= 0; --r) q = k < end[r] ? k + shift[r] : q;
+            j = b.items[q];
+            hit = j != i && overlaps<DIM>(ai, oi, si0.w, b.snap[2 * j], b.snap[2 * j + 1], g, rho);
+        }
+        const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
+        const int pos = total + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        if (hit && pos < NB_BUF) mine[pos] = j;
+        total += __builtin_popcountll(m);
+    }
     int count;
     if (total <= NB_BUF) {
         // the lanes' buffer writes before any lane reads the buffer
@@ -207,17 +234,18 @@ __global__ __launch_bounds__(64 * NB_LIST_WAVES) void nb_list_kernel(int n, Geom
 }  // namespace
 
 hipError_t launch_neighbours(const DevContour *st, int n, const Geometry &g, int dim, float rho,
-                             const NeighbourArgs &b0, hipStream_t s) {
+                             const NeighbourArgs &b0, bool first, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     NeighbourArgs b = b0;
     b.status = st;
     const int G = b.G[0] * b.G[1] * b.G[2];
     const int blocks = (n + NB_T - 1) / NB_T;
-    hipLaunchKernelGGL(nb_zero_kernel, dim3((G + 1 + NB_T - 1) / NB_T), dim3(NB_T), 0, s, b);
+    if (first) hipLaunchKernelGGL(nb_clear_kernel, dim3((G + 1 + NB_T - 1) / NB_T), dim3(NB_T), 0, s, b);
     if (dim == 2) hipLaunchKernelGGL(nb_snap_kernel<2>, dim3(blocks), dim3(NB_T), 0, s, st, n, g, b);
     else hipLaunchKernelGGL(nb_snap_kernel<3>, dim3(blocks), dim3(NB_T), 0, s, st, n, g, b);
-    hipLaunchKernelGGL(nb_scan_kernel, dim3(1), dim3(1024), 0, s, b);
-    hipLaunchKernelGGL(nb_scatter_kernel, dim3(blocks), dim3(NB_T), 0, s, n, b);
+    const bool place = n <= kNbOneGroup;
+    hipLaunchKernelGGL(nb_scan_kernel, dim3(1), dim3(1024), 0, s, n, place ? 1 : 0, b);
+    if (!place) hipLaunchKernelGGL(nb_place_kernel, dim3(blocks), dim3(NB_T), 0, s, n, b);
     const int lblocks = (n + NB_LIST_WAVES - 1) / NB_LIST_WAVES;
     if (dim == 2) hipLaunchKernelGGL(nb_list_kernel<2>, dim3(lblocks), dim3(64 * NB_LIST_WAVES), 0, s, n, g, rho, b);
     else hipLaunchKernelGGL(nb_list_kernel<3>, dim3(lblocks), dim3(64 * NB_LIST_WAVES), 0, s, n, g, rho, b);

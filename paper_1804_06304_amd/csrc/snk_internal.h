@@ -153,7 +153,8 @@ inline bool full_passes(int G, int U, int M, int L) { return L == 16 && (M / 2 *
 // contours, then per ACTIVE contour the live contours whose inner sphere overlaps its own.
 struct NeighbourArgs {
     float4 *snap;
-    int *cell_start, *cell_fill, *items, *cell_of;   // grid: G + 1, G, n, n
+    int *cell_start, *cell_next; // grid: G + 1 each, this rebuild's and the next one's (cleared by this one)
+    int *items, *cell_of;        // n, n
     int *nb, *nbn;               // n x cap, n
     int *overflow;               // set when a contour has more than cap neighbours
     int cap;
@@ -161,8 +162,9 @@ struct NeighbourArgs {
     float cell;
     const DevContour *status;
 };
+// first: no rebuild of this run has cleared b.cell_start yet.
 hipError_t launch_neighbours(const DevContour *st, int n, const Geometry &g, int dim, float rho,
-                             const NeighbourArgs &b, hipStream_t s);
+                             const NeighbourArgs &b, bool first, hipStream_t s);
 
 // One job of a batch, resident in device memory.
 struct JobDev {

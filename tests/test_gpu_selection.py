@@ -14,6 +14,12 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch   # before the library: the process then has one HIP runtime
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+
+
 def _run(dim, n, shape, r, noalloc=False):
     from paper_1804_06304_amd import snk
     rng = np.random.default_rng(n + dim)

@@ -12,6 +12,12 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch   # before the library: the process then has one HIP runtime
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+
+
 def _volume(dim, rng):
     shape = (1, 90, 101) if dim == 2 else (40, 44, 50)
     z, y, x = np.meshgrid(*(np.arange(s) for s in shape), indexing="ij")
