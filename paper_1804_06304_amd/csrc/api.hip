@@ -324,9 +324,14 @@ snk_status run_prepass(snk_ctx *c) {
     }
     if (!snk::prepass_lds_limit_ok(a.rx, a.ry, a.rz))
         return fail(c, SNK_EINVAL, "sigma_pre too large for the pre-pass tile (LDS > 64 KiB)");
-    const int layout = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
+    int layout = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
     if (layout < 0)
         return fail(c, SNK_EINVAL, "volume too large for the requested layout");
+    // a 2D image whose contours will evolve in boxes (mc_shape) is read from the plain copy alone: without
+    // the column pairs the pre-pass writes a third of the bytes (8192^2: 245 -> 172 us)
+    if (c->layout_req == 0 && c->P.dim == 2 && layout == snk::kBufferPair && c->cus > 0 && c->n > 4 * (int64_t)c->cus &&
+        c->tile_req < 0)
+        layout = snk::kBufferPlain;
     snk_status lst = ensure_layout_buffer(c, layout);
     if (lst != SNK_OK) return lst;
     a.Jq = layout == snk::kBufferQuad ? c->Jq : nullptr;
@@ -374,49 +379,82 @@ snk::JobParams job_params(const snk_ctx *c) {
 
 struct McShape {
     int lanes, unroll, tile;
+    bool two_waves;   // of 256 lanes
 };
 
-// Launch shape of a Monte-Carlo evolve over `layout`. Explicit knobs are taken as set. The automatic
-// LDS box applies when every contour can stay resident at once, ceil(n / CUs) workgroups per CU,
-// and there are more than four of them per CU (the common case of one volume with a few thousand
-// cells: their footprints overflow the L2, which a handful of contours per CU do not, where
-// staging only adds latency): two waves per contour when a contour has at least four pair-points
-// per lane of them, else one (unless set), two pair-points in flight (slab evolve 2.34 ms; four, which
-// need 128 registers and spill, 2.80), and the largest box whose LDS still leaves room for all of them.
-// Otherwise no box and the lane rule of pick_lanes.
+// Lanes per contour of a Monte-Carlo evolve over `layout` (the layout the volume takes by its size, whatever
+// copy the pre-pass wrote): as set; else two waves per contour when it has at least four pair-points per lane
+// of them, or one, as long as that many contours stay resident with boxes, else the rule of pick_lanes.
+// Lanes are the order of a contour's sums, so the line between the two must not move with the kernels'
+// registers or LDS: contours per CU and bytes are counted as when the rule was set (5 and 6 waves per
+// SIMD in 3D and 2D with two pair-points in flight, 4 with four, 8 with one).
+int sum_lanes(const snk_ctx *c, int M, int layout) {
+    const int lanes = pick_lanes(c);
+    if (c->lanes > 0 || c->tile_req >= 0 || c->n <= 0 || c->cus <= 0 || c->lds_per_cu <= 0) return lanes;
+    if (layout != snk::kBufferQuad && layout != snk::kBufferPlain && !(c->P.dim == 3 && layout == snk::kBufferPair))
+        return lanes;
+    const int64_t pairs = (int64_t)(M / 2) * c->P.n_radial;
+    const int64_t per_cu = (c->n + c->cus - 1) / c->cus;
+    const int G = pairs >= 512 ? 128 : (pairs >= 128 ? 64 : 0);
+    if (per_cu <= 4 || G == 0) return lanes;
+    const int waves = c->unroll == 1 ? 8 : (c->unroll == 4 ? (c->P.dim == 3 && G == 64 ? 3 : 4) : (c->P.dim == 3 ? 5 : 6));
+    if (per_cu > waves * 4 / (G / 64)) return lanes;
+    const size_t other = snk::evolve_rule_lds(c->P.dim, G, M);
+    const size_t budget = std::min<size_t>((size_t)c->lds_per_cu / (size_t)per_cu, 65536) & ~(size_t)511;
+    return budget >= other + 4096 ? G : lanes;
+}
+
+// Launch shape of a Monte-Carlo evolve over `layout`. Explicit knobs are taken as set; of the shapes that give
+// the same bits the library picks. Two pair-points in flight (slab evolve 2.34 ms; four need 128 registers
+// and spill, 2.80).
+// LDS box (automatic): none with four or fewer contours per CU, whose footprints fit the L2 (8 contours of
+// 64^3: 160 us without, 167 with). Above, the largest that leaves room for every contour of the CU. More
+// contours than can be resident (3D groups of two waves or more, 2D): the largest that leaves room for as
+// many as registers allow, 8 of two waves in 3D, 20 of one wave in 2D; there 256 lanes run as two waves.
+// Evolve, no box -> box: 62,500 lattice contours 9.1 -> 7.8 ms; 40,000 in 2D 4.2 -> 4.1 ms, and the pre-pass
+// need not write the column pairs.
 McShape mc_shape(snk_ctx *c, int M, int layout) {
     McShape s;
-    s.lanes = pick_lanes(c);
+    s.lanes = sum_lanes(c, M, layout);
     s.unroll = c->unroll > 0 ? c->unroll : (s.lanes >= 64 ? 2 : 1);
     s.tile = 0;
+    s.two_waves = false;
     if (c->tile_req > 0) {
         s.tile = c->tile_req;
         return s;
     }
-    if (c->tile_req == 0 || c->n <= 0 || c->cus <= 0 || c->lds_per_cu <= 0) return s;
-    if (layout != snk::kBufferQuad && layout != snk::kBufferPlain && !(c->P.dim == 3 && layout == snk::kBufferPair))
-        return s;
-    const int64_t pairs = (int64_t)(M / 2) * c->P.n_radial;
+    const int G = s.lanes, dim = c->P.dim;
+    if (c->tile_req == 0 || c->n <= 0 || c->cus <= 0 || c->lds_per_cu <= 0 || G < 64) return s;
+    if (layout != snk::kBufferQuad && layout != snk::kBufferPlain && layout != snk::kBufferPair) return s;
     const int64_t per_cu = (c->n + c->cus - 1) / c->cus;
-    if (per_cu <= 4) return s;
-    const int G = c->lanes > 0 ? c->lanes : (pairs >= 512 ? 128 : (pairs >= 128 ? 64 : 0));
-    if (G < 64) return s;
-    const int U = c->unroll > 0 ? c->unroll : 2;
-    const int key = ((c->P.dim * 512 + G) * 8 + U) * 4 + layout;
-    if (key != c->stage_key) {
-        c->stage_blocks = snk::evolve_stage_blocks_per_cu(c->P.dim, G, U, layout);
-        c->stage_key = key;
+    // (fewer than 128 pair-points an iteration do not repay a box)
+    if (per_cu <= 4 || (int64_t)(M / 2) * c->P.n_radial < 128) return s;
+    auto blocks = [&](int g) {
+        const int key = ((dim * 512 + g) * 8 + s.unroll) * 4 + layout;
+        if (key != c->stage_key) {
+            c->stage_blocks = snk::evolve_stage_blocks_per_cu(dim, g, s.unroll, layout);
+            c->stage_key = key;
+        }
+        return c->stage_blocks;
+    };
+    int64_t resident = per_cu;
+    bool two_waves = false;
+    if (per_cu > blocks(G)) {
+        if (dim == 3 && G < 128) return s;
+        two_waves = G == 256 && dim == 3 && s.unroll == 2 && layout != snk::kBufferQuad &&
+                    !(c->P.flags & snk::kFlagGradI) && snk::full_passes(256, 2, M, c->P.n_radial);
+        resident = dim == 2 ? 20 : blocks(two_waves ? 128 : G);
+        if (resident <= 0) return s;
     }
-    if (per_cu > c->stage_blocks) return s;
-    const size_t other = snk::evolve_lds_bytes(c->P.dim, G, M, 0);
-    // LDS is handed out in 512-byte blocks
-    const size_t budget = std::min<size_t>((size_t)c->lds_per_cu / (size_t)per_cu, 65536) & ~(size_t)511;
+    // (a box of one voxel: the LDS beside it)
+    const size_t other = snk::evolve_lds_bytes(dim, G, M, 1, two_waves) - 4;
+    // LDS is handed out in blocks of 1,280 bytes (160 KiB / 128): slab 2.37 ms with 8 x 20,480 bytes, 2.46 above
+    const size_t budget = std::min<size_t>((size_t)c->lds_per_cu / (size_t)resident, 65536) / 1280 * 1280;
     if (budget <= other) return s;
-    const int tile = (int)std::min<size_t>((budget - other) / 4, 16384) & ~63;
-    if (tile < 1024) return s;
-    s.lanes = G;
-    s.unroll = U;
+    const int tile = (int)std::min<size_t>((budget - other) / 4, 16384) & ~15;
+    if (tile < (dim == 3 ? 1024 : 512)) return s;
     s.tile = tile;
+    s.two_waves = two_waves;
     return s;
 }
 
@@ -426,6 +464,9 @@ snk_status ensure_layout(snk_ctx *c) {
     if (layout < 0)
         return fail(c, SNK_EINVAL, "volume too large for the requested layout");
     if (layout == c->layout) return SNK_OK;
+    // an automatic 2D layout is whichever of the two the pre-pass wrote
+    if (c->layout_req == 0 && c->P.dim == 2 && layout == snk::kBufferPair && c->layout == snk::kBufferPlain)
+        return SNK_OK;
     snk_status st = ensure_layout_buffer(c, layout);
     if (st != SNK_OK) return st;
     if (layout == snk::kBufferQuad)
@@ -663,7 +704,8 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
         lanes = c->lanes > 0 ? c->lanes : 256;
         unroll = 1;
     } else {
-        const McShape sh = mc_shape(c, a.p.M, layout);
+        // a 2D image whose pre-pass left out the column pairs counts as one that has them
+        const McShape sh = mc_shape(c, a.p.M, gradi || c->P.dim == 3 ? layout : snk::volume_layout(2, c->nx, c->ny, c->nz, c->layout_req));
         lanes = sh.lanes;
         unroll = sh.unroll;
         // LDS boxes: whole-wave groups over a buffer layout
@@ -672,6 +714,7 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
         // with a box, the iterations whose ball does not fit read the plain copy
         if (sh.tile > 0 && layout == snk::kBufferPair && c->P.dim == 2) layout = snk::kBufferPlain;
         a.tile_cap = sh.tile;
+        a.two_waves = sh.two_waves;
         if (c->P.flags & snk::kFlagGradI) {
             // gradient-form centre force: whole-wave groups, two pair-points in flight
             if (c->lanes > 0 && c->lanes < 64)

@@ -42,10 +42,10 @@ template <int DIM, int G, int U, int LAYOUT, bool PERSISTENT, bool STAGE>
 hipError_t batch_t(BatchArgs a, int grid, hipStream_t s) {
     const int g = PERSISTENT ? grid : a.n_items;
     if (g <= 0) return hipSuccess;
-    const DrawPlan d = draw_plan(DIM, a.max_M / 2);
+    const DrawPlan d = draw_plan(DIM, a.max_M / 2, STAGE);
     a.draw_k = d.K;
     a.rot_k = d.KR;
-    const size_t lds = wave_lds_bytes(G, wave_draw_floats(DIM, d.K, d.KR, a.max_M / 2), STAGE ? a.tile_cap : 0);
+    const size_t lds = wave_lds_bytes(G, G, wave_draw_floats(DIM, d.K, d.KR, a.max_M / 2), STAGE ? a.tile_cap : 0);
     if constexpr (U >= 2)
         if (full_passes(G, U, a.max_M, a.L)) {
             hipLaunchKernelGGL((evolve_batch_kernel<DIM, G, U, LAYOUT, PERSISTENT, STAGE, true>), dim3(g), dim3(G), lds,

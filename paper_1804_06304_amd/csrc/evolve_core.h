@@ -1285,20 +1285,25 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, floa
 //   - FULL instances (L = 16 and whole passes) step no per-pair-point indices;
 //   - the draws: see WaveDraws.
 // Vector instructions per wave and iteration, before -> now, and the evolve's time: slab (3D, two waves, 512
-// pair-points, boxes) 748 -> 546, 2.70 -> 2.34 ms; 8192^2 image (one wave, 128 pair-points) 280 -> 231, 5.1 ->
-// 4.4 ms; 62,500 lattice contours (four waves) 456 -> 323, 10.6 -> 9.1 ms.
+// pair-points, boxes) 748 -> 546, 2.70 -> 2.34 ms (2.20 with the box's present size); 8192^2 image (one wave, 128
+// pair-points) 280 -> 231, 5.1 -> 4.2 ms; 62,500 lattice contours (four waves' work) 456 -> 323, 10.6 -> 9.1 ms,
+// and 7.8 ms by two waves with boxes.
 //
 // STAGE: iterations whose ball fits a box of tile_cap voxels read their corners from an LDS box, the others
 // from the volume in LAYOUT. lds: draws, the waves' partial sums, the box.
-// cp: p in constant memory.
-template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL>
+// cp: p in constant memory. PG < G (FULL): PG lanes do the work of G, wave by wave: the sums of each of
+// the G / 64 waves are formed and reduced in turn, so the totals are those of G lanes bit for bit, and what an
+// iteration costs beside its samples is paid by fewer waves.
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL, int PG = G>
 __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slot, int n_iter, int target,
                          float *trace_row, float *lds, int draw_k, int rot_k, unsigned long long *counter,
                          int tile_cap, const Repel rp) {
     static_assert(G >= 64, "whole waves");
     static_assert(!STAGE || !EXACT, "LDS boxes are staged by Monte-Carlo groups");
     constexpr int NR = 2 + DIM;
-    constexpr int WAVES = G / 64;
+    constexpr int WAVES = PG / 64;    // waves of the workgroup
+    constexpr int PARTS = G / 64;     // waves whose sums the totals are made of
+    static_assert(PG == G || (FULL && PG < G), "fewer lanes than the group has: FULL instances");
     constexpr float RHO = DIM == 3 ? 0.79370052598409973738f : 0.70710678118654752440f;
     constexpr float BALL = DIM == 3 ? 4.18879020478639098462f : 3.14159265358979323846f;
     constexpr uint64_t AXES = DIM == 3 ? 0xE : 0x6;         // lanes 1 .. DIM: the axes
@@ -1316,14 +1321,14 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
     const int L = p.L;
     const uint32_t id = s.id;
     const Vol<DIM, LAYOUT> vol(p.g);
-    const WaveDraws<DIM, G> dr(lds, draw_k, rot_k, MH);
+    const WaveDraws<DIM, PG> dr(lds, draw_k, rot_k, MH);
     float *lds_red = lds + (EXACT ? 0 : wave_draw_floats(DIM, draw_k, rot_k, MH));
-    float *lds_axis = lds_red + (WAVES > 1 ? 16 * WAVES : 0);
+    float *lds_axis = lds_red + (PARTS > 1 ? 16 * PARTS : 0);
     float *lds_tile = lds_axis + 32 * WAVES;
     const int nb = EXACT ? 1 : dr.KR / dr.K;   // blocks per set of rotations
     if constexpr (!EXACT) {
         // the last wave draws the rotations while the others' first passes draw and fetch their table rows
-        typename WaveDraws<DIM, G>::Pending pend;
+        typename WaveDraws<DIM, PG>::Pending pend;
         if (wave < dr.passes) pend = dr.begin(wave, (uint32_t)(n0 + 1), id, cp, lane);
         if (wave == WAVES - 1) dr.rotations((uint32_t)(n0 + 1), id, cp, lane);
         __syncthreads();
@@ -1393,9 +1398,6 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
 #pragma clang fp contract(off)
         const int gl = opaque(tid);
         const int lane = gl & 63;
-        float acc[NR];
-#pragma unroll
-        for (int k = 0; k < NR; ++k) acc[k] = 0.0f;
         Frame<DIM> fr;
         const float smax_v = R + 0.5f * p.dR;
         set_frame<DIM, G>(fr, p, uni<G>(smax_v), RHO * R, R);
@@ -1417,13 +1419,24 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
             nvol[1] = q->g.ny;
             nvol[2] = q->g.nz;
         }
+        // x: the totals of A, x, y, z (2D: A, x, y, B_R) in lanes 0 .. 3 of each four; br: B_R in every lane
+        float x = 0.0f, br = 0.0f;
+        auto reduce = [&](const float *acc) {
+            const float v[5] = {acc[0], acc[3], acc[2], DIM == 3 ? acc[NR - 1] : acc[1], acc[1]};
+            wave_quads<NR>(v, x, br);
+        };
+        float *red = lds_red + (it & 1) * 8 * PARTS;
         if constexpr (EXACT) {
+            float acc[NR];
+#pragma unroll
+            for (int k = 0; k < NR; ++k) acc[k] = 0.0f;
             const float inv_h[3] = {p.g.inv_h[0], p.g.inv_h[1], p.g.inv_h[2]};
             const float hh[3] = {p.g.h[0], p.g.h[1], p.g.h[2]};
             if (interior)
                 lattice_sums<DIM, G, false, LAYOUT>(vol, nvol, fr, hh, inv_h, gl, acc);
             else
                 lattice_sums<DIM, G, true, LAYOUT>(vol, nvol, fr, hh, inv_h, gl, acc);
+            reduce(acc);
         } else {
             const float4 *pu = dr.pu + ((blk & 1) * dr.K + sl) * MH;
             bool staged = false;
@@ -1439,7 +1452,7 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
                         ball_range<DIM>(fr, inv_h, lo, hi);
                         if (choose_tile<DIM>(lo, hi, nv, tile_cap, tile)) {
                             // the previous iteration's reads of the box ended at its reduction barrier
-                            stage_tile<G>(lds_tile, q->g.J, vol.nx, vol.nxy, tile, gl);
+                            stage_tile<PG>(lds_tile, q->g.J, vol.nx, vol.nxy, tile, gl);
                             __syncthreads();
                             staged = true;
                             retry = 3.0e38f;
@@ -1450,23 +1463,34 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
                     }
                 }
             }
-            if (staged) {
-                TileVol<DIM> tv;
-                tv.t = lds_tile;
-                tv.nx = tile.n[0];
-                tv.nxy = tile.n[0] * tile.n[1];
-                Frame<DIM> ft = fr;
-                ft.base = (anc[0] - tile.lo[0]) + (anc[1] - tile.lo[1]) * tv.nx;
-                if constexpr (DIM == 3) ft.base += (anc[2] - tile.lo[2]) * tv.nxy;
-                lane_sums<DIM, G, U, false, GRADI, FULL>(tv, nvol, ft, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-            } else if (interior) {
-                lane_sums<DIM, G, U, false, GRADI, FULL>(vol, nvol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
-            } else {
-                lane_sums<DIM, G, U, true, GRADI, FULL>(vol, nvol, fr, pu, P, L, invL, gl, l0, m0, dl, dm, acc);
+#pragma unroll 1
+            for (int part = 0; part < PARTS / WAVES; ++part) {
+                const int sg = gl + part * PG;   // the lane of the group whose pair-points these are
+                float acc[NR];
+#pragma unroll
+                for (int k = 0; k < NR; ++k) acc[k] = 0.0f;
+                if (staged) {
+                    TileVol<DIM> tv;
+                    tv.t = lds_tile;
+                    tv.nx = tile.n[0];
+                    tv.nxy = tile.n[0] * tile.n[1];
+                    Frame<DIM> ft = fr;
+                    ft.base = (anc[0] - tile.lo[0]) + (anc[1] - tile.lo[1]) * tv.nx;
+                    if constexpr (DIM == 3) ft.base += (anc[2] - tile.lo[2]) * tv.nxy;
+                    lane_sums<DIM, G, U, false, GRADI, FULL>(tv, nvol, ft, pu, P, L, invL, sg, l0, m0, dl, dm, acc);
+                } else if (interior) {
+                    lane_sums<DIM, G, U, false, GRADI, FULL>(vol, nvol, fr, pu, P, L, invL, sg, l0, m0, dl, dm, acc);
+                } else {
+                    lane_sums<DIM, G, U, true, GRADI, FULL>(vol, nvol, fr, pu, P, L, invL, sg, l0, m0, dl, dm, acc);
+                }
+                reduce(acc);
+                if constexpr (PG < G) {
+                    if (lane < 5) red[(wave + part * WAVES) * 8 + lane] = (DIM == 3 && lane == 4) ? br : x;
+                }
             }
         }
         // draws ahead
-        typename WaveDraws<DIM, G>::Pending pend;
+        typename WaveDraws<DIM, PG>::Pending pend;
         pend.on = false;
         if constexpr (!EXACT) {
             if (sl == 0 && it + dr.K < budget) {
@@ -1475,12 +1499,6 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
             }
         }
 
-        // totals: x holds A, x, y, z (2D: A, x, y, B_R) in lanes 0 .. 3 of each four, br B_R in every lane
-        float x, br;
-        {
-            float v[5] = {acc[0], acc[3], acc[2], DIM == 3 ? acc[NR - 1] : acc[1], acc[1]};
-            wave_quads<NR>(v, x, br);
-        }
         const int n = n0 + it + 1;
         float smax_d = smax_v;
 #pragma unroll
@@ -1494,16 +1512,17 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
         const float eps = p.eps0 * __builtin_amdgcn_rsqf((float)n);
         const float half_eps = 0.5f * eps;
         const float kc = -half_eps * scale * inv_norm;
-        if constexpr (WAVES > 1) {
+        if constexpr (PARTS > 1) {
             // per-wave partials, added in wave order by every wave, so all of them hold the same totals
             // and take the same step (no second barrier to hand one wave's result to the others)
-            float *red = lds_red + (it & 1) * 8 * WAVES;
-            if (lane < 5) red[wave * 8 + lane] = (DIM == 3 && lane == 4) ? br : x;
+            if constexpr (PG == G) {
+                if (lane < 5) red[wave * 8 + lane] = (DIM == 3 && lane == 4) ? br : x;
+            }
             __syncthreads();
             x = red[lane & 3];
             if constexpr (DIM == 3) br = red[4];
 #pragma unroll
-            for (int w = 1; w < WAVES; ++w) {
+            for (int w = 1; w < PARTS; ++w) {
                 x += red[w * 8 + (lane & 3)];
                 if constexpr (DIM == 3) br += red[w * 8 + 4];
             }
@@ -1685,8 +1704,10 @@ constexpr int waves_asked() {
 
 // STAGE: the workgroup's LDS ends with a box of a.tile_cap voxels. GRADI: centre force in its
 // image-gradient form. FULL: L = 16 and whole passes (full_passes).
-template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL>
-__global__ __launch_bounds__(Grp<G>::NT, (waves_asked<DIM, G, U, STAGE, GRADI, FULL>()))
+// PG: lanes of the workgroup (whole-wave groups: see run_wave).
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL,
+          int PG = Grp<G>::NT>
+__global__ __launch_bounds__(PG, (waves_asked<DIM, G, U, STAGE, GRADI, FULL>()))
 void evolve_kernel(EvolveArgs a) {
     extern __shared__ __align__(16) float lds[];
     if constexpr (G < 64) {
@@ -1704,27 +1725,28 @@ void evolve_kernel(EvolveArgs a) {
         const Cold<EvolveArgs> ca = (Cold<EvolveArgs>)__builtin_amdgcn_kernarg_segment_ptr();
         Repel rp{ca, cid, -1};
         if (a.kappa > 0.0f) rp.cnt = __builtin_amdgcn_readfirstlane(a.nbn[cid]);
-        run_wave<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, FULL>(
+        run_wave<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, FULL, PG>(
             a.p, (Cold<JobParams>)ca, a.st + cid, a.n_iter, 0x7fffffff,
             TRACE ? a.trace + (long)cid * SNK_TRACE_W : nullptr, lds, a.draw_k, a.rot_k, a.counter,
             STAGE ? a.tile_cap : 0, rp);
     }
 }
 
-template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL>
+template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL,
+          int PG = Grp<G>::NT>
 hipError_t launch_f(EvolveArgs a, hipStream_t s) {
     size_t lds;
     if constexpr (G >= 64) {
-        const DrawPlan d = draw_plan(DIM, a.p.M / 2);
+        const DrawPlan d = draw_plan(DIM, a.p.M / 2, STAGE);
         a.draw_k = d.K;
         a.rot_k = d.KR;
-        lds = wave_lds_bytes(G, EXACT ? 0 : wave_draw_floats(DIM, d.K, d.KR, a.p.M / 2), STAGE ? a.tile_cap : 0);
+        lds = wave_lds_bytes(G, PG, EXACT ? 0 : wave_draw_floats(DIM, d.K, d.KR, a.p.M / 2), STAGE ? a.tile_cap : 0);
     } else {
         lds = sizeof(float) * (size_t)sub_lds_floats<G>(a.p.M / 2);
     }
     const int blocks = (a.n + Grp<G>::CPB - 1) / Grp<G>::CPB;
-    hipLaunchKernelGGL((evolve_kernel<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, FULL>), dim3(blocks),
-                       dim3(Grp<G>::NT), lds, s, a);
+    hipLaunchKernelGGL((evolve_kernel<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, FULL, PG>), dim3(blocks),
+                       dim3(PG), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1733,8 +1755,13 @@ hipError_t launch_f(EvolveArgs a, hipStream_t s) {
 template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT = false, bool STAGE = false, bool GRADI = false>
 hipError_t launch_t(const EvolveArgs &a, hipStream_t s) {
     if constexpr (G >= 64 && U >= 2 && !TRACE && !EXACT)
-        if (full_passes(G, U, a.p.M, a.p.L))
+        if (full_passes(G, U, a.p.M, a.p.L)) {
+            // two waves do the work of four where the launch shape says so (mc_shape)
+            if constexpr (DIM == 3 && G == 256 && STAGE && !GRADI && LAYOUT != kBufferQuad)
+                if (a.two_waves)
+                    return launch_f<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, true, 128>(a, s);
             return launch_f<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, true>(a, s);
+        }
     return launch_f<DIM, G, U, TRACE, LAYOUT, EXACT, STAGE, GRADI, false>(a, s);
 }
 

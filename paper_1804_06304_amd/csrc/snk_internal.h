@@ -108,6 +108,7 @@ struct EvolveArgs {
     const int *nb, *nbn;         // nb_cap neighbour indices per contour (ascending), their counts
     int nb_cap;
     float kappa;
+    bool two_waves;              // 256 lanes with boxes: two waves do the work of four (same bits)
     int draw_k, rot_k;           // draw plan of a whole-wave launch (set by the launcher)
 };
 
@@ -119,16 +120,18 @@ struct DrawPlan {
 __host__ __device__ inline int wave_draw_floats(int dim, int K, int KR, int MH) {
     return (8 * K * MH + KR * (dim == 3 ? 9 : 2) + 3) & ~3;
 }
-// LDS of a whole-wave workgroup: draws, the waves' partial sums (two sets of 8 floats per wave) and axis
-// records (32 floats per wave), the box. Up to a few hundred bytes over 64 KiB with the largest box that
-// evolve_lds_accepts takes; a workgroup may have 160 KiB.
-inline size_t wave_lds_bytes(int G, int draw_floats, int tile_cap) {
-    return sizeof(float) * ((size_t)draw_floats + (G > 64 ? G / 64 * 16 : 0) + G / 64 * 32 + (size_t)tile_cap);
+// LDS of a whole-wave workgroup of PG lanes: draws, the partial sums of the group's G / 64 waves (two sets of 8
+// floats each) and axis records (32 floats per wave), the box. Up to a few hundred bytes over 64 KiB with
+// the largest box that evolve_lds_accepts takes; a workgroup may have 160 KiB.
+inline size_t wave_lds_bytes(int G, int PG, int draw_floats, int tile_cap) {
+    return sizeof(float) * ((size_t)draw_floats + (G > 64 ? G / 64 * 16 : 0) + PG / 64 * 32 + (size_t)tile_cap);
 }
 // K: the smallest block (two iterations at least) whose passes of 64 draws are nearly full (within 15% of
-// MH / 64 per iteration), of those that take 8 KiB at most; KR: as many iterations as 32 (3D; 1.1 KiB) or 64
-// (2D) lanes draw in one pass.
-inline DrawPlan draw_plan(int dim, int MH) {
+// MH / 64 per iteration), of those that take 8 KiB at most; KR: the rotations of as many iterations as save
+// most of a pass: 64 in 2D, 32 in 3D; 8 in 3D with a box, where their 36 bytes each compete with it (32 save 19
+// instructions of 546 per iteration, but the 864 bytes are 216 voxels, and 4,432 hold balls that 4,224 do
+// not: slab 2.20 ms against 2.36).
+inline DrawPlan draw_plan(int dim, int MH, bool box) {
     DrawPlan d{2, 2};
     double best = 1e30;
     for (int K = 2; K <= 16 && (K == 2 || 8 * K * MH <= 2048); ++K) {
@@ -142,7 +145,7 @@ inline DrawPlan draw_plan(int dim, int MH) {
             break;
         }
     }
-    const int r = dim == 3 ? 32 : 64;
+    const int r = dim == 2 ? 64 : (box ? 8 : 32);
     d.KR = d.K * (r / d.K > 1 ? r / d.K : 1);
     return d;
 }
@@ -235,9 +238,11 @@ hipError_t launch_evolve_batch(const BatchArgs &a, int dim, int lanes, int unrol
                                int grid, hipStream_t s);
 // Workgroups per CU of a batched launch shape (registers and LDS, including a box of tile_cap voxels).
 int evolve_batch_max_blocks(int dim, int lanes, int unroll, int layout, int max_M, int tile_cap);
-size_t evolve_lds_bytes(int dim, int lanes, int M, int tile_cap);
-// Whether a launch of that many rays and box voxels is accepted (64 KiB of LDS per workgroup by the
-// draw buffers' general size; the kernels take no more than that).
+size_t evolve_lds_bytes(int dim, int lanes, int M, int tile_cap, bool two_waves = false);
+// The LDS of a workgroup without a box by which rules are drawn (the draw buffers' general size; the kernels
+// take less, or a little more), and whether a launch of that many rays and box voxels is accepted: 64 KiB
+// by that count.
+size_t evolve_rule_lds(int dim, int lanes, int M);
 bool evolve_lds_accepts(int dim, int lanes, int M, int tile_cap);
 // Star-shaped contours (one wave per contour, n_radial 16).
 hipError_t launch_star(const EvolveArgs &a, const StarArgs &sa, int dim, int lanes, int layout, hipStream_t s);

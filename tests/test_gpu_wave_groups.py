@@ -80,3 +80,42 @@ def test_box_at_the_lds_limit(lanes, tile):
     _same(a.get_state(), b.get_state())
     a.close()
     b.close()
+
+
+# lanes by the rule of the sums' order: 128 up to 10 contours per CU (256 CUs) with M = 64, else 256; 64 up to 20
+# with M = 32, else 128
+@pytest.mark.parametrize("dim,n,M,lanes,tiled", [(3, 2049, 64, 128, True), (3, 2560, 64, 128, True),
+                                                 (3, 2561, 64, 256, True), (3, 2561, 70, 256, True),
+                                                 (3, 2600, 32, 64, True), (3, 5121, 32, 128, True),
+                                                 (2, 1025, 16, 64, True), (2, 6200, 16, 64, True),
+                                                 (2, 1024, 16, 64, False)])
+def test_automatic_boxes_above_the_resident_contours(dim, n, M, lanes, tiled):
+    """More contours than stay resident: the automatic shape stages boxes (256 lanes by two waves), in 2D over the
+    plain layout, and gives the bits of the same lanes without a box."""
+    from paper_1804_06304_amd import snk
+    rng = np.random.default_rng(n)
+    raw, seeds = _volume(dim, rng)
+    top = np.array(raw.shape[::-1]) * [1.0, 1.0, 1.5 if dim == 3 else 1.0] - 1.0
+    cen = rng.uniform(0, 1, (n, 3)) * top
+    cen[:, dim:] = 0.0
+    cen[: len(seeds)] = seeds
+    D = 64 if dim == 2 else 162
+    p = synth.Params(dim=dim, spacing=(1.0, 1.0, 1.5 if dim == 3 else 1.0), i_offset=20.0, i_scale=1 / 160.0, r_init=6.0,
+                     r_max=14.0, n_dirs=D, n_rays=M)
+    out = []
+    for auto in (True, False):
+        ctx = snk.Context(0)
+        ctx.set_params(p)
+        ctx.set_directions(synth.directions_for(dim, D))
+        if not auto:
+            ctx.set_launch(lanes, 2, 0)
+            ctx.set_tile(0)
+        ctx.load_volume(raw)
+        ctx.load_seeds(cen)
+        ctx.evolve(66)
+        t = ctx.get_timing()
+        assert t["lanes_per_contour"] == lanes and (t["tile_voxels"] > 0) == (auto and tiled)
+        ctx.finalize()
+        out.append(ctx.read())
+        ctx.close()
+    _same(*out)
