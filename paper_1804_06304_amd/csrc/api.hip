@@ -322,8 +322,6 @@ snk_status run_prepass(snk_ctx *c) {
         }
         for (int k = 0; k <= 2 * r; ++k) tap[ax][k] = (float)(g[k] / sum);
     }
-    if (!snk::prepass_lds_limit_ok(a.rx, a.ry, a.rz))
-        return fail(c, SNK_EINVAL, "sigma_pre too large for the pre-pass tile (LDS > 64 KiB)");
     int layout = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
     if (layout < 0)
         return fail(c, SNK_EINVAL, "volume too large for the requested layout");

@@ -1,0 +1,10 @@
+// Pre-pass kernels of u8 volumes.
+#include "prepass_core.h"
+
+namespace snk {
+
+hipError_t launch_prepass_u8(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s, int *slots) {
+    return launch_r<uint8_t>(one, jobs, n, blocks, s, slots);
+}
+
+}  // namespace snk

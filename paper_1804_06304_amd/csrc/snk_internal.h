@@ -212,12 +212,30 @@ struct PrepassArgs {
     float gx[33], gy[33], gz[33];
 };
 
-constexpr int kPrepassTX = 64;
 constexpr int kPrepassMaxR = 16;
-constexpr size_t kPrepassMaxLds = 65536;
+
+// One volume of a launch: cut into bx x by tiles and chunks of z_chunk planes, its first workgroup.
+struct PrepassJob {
+    PrepassArgs a;
+    int first;
+    struct {
+        int bx, by, z_chunk;
+    } cut;
+};
 
 hipError_t launch_prepass(const PrepassArgs &a, hipStream_t s);
-bool prepass_lds_limit_ok(int rx, int ry, int rz);
+int prepass_rows_per_thread(const PrepassArgs &a);
+// Pre-pass of n volumes in one launch: they must agree in prepass_same_launch. prepass_plan fills first and cut and
+// returns the workgroups; host and dev are the same table.
+bool prepass_same_launch(const PrepassArgs &a, const PrepassArgs &b);
+int prepass_plan(PrepassJob *jobs, int n);
+hipError_t launch_prepass_batch(const PrepassJob *host, const PrepassJob *dev, int n, int blocks, hipStream_t s);
+hipError_t launch_prepass_u8(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s,
+                              int *slots);
+hipError_t launch_prepass_u16(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s,
+                              int *slots);
+hipError_t launch_prepass_f32(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s,
+                              int *slots);
 // Pack J into the quad layout (one record per voxel, neighbours clamped at the upper edges).
 hipError_t launch_pack_quad(const float *J, float4 *Jq, int nx, int ny, int nz, hipStream_t s);
 hipError_t launch_pack_pair(const float *J, float2 *Jp, int nx, int ny, int nz, hipStream_t s);
