@@ -6,7 +6,7 @@
 // many volumes of uneven size and contour count.
 //
 //  - snk_engine_run (batched): every admitted job is evolved from its seeds to its iteration target
-//    and finalised in one captured hipGraph: state reset -> pre-pass per volume -> one evolve launch
+//    and finalised in one captured hipGraph: state reset -> pre-pass -> one evolve launch
 //    per launch class (dim, D, M, L) -> exact energy over all items -> selection, one workgroup per
 //    job. The graph is replayed while the job set is unchanged. The launch shape of each class
 //    (lanes per contour, pair-points in flight, persistent work queue or one workgroup per item) is
@@ -72,8 +72,8 @@ struct EJob {
     int G[3] = {1, 1, 1};
     double cell = 1.0;
     int64_t grid_cells = 1;
-    bool prepared = false;               // pre-pass done (served mode)
     std::vector<DevContour> result;
+    bool prepared = false;               // pre-pass launched (served mode)
     double t_submit = 0, t_done = 0;
 };
 
@@ -132,6 +132,8 @@ struct snk_engine {
     size_t items_cap = 0;
     int *d_joblist = nullptr;
     size_t joblist_cap = 0;
+    snk::PrepassJob *d_pre = nullptr;          // the volumes to smooth, by launch
+    size_t pre_cap = 0;
     int *d_unfinished = nullptr;
     unsigned long long *d_counters = nullptr;  // [0] evolved, [1..] queue heads (as int) / kept
     int *d_queues = nullptr;                   // one queue head per launch class
@@ -415,7 +417,7 @@ snk_status admit_pending(snk_engine *e, std::vector<EJob *> &newly) {
     return SNK_OK;
 }
 
-snk_status prepass_job(snk_engine *e, const EJob &j) {
+snk::PrepassArgs prepass_args(const snk_engine *e, const EJob &j) {
     snk::PrepassArgs a{};
     a.raw = j.d_raw;
     a.dtype = (int)j.dtype;
@@ -443,7 +445,42 @@ snk_status prepass_job(snk_engine *e, const EJob &j) {
         }
         for (int k = 0; k <= 2 * r; ++k) tap[ax][k] = (float)(g[k] / sum);
     }
-    EHIP(e, snk::launch_prepass(a, e->stream));
+    return a;
+}
+
+// The pre-pass of the given jobs: one launch for all that agree in raw type and radii. A subvolume alone is a
+// few dozen workgroups (24 of 32^3 to 112^3: 24 launches of 14 us each, one launch 67 us).
+struct PrepassPlan {
+    std::vector<snk::PrepassJob> rows;
+    struct Group {
+        int begin, n, blocks;
+    };
+    std::vector<Group> groups;
+};
+
+PrepassPlan plan_prepass(const snk_engine *e, const std::vector<EJob *> &js) {
+    PrepassPlan pp;
+    std::vector<std::vector<snk::PrepassJob>> by;
+    for (const EJob *j : js) {
+        snk::PrepassJob r{};
+        r.a = prepass_args(e, *j);
+        size_t k = 0;
+        while (k < by.size() && !snk::prepass_same_launch(by[k][0].a, r.a)) ++k;
+        if (k == by.size()) by.emplace_back();
+        by[k].push_back(r);
+    }
+    for (auto &g : by) {
+        const int blocks = snk::prepass_plan(g.data(), (int)g.size());
+        pp.groups.push_back({(int)pp.rows.size(), (int)g.size(), blocks});
+        pp.rows.insert(pp.rows.end(), g.begin(), g.end());
+    }
+    return pp;
+}
+
+// Of a plan whose rows are in the device table (upload_plan).
+snk_status launch_prepasses(snk_engine *e, const PrepassPlan &pp) {
+    for (const PrepassPlan::Group &g : pp.groups)
+        EHIP(e, snk::launch_prepass_batch(pp.rows.data() + g.begin, e->d_pre + g.begin, g.n, g.blocks, e->stream));
     return SNK_OK;
 }
 
@@ -473,11 +510,16 @@ ItemPlan plan_items(const std::vector<EJob *> &js) {
     return pl;
 }
 
-snk_status upload_plan(snk_engine *e, const ItemPlan &pl) {
+snk_status upload_plan(snk_engine *e, const ItemPlan &pl, const PrepassPlan &pp = {}) {
     snk_status st = grow(e, &e->d_items, &e->items_cap, pl.items.size());
     if (st != SNK_OK) return st;
     st = grow(e, &e->d_joblist, &e->joblist_cap, pl.joblist.size());
     if (st != SNK_OK) return st;
+    st = grow(e, &e->d_pre, &e->pre_cap, pp.rows.size());
+    if (st != SNK_OK) return st;
+    if (!pp.rows.empty())
+        EHIP(e, hipMemcpyAsync(e->d_pre, pp.rows.data(), sizeof(snk::PrepassJob) * pp.rows.size(), hipMemcpyHostToDevice,
+                               e->stream));
     if (!pl.items.empty())
         EHIP(e, hipMemcpyAsync(e->d_items, pl.items.data(), sizeof(int2) * pl.items.size(), hipMemcpyHostToDevice,
                                e->stream));
@@ -674,7 +716,8 @@ snk_status snk_engine_destroy(snk_engine *e) {
         delete kv.second;
     }
     pool_drain(e);
-    void *bufs[] = {e->d_jobs, e->d_init_ptrs, e->d_items, e->d_joblist, e->d_unfinished, e->d_counters, e->d_queues};
+    void *bufs[] = {e->d_jobs, e->d_init_ptrs, e->d_items, e->d_joblist, e->d_pre, e->d_unfinished, e->d_counters,
+                    e->d_queues};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     for (hipEvent_t ev : {e->ev0, e->ev1, e->ev2})
@@ -835,11 +878,14 @@ snk_status snk_engine_run(snk_engine *e) {
     const bool same = e->graph && ids == e->graph_jobs;
     if (!same) {
         drop_graph(e);
-        st = upload_plan(e, pl);
+        const PrepassPlan pp = plan_prepass(e, js);
+        st = upload_plan(e, pl, pp);
         if (st != SNK_OK) return st;
         std::vector<Launch> shapes;
-        for (EJob *j : js) {
-            st = prepass_job(e, *j);
+        bool trials = false;
+        for (const auto &c : pl.classes) trials = trials || (!e->force && !e->tuned.count(c.first));
+        if (trials) {   // which evolve the smoothed volumes
+            st = launch_prepasses(e, pp);
             if (st != SNK_OK) return st;
         }
         st = shapes_for(e, pl, true, shapes);
@@ -853,7 +899,7 @@ snk_status snk_engine_run(snk_engine *e) {
         ok = ok && snk::launch_zero(e->d_counters, 4, e->stream) == hipSuccess;
         ok = ok && snk::launch_zero(reinterpret_cast<unsigned long long *>(e->d_queues), kQueueWords, e->stream) ==
                        hipSuccess;
-        for (EJob *j : js) ok = ok && prepass_job(e, *j) == SNK_OK;
+        ok = ok && launch_prepasses(e, pp) == SNK_OK;
         ok = ok && launch_classes(e, pl, max_target, shapes) == SNK_OK;
         ok = ok && snk::launch_energy_vox_batch(e->d_jobs, e->d_items, (int)pl.items.size(), js[0]->P.dim == 2 ? 2 : 3,
                                                 e->stream) == hipSuccess;
@@ -896,19 +942,21 @@ snk_status snk_engine_step(snk_engine *e, int32_t chunk, int32_t *n_finished) {
     std::vector<EJob *> fresh;
     snk_status st = admit_pending(e, fresh);
     if (st != SNK_OK) return st;
-    for (EJob *j : fresh) {
-        st = prepass_job(e, *j);
-        if (st != SNK_OK) return st;
-        j->prepared = true;
-    }
-    std::vector<EJob *> running;
+    std::vector<EJob *> running, raw;
     for (auto &kv : e->jobs)
-        if (kv.second->state == RUNNING) running.push_back(kv.second);
+        if (kv.second->state == RUNNING) {
+            running.push_back(kv.second);
+            if (!kv.second->prepared) raw.push_back(kv.second);
+        }
     if (running.empty()) return SNK_OK;
+    const PrepassPlan pp = plan_prepass(e, raw);
     ItemPlan pl = plan_items(running);
     if ((int)pl.classes.size() > kMaxClasses) return efail(e, SNK_EINVAL, "too many launch classes");
-    st = upload_plan(e, pl);
+    st = upload_plan(e, pl, pp);
     if (st != SNK_OK) return st;
+    st = launch_prepasses(e, pp);
+    if (st != SNK_OK) return st;
+    for (EJob *j : raw) j->prepared = true;
     std::vector<Launch> shapes;
     st = shapes_for(e, pl, false, shapes);
     if (st != SNK_OK) return st;
@@ -920,7 +968,7 @@ snk_status snk_engine_step(snk_engine *e, int32_t chunk, int32_t *n_finished) {
     EHIP(e, hipEventRecord(e->ev1, e->stream));
     // which jobs have stopped?
     EHIP(e, hipMemsetAsync(e->d_unfinished, 0, sizeof(int) * e->table_cap, e->stream));
-    EHIP(e, snk::launch_count_unfinished(e->d_jobs, e->d_items, (int)pl.items.size(), e->d_unfinished, e->stream));
+    EHIP(e, snk::launch_mark_unfinished(e->d_jobs, e->d_items, (int)pl.items.size(), e->d_unfinished, e->stream));
     std::vector<int> unfinished((size_t)e->table_cap, 0);
     EHIP(e, hipMemcpyAsync(unfinished.data(), e->d_unfinished, sizeof(int) * e->table_cap, hipMemcpyDeviceToHost,
                            e->stream));

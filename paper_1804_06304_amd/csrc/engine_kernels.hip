@@ -19,13 +19,14 @@ __global__ void zero_kernel(unsigned long long *p, int n) {
     if (i < n) p[i] = 0ull;
 }
 
-// Per job: contours that can still evolve (ACTIVE and below the job's iteration target).
-__global__ void count_unfinished_kernel(const JobDev *jobs, const int2 *items, int n_items, int *unfinished) {
+// Per job: whether a contour can still evolve (ACTIVE and below the job's iteration target). Every one that can
+// stores the same 1; counting them by atomics on a word per job took 23 us for ten tiles.
+__global__ void mark_unfinished_kernel(const JobDev *jobs, const int2 *items, int n_items, int *unfinished) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_items) return;
     const int2 it = items[i];
     const DevContour &c = jobs[it.x].st[it.y];
-    if ((c.status & 0x0f) == SNK_ACTIVE && c.iters < jobs[it.x].target) atomicAdd(&unfinished[it.x], 1);
+    if ((c.status & 0x0f) == SNK_ACTIVE && c.iters < jobs[it.x].target) unfinished[it.x] = 1;
 }
 
 }  // namespace
@@ -43,9 +44,9 @@ hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_count_unfinished(const JobDev *jobs, const int2 *items, int n_items, int *unfinished, hipStream_t s) {
+hipError_t launch_mark_unfinished(const JobDev *jobs, const int2 *items, int n_items, int *unfinished, hipStream_t s) {
     if (n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(count_unfinished_kernel, dim3((n_items + 255) / 256), dim3(256), 0, s, jobs, items, n_items,
+    hipLaunchKernelGGL(mark_unfinished_kernel, dim3((n_items + 255) / 256), dim3(256), 0, s, jobs, items, n_items,
                        unfinished);
     return hipGetLastError();
 }

@@ -274,7 +274,7 @@ int evolve_stage_blocks_per_cu(int dim, int lanes, int unroll, int layout);
 hipError_t launch_reset_items(const JobDev *jobs, const int2 *items, int n_items, const DevContour *const *init,
                               hipStream_t s);
 hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s);
-hipError_t launch_count_unfinished(const JobDev *jobs, const int2 *items, int n_items, int *unfinished, hipStream_t s);
+hipError_t launch_mark_unfinished(const JobDev *jobs, const int2 *items, int n_items, int *unfinished, hipStream_t s);
 // Indices of the ACTIVE contours among st[0..n-1] into idx, their number into *count (which must be
 // zero beforehand); the order of the indices is unspecified.
 hipError_t launch_compact_active(const DevContour *st, int n, int *idx, int *count, hipStream_t s);

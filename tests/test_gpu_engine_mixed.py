@@ -1,0 +1,72 @@
+"""The engine's pre-pass takes volumes that agree in raw type and radii in one launch: a mix of types, radii, layouts
+and odd shapes, in batched and served runs, gives every job the bits of the plain path on its volume alone.
+"""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("radii", "centers", "e_mc", "e_vox", "iters", "status", "keep")
+
+
+@pytest.fixture(scope="module")
+def snk():
+    import torch   # before the library: the process then has one HIP runtime
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1804_06304_amd import snk as mod
+    return mod
+
+
+def _jobs():
+    rng = np.random.default_rng(3)
+    out = []
+    for k, (shape, dtype, sigma, hz) in enumerate([
+            ((24, 31, 65), np.uint16, 1.0, 2.0), ((2, 16, 64), np.uint16, 1.0, 2.0), ((33, 70, 40), np.uint8, 1.0, 2.0),
+            ((24, 31, 65), np.uint16, 1.0, 1.0), ((17, 17, 17), np.float32, 0.0, 2.0), ((50, 12, 129), np.uint16, 1.0, 2.0),
+            ((20, 40, 30), np.uint8, 3.2, 1.0), ((21, 40, 30), np.uint8, 3.2, 1.0)]):
+        raw = rng.uniform(0.0, 250.0, shape).astype(dtype)
+        h = (1.0, 1.0, hz)
+        p = synth.Params(dim=3, spacing=h, sigma_pre=sigma, dR=0.8, r_max=8.0, r_init=4.0, n_rays=16, n_dirs=162, seed=k)
+        cen = rng.uniform(0.0, 1.0, (9 + k, 3)) * (np.array(shape[::-1]) - 1.0) * h
+        out.append((p, synth.directions_for(3, 162), raw, cen))
+    return out
+
+
+def _plain(snk, p, dirs, raw, cen, layout):
+    ctx = snk.Context(0)
+    ctx.set_params(p)
+    ctx.set_launch(64, 1, layout)
+    ctx.set_directions(dirs)
+    ctx.load_volume(raw)
+    ctx.load_seeds(cen)
+    ctx.evolve(30)
+    ctx.finalize()
+    out = ctx.read()
+    ctx.close()
+    return out
+
+
+@pytest.mark.parametrize("served", [False, True])
+@pytest.mark.parametrize("layout", [0, 2])
+def test_mixed_volumes_equal_plain(snk, served, layout):
+    jobs = _jobs()
+    eng = snk.Engine(0, None, 1 << 30)
+    eng.set_launch(64, 1, 0, layout)
+    late = 3 if served else 0
+    ids = [eng.submit(p, d, raw, cen, n_iter=30) for p, d, raw, cen in jobs[late:]]
+    print("served" if served else "batched", "layout", layout, flush=True)
+    if served:
+        eng.step(10)
+        ids = [eng.submit(p, d, raw, cen, n_iter=30) for p, d, raw, cen in jobs[:late]] + ids
+        for _ in range(4):
+            eng.step(10)
+    else:
+        eng.run()
+        eng.run()
+    for (p, d, raw, cen), j in zip(jobs, ids):
+        got, ref = eng.read(j), _plain(snk, p, d, raw, cen, layout)
+        for k in KEYS:
+            assert np.array_equal(got[k], ref[k], equal_nan=True), (raw.shape, k)
+    eng.close()
