@@ -92,7 +92,17 @@ struct Launch {
 };
 
 constexpr int kMaxClasses = 64;            // launch classes per run (one queue head each)
-constexpr int kQueueWords = kMaxClasses / 2;  // queue heads are ints, zeroed as 64-bit words
+// Status block, zeroed as 64-bit words: sample evaluations (one, one unused), the queue heads (ints), and, in the
+// served mode, whether each job of the table has contours left (ints).
+constexpr int kQueueAt = 2, kFlagsAt = kQueueAt + kMaxClasses / 2;
+
+// Small host data on its way to the device is collected and sent as one copy, which a kernel spreads out: a
+// copy of its own costs the host some 6 us and the stream 3 us, and a job needs five. Data larger than
+// kDirectBytes is copied directly; no more than kStageBytes are collected.
+constexpr size_t kDirectBytes = (size_t)4 << 20, kStageBytes = (size_t)16 << 20;
+constexpr size_t kPieceBytes = 16384;    // spread by one workgroup
+// Contours read back at a time.
+constexpr int kReadItems = 65536;
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -134,9 +144,16 @@ struct snk_engine {
     size_t joblist_cap = 0;
     snk::PrepassJob *d_pre = nullptr;          // the volumes to smooth, by launch
     size_t pre_cap = 0;
-    int *d_unfinished = nullptr;
-    unsigned long long *d_counters = nullptr;  // [0] evolved, [1..] queue heads (as int) / kept
-    int *d_queues = nullptr;                   // one queue head per launch class
+    std::vector<uint64_t> plan_jobs;           // the jobs whose items the lists hold
+    unsigned long long *d_status = nullptr;    // status block (kQueueAt, kFlagsAt)
+    unsigned long long *d_kept = nullptr;
+
+    // uploads not yet sent, their staging buffers (pinned, device), and the same for results
+    std::vector<snk::CopyPiece> up_pieces;
+    std::vector<char> up_data;
+    char *h_stage = nullptr, *d_stage = nullptr, *h_out = nullptr, *d_out = nullptr;
+    size_t h_stage_cap = 0, d_stage_cap = 0, h_out_cap = 0, d_out_cap = 0;
+    bool stage_busy = false;                   // h_stage is being read until the next synchronisation
     hipStream_t own_stream = nullptr;          // created when the caller passes the null stream
     int dim = 0;                               // every job of an engine has the same dimension
 
@@ -185,6 +202,62 @@ snk_status grow(snk_engine *e, T **p, size_t *cap, size_t count) {
     return SNK_OK;
 }
 
+snk_status grow_pinned(snk_engine *e, char **p, size_t *cap, size_t bytes) {
+    if (*p && *cap >= bytes) return SNK_OK;
+    if (*p) (void)hipHostFree(*p);
+    *p = nullptr;
+    *cap = 0;
+    const size_t c = std::max<size_t>(bytes, 4096) * 2;
+    if (hipHostMalloc(reinterpret_cast<void **>(p), c, hipHostMallocDefault) != hipSuccess)
+        return efail(e, SNK_ENOMEM, "hipHostMalloc (engine staging)");
+    *cap = c;
+    return SNK_OK;
+}
+
+// Send what put() collected.
+snk_status flush(snk_engine *e) {
+    if (e->up_pieces.empty()) return SNK_OK;
+    if (e->stage_busy) {
+        EHIP(e, hipStreamSynchronize(e->stream));
+        unstage(e);
+    }
+    const size_t head = sizeof(snk::CopyPiece) * e->up_pieces.size(), bytes = head + e->up_data.size();
+    snk_status st = grow_pinned(e, &e->h_stage, &e->h_stage_cap, bytes);
+    if (st == SNK_OK) st = grow(e, &e->d_stage, &e->d_stage_cap, bytes);
+    if (st != SNK_OK) return st;
+    memcpy(e->h_stage, e->up_pieces.data(), head);
+    memcpy(e->h_stage + head, e->up_data.data(), e->up_data.size());
+    e->stage_busy = true;
+    EHIP(e, hipMemcpyAsync(e->d_stage, e->h_stage, bytes, hipMemcpyHostToDevice, e->stream));
+    EHIP(e, snk::launch_spread(e->d_stage, (int)e->up_pieces.size(), e->stream));
+    e->up_pieces.clear();
+    e->up_data.clear();
+    return SNK_OK;
+}
+
+// Copy src to dst, and to dst2 if given (device memory, 4-byte words), by the next flush.
+snk_status put(snk_engine *e, void *dst, const void *src, size_t bytes, void *dst2 = nullptr) {
+    if (bytes > kDirectBytes) {
+        EHIP(e, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, e->stream));
+        if (dst2) EHIP(e, hipMemcpyAsync(dst2, src, bytes, hipMemcpyHostToDevice, e->stream));
+        EHIP(e, hipStreamSynchronize(e->stream));
+        unstage(e);
+        return SNK_OK;
+    }
+    if (e->up_data.size() + bytes > kStageBytes) {
+        snk_status st = flush(e);
+        if (st != SNK_OK) return st;
+    }
+    const size_t at = e->up_data.size();
+    e->up_data.insert(e->up_data.end(), static_cast<const char *>(src), static_cast<const char *>(src) + bytes);
+    for (size_t o = 0; o < bytes; o += kPieceBytes) {
+        const unsigned n = (unsigned)std::min(kPieceBytes, bytes - o);
+        for (void *d : {dst, dst2})
+            if (d) e->up_pieces.push_back({static_cast<char *>(d) + o, (unsigned)(at + o), n});
+    }
+    return SNK_OK;
+}
+
 void drop_graph(snk_engine *e) {
     if (e->graph) (void)hipGraphExecDestroy(e->graph);
     e->graph = nullptr;
@@ -193,20 +266,22 @@ void drop_graph(snk_engine *e) {
 
 snk_status ensure_table(snk_engine *e, int need) {
     if (need <= e->table_cap) return SNK_OK;
+    snk_status st = flush(e);   // rows on their way to the old table
+    if (st != SNK_OK) return st;
     int cap = std::max(64, e->table_cap * 2);
     while (cap < need) cap *= 2;
     JobDev *nj = nullptr;
     DevContour **np = nullptr;
-    int *nu = nullptr;
+    unsigned long long *ns = nullptr;
     if (hipMalloc(&nj, sizeof(JobDev) * cap) != hipSuccess || hipMalloc(&np, sizeof(DevContour *) * cap) != hipSuccess ||
-        hipMalloc(&nu, sizeof(int) * cap) != hipSuccess)
+        hipMalloc(&ns, sizeof(unsigned long long) * (kFlagsAt + cap / 2)) != hipSuccess)
         return efail(e, SNK_ENOMEM, "hipMalloc (job table)");
     if (e->d_jobs) (void)hipFree(e->d_jobs);
     if (e->d_init_ptrs) (void)hipFree(e->d_init_ptrs);
-    if (e->d_unfinished) (void)hipFree(e->d_unfinished);
+    if (e->d_status) (void)hipFree(e->d_status);
     e->d_jobs = nj;
     e->d_init_ptrs = np;
-    e->d_unfinished = nu;
+    e->d_status = ns;
     for (int s = e->table_cap; s < cap; ++s) e->free_slots.push_back(s);
     std::sort(e->free_slots.begin(), e->free_slots.end(), std::greater<int>());
     e->h_jobs.resize(cap);
@@ -343,11 +418,9 @@ snk_status admit(snk_engine *e, EJob &j) {
     j.d_sel = reinterpret_cast<int *>(b + o_sel);
     if (!j.borrowed)
         EHIP(e, hipMemcpyAsync(b + o_raw, j.host_raw.data(), j.raw_bytes, hipMemcpyHostToDevice, e->stream));
-    EHIP(e, hipMemcpyAsync(j.d_dirs, j.dirs.data(), j.dirs.size() * 4, hipMemcpyHostToDevice, e->stream));
-    if (j.n > 0) {
-        EHIP(e, hipMemcpyAsync(j.d_init, j.init.data(), sizeof(DevContour) * j.n, hipMemcpyHostToDevice, e->stream));
-        EHIP(e, hipMemcpyAsync(j.d_st, j.init.data(), sizeof(DevContour) * j.n, hipMemcpyHostToDevice, e->stream));
-    }
+    st = put(e, j.d_dirs, j.dirs.data(), j.dirs.size() * 4);
+    if (st == SNK_OK && j.n > 0) st = put(e, j.d_init, j.init.data(), sizeof(DevContour) * j.n, j.d_st);
+    if (st != SNK_OK) return st;
     j.slot = e->free_slots.back();
     e->free_slots.pop_back();
     JobDev d{};
@@ -367,12 +440,12 @@ snk_status admit(snk_engine *e, EJob &j) {
     d.dec = d.cell_of + n;
     for (int i = 0; i < 3; ++i) d.G[i] = j.G[i];
     d.cell = (float)j.cell;
-    d.kept = e->d_counters + 1;
+    d.kept = e->d_kept;
     e->h_jobs[j.slot] = d;
     e->h_init_ptrs[j.slot] = j.d_init;
-    EHIP(e, hipMemcpyAsync(e->d_jobs + j.slot, &e->h_jobs[j.slot], sizeof(JobDev), hipMemcpyHostToDevice, e->stream));
-    EHIP(e, hipMemcpyAsync(e->d_init_ptrs + j.slot, &e->h_init_ptrs[j.slot], sizeof(DevContour *),
-                           hipMemcpyHostToDevice, e->stream));
+    st = put(e, e->d_jobs + j.slot, &e->h_jobs[j.slot], sizeof(JobDev));
+    if (st == SNK_OK) st = put(e, e->d_init_ptrs + j.slot, &e->h_init_ptrs[j.slot], sizeof(DevContour *));
+    if (st != SNK_OK) return st;
     e->staged.push_back(&j);
     j.state = RUNNING;
     j.charged = cap;
@@ -388,6 +461,7 @@ void unstage(snk_engine *e) {
         j->host_raw.shrink_to_fit();
     }
     e->staged.clear();
+    e->stage_busy = false;
 }
 
 // Returns a job's device memory and table row; idempotent (a finished job is released when it
@@ -510,26 +584,30 @@ ItemPlan plan_items(const std::vector<EJob *> &js) {
     return pl;
 }
 
+// Send the lists of a plan, and with them what admission collected.
 snk_status upload_plan(snk_engine *e, const ItemPlan &pl, const PrepassPlan &pp = {}) {
+    e->plan_jobs.clear();
     snk_status st = grow(e, &e->d_items, &e->items_cap, pl.items.size());
+    if (st == SNK_OK) st = grow(e, &e->d_joblist, &e->joblist_cap, pl.joblist.size());
+    if (st == SNK_OK) st = grow(e, &e->d_pre, &e->pre_cap, pp.rows.size());
+    const size_t bytes = sizeof(snk::PrepassJob) * pp.rows.size() + sizeof(int2) * pl.items.size() +
+                         sizeof(int) * pl.joblist.size();
+    if (st == SNK_OK && e->up_data.size() + bytes > kStageBytes) st = flush(e);
     if (st != SNK_OK) return st;
-    st = grow(e, &e->d_joblist, &e->joblist_cap, pl.joblist.size());
-    if (st != SNK_OK) return st;
-    st = grow(e, &e->d_pre, &e->pre_cap, pp.rows.size());
-    if (st != SNK_OK) return st;
-    if (!pp.rows.empty())
-        EHIP(e, hipMemcpyAsync(e->d_pre, pp.rows.data(), sizeof(snk::PrepassJob) * pp.rows.size(), hipMemcpyHostToDevice,
-                               e->stream));
-    if (!pl.items.empty())
-        EHIP(e, hipMemcpyAsync(e->d_items, pl.items.data(), sizeof(int2) * pl.items.size(), hipMemcpyHostToDevice,
-                               e->stream));
-    if (!pl.joblist.empty())
-        EHIP(e, hipMemcpyAsync(e->d_joblist, pl.joblist.data(), sizeof(int) * pl.joblist.size(),
-                               hipMemcpyHostToDevice, e->stream));
-    EHIP(e, hipStreamSynchronize(e->stream));
-    unstage(e);
-    return SNK_OK;
+    const size_t pieces = e->up_pieces.size(), data = e->up_data.size();
+    if (!pp.rows.empty()) st = put(e, e->d_pre, pp.rows.data(), sizeof(snk::PrepassJob) * pp.rows.size());
+    if (st == SNK_OK && !pl.items.empty()) st = put(e, e->d_items, pl.items.data(), sizeof(int2) * pl.items.size());
+    if (st == SNK_OK && !pl.joblist.empty())
+        st = put(e, e->d_joblist, pl.joblist.data(), sizeof(int) * pl.joblist.size());
+    if (st == SNK_OK) st = flush(e);
+    if (st != SNK_OK) {   // the lists are sent anew: only one copy of a list may be on its way
+        e->up_pieces.resize(std::min(pieces, e->up_pieces.size()));
+        e->up_data.resize(std::min(data, e->up_data.size()));
+    }
+    return st;
 }
+
+int *queues(const snk_engine *e) { return reinterpret_cast<int *>(e->d_status + kQueueAt); }
 
 snk::BatchArgs batch_args(snk_engine *e, const ClassKey &k, int b, int end, int cls, int chunk, int tile) {
     snk::BatchArgs a{};
@@ -537,9 +615,9 @@ snk::BatchArgs batch_args(snk_engine *e, const ClassKey &k, int b, int end, int 
     a.jobs = e->d_jobs;
     a.items = e->d_items + b;
     a.n_items = end - b;
-    a.queue = e->d_queues + cls;
+    a.queue = queues(e) + cls;
     a.chunk = chunk;
-    a.counter = e->d_counters;
+    a.counter = e->d_status;
     a.max_D = k.D;
     a.max_M = k.M;
     a.L = k.L;
@@ -604,8 +682,7 @@ snk_status shapes_for(snk_engine *e, const ItemPlan &pl, bool allow_trials, std:
                             T.grid = grid_for(e, k, T, n_items);
                             EHIP(e, snk::launch_reset_items(e->d_jobs, e->d_items + b, n_items, e->d_init_ptrs,
                                                             e->stream));
-                            EHIP(e, snk::launch_zero(reinterpret_cast<unsigned long long *>(e->d_queues), kQueueWords,
-                                                     e->stream));
+                            EHIP(e, snk::launch_zero(e->d_status, kFlagsAt, e->stream));
                             snk::BatchArgs a = batch_args(e, k, b, end, (int)c, trial_iters, tile);
                             EHIP(e, hipEventRecord(e->ev0, e->stream));
                             EHIP(e, snk::launch_evolve_batch(a, k.dim, g, u, e->layout, T.persistent != 0, T.grid,
@@ -630,7 +707,7 @@ snk_status shapes_for(snk_engine *e, const ItemPlan &pl, bool allow_trials, std:
             unstage(e);
             e->tuned[k] = L;
         }
-        L.grid = grid_for(e, k, L, n_items);
+        if (L.persistent) L.grid = grid_for(e, k, L, n_items);
         out.push_back(L);
     }
     return SNK_OK;
@@ -640,15 +717,36 @@ snk_status shapes_for(snk_engine *e, const ItemPlan &pl, bool allow_trials, std:
 
 namespace {
 
-snk_status collect(snk_engine *e, const std::vector<EJob *> &js) {
+// Final states of the jobs of a plan whose items are in the device list, and the sample evaluations of the
+// evolve launches, gathered on the device into one copy.
+snk_status collect(snk_engine *e, const ItemPlan &pl, const std::vector<EJob *> &js) {
+    std::map<int, EJob *> of;
     for (EJob *j : js) {
         j->result.resize((size_t)j->n);
-        if (j->n > 0)
-            EHIP(e, hipMemcpyAsync(j->result.data(), j->d_st, sizeof(DevContour) * j->n, hipMemcpyDeviceToHost,
-                                   e->stream));
+        of[j->slot] = j;
     }
-    EHIP(e, hipStreamSynchronize(e->stream));
-    unstage(e);
+    const int n = (int)pl.items.size();
+    for (int i = 0; i == 0 || i < n; i += kReadItems) {
+        const int m = std::min(n - i, kReadItems);
+        const size_t bytes = 16 + sizeof(DevContour) * (size_t)m;
+        snk_status st = grow(e, &e->d_out, &e->d_out_cap, bytes);
+        if (st == SNK_OK) st = grow_pinned(e, &e->h_out, &e->h_out_cap, bytes);
+        if (st != SNK_OK) return st;
+        EHIP(e, snk::launch_gather(e->d_jobs, e->d_items + i, m, e->d_status, e->d_out, e->stream));
+        EHIP(e, hipMemcpyAsync(e->h_out, e->d_out, bytes, hipMemcpyDeviceToHost, e->stream));
+        EHIP(e, hipStreamSynchronize(e->stream));
+        unstage(e);
+        const DevContour *got = reinterpret_cast<const DevContour *>(e->h_out + 16);
+        EJob *j = nullptr;
+        for (int k = 0; k < m; ++k) {
+            const int2 it = pl.items[i + k];
+            if (!j || j->slot != it.x) j = of[it.x];
+            j->result[it.y] = got[k];
+        }
+        unsigned long long cnt = 0;
+        memcpy(&cnt, e->h_out, sizeof(cnt));
+        e->last_evolved = (int64_t)cnt;
+    }
     const double t = now_ms();
     for (EJob *j : js) {
         j->state = DONE;
@@ -692,8 +790,7 @@ snk_status snk_engine_create(snk_engine **out, int device, void *hip_stream, uin
     if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
         e->cus = prop.multiProcessorCount;
     if (hipEventCreate(&e->ev0) != hipSuccess || hipEventCreate(&e->ev1) != hipSuccess ||
-        hipEventCreate(&e->ev2) != hipSuccess || hipMalloc(&e->d_counters, sizeof(unsigned long long) * 4) != hipSuccess ||
-        hipMalloc(&e->d_queues, sizeof(int) * kMaxClasses) != hipSuccess) {
+        hipEventCreate(&e->ev2) != hipSuccess || hipMalloc(&e->d_kept, sizeof(unsigned long long)) != hipSuccess) {
         snk_engine_destroy(e);
         return SNK_EDEVICE;
     }
@@ -716,10 +813,12 @@ snk_status snk_engine_destroy(snk_engine *e) {
         delete kv.second;
     }
     pool_drain(e);
-    void *bufs[] = {e->d_jobs, e->d_init_ptrs, e->d_items, e->d_joblist, e->d_pre, e->d_unfinished, e->d_counters,
-                    e->d_queues};
+    void *bufs[] = {e->d_jobs, e->d_init_ptrs, e->d_items, e->d_joblist, e->d_pre,
+                    e->d_status, e->d_kept, e->d_stage, e->d_out};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
+    for (void *b : {e->h_stage, e->h_out})
+        if (b) (void)hipHostFree(b);
     for (hipEvent_t ev : {e->ev0, e->ev1, e->ev2})
         if (ev) (void)hipEventDestroy(ev);
     if (e->own_stream) (void)hipStreamDestroy(e->own_stream);
@@ -896,9 +995,7 @@ snk_status snk_engine_run(snk_engine *e) {
         EHIP(e, hipStreamBeginCapture(e->stream, hipStreamCaptureModeThreadLocal));
         bool ok = snk::launch_reset_items(e->d_jobs, e->d_items, (int)pl.items.size(), e->d_init_ptrs, e->stream) ==
                   hipSuccess;
-        ok = ok && snk::launch_zero(e->d_counters, 4, e->stream) == hipSuccess;
-        ok = ok && snk::launch_zero(reinterpret_cast<unsigned long long *>(e->d_queues), kQueueWords, e->stream) ==
-                       hipSuccess;
+        ok = ok && snk::launch_zero(e->d_status, kFlagsAt, e->stream) == hipSuccess;
         ok = ok && launch_prepasses(e, pp) == SNK_OK;
         ok = ok && launch_classes(e, pl, max_target, shapes) == SNK_OK;
         ok = ok && snk::launch_energy_vox_batch(e->d_jobs, e->d_items, (int)pl.items.size(), js[0]->P.dim == 2 ? 2 : 3,
@@ -922,15 +1019,12 @@ snk_status snk_engine_run(snk_engine *e) {
     EHIP(e, hipGraphLaunch(e->graph, e->stream));
     EHIP(e, hipEventRecord(e->ev1, e->stream));
     e->graph_replays += 1;
-    st = collect(e, js);
+    st = collect(e, pl, js);
     if (st != SNK_OK) return st;
     float ms = 0.0f;
     EHIP(e, hipEventElapsedTime(&ms, e->ev0, e->ev1));
     e->last_ms = ms;
     e->last_evolve_ms = 0;
-    unsigned long long cnt = 0;
-    EHIP(e, hipMemcpy(&cnt, e->d_counters, sizeof(cnt), hipMemcpyDeviceToHost));
-    e->last_evolved = (int64_t)cnt;
     return SNK_OK;
 }
 
@@ -952,34 +1046,39 @@ snk_status snk_engine_step(snk_engine *e, int32_t chunk, int32_t *n_finished) {
     const PrepassPlan pp = plan_prepass(e, raw);
     ItemPlan pl = plan_items(running);
     if ((int)pl.classes.size() > kMaxClasses) return efail(e, SNK_EINVAL, "too many launch classes");
-    st = upload_plan(e, pl, pp);
-    if (st != SNK_OK) return st;
-    st = launch_prepasses(e, pp);
-    if (st != SNK_OK) return st;
-    for (EJob *j : raw) j->prepared = true;
+    std::vector<uint64_t> ids;
+    for (const EJob *j : running) ids.push_back(j->id);
+    if (!raw.empty() || ids != e->plan_jobs) {
+        st = upload_plan(e, pl, pp);
+        if (st == SNK_OK) st = launch_prepasses(e, pp);
+        if (st != SNK_OK) return st;
+        for (EJob *j : raw) j->prepared = true;
+        e->plan_jobs = ids;
+    }
     std::vector<Launch> shapes;
     st = shapes_for(e, pl, false, shapes);
     if (st != SNK_OK) return st;
-    EHIP(e, snk::launch_zero(e->d_counters, 4, e->stream));
-    EHIP(e, snk::launch_zero(reinterpret_cast<unsigned long long *>(e->d_queues), kQueueWords, e->stream));
+    const int words = kFlagsAt + e->table_cap / 2;
+    st = grow_pinned(e, &e->h_out, &e->h_out_cap, sizeof(unsigned long long) * words);
+    if (st != SNK_OK) return st;
+    EHIP(e, snk::launch_zero(e->d_status, words, e->stream));
     EHIP(e, hipEventRecord(e->ev0, e->stream));
     st = launch_classes(e, pl, chunk, shapes);
     if (st != SNK_OK) return st;
     EHIP(e, hipEventRecord(e->ev1, e->stream));
     // which jobs have stopped?
-    EHIP(e, hipMemsetAsync(e->d_unfinished, 0, sizeof(int) * e->table_cap, e->stream));
-    EHIP(e, snk::launch_mark_unfinished(e->d_jobs, e->d_items, (int)pl.items.size(), e->d_unfinished, e->stream));
-    std::vector<int> unfinished((size_t)e->table_cap, 0);
-    EHIP(e, hipMemcpyAsync(unfinished.data(), e->d_unfinished, sizeof(int) * e->table_cap, hipMemcpyDeviceToHost,
-                           e->stream));
+    EHIP(e, snk::launch_mark_unfinished(e->d_jobs, e->d_items, (int)pl.items.size(),
+                                        reinterpret_cast<int *>(e->d_status + kFlagsAt), e->stream));
+    EHIP(e, hipMemcpyAsync(e->h_out, e->d_status, sizeof(unsigned long long) * words, hipMemcpyDeviceToHost, e->stream));
     EHIP(e, hipStreamSynchronize(e->stream));
     unstage(e);
     float ms = 0.0f;
     EHIP(e, hipEventElapsedTime(&ms, e->ev0, e->ev1));
     e->last_evolve_ms = ms;
     unsigned long long cnt = 0;
-    EHIP(e, hipMemcpy(&cnt, e->d_counters, sizeof(cnt), hipMemcpyDeviceToHost));
+    memcpy(&cnt, e->h_out, sizeof(cnt));
     e->last_evolved = (int64_t)cnt;
+    const int *unfinished = reinterpret_cast<const int *>(e->h_out) + 2 * kFlagsAt;
     std::vector<EJob *> fin;
     for (EJob *j : running)
         if (unfinished[j->slot] == 0) fin.push_back(j);
@@ -990,7 +1089,7 @@ snk_status snk_engine_step(snk_engine *e, int32_t chunk, int32_t *n_finished) {
     const int dim = fin[0]->P.dim == 2 ? 2 : 3;
     EHIP(e, snk::launch_energy_vox_batch(e->d_jobs, e->d_items, (int)fp.items.size(), dim, e->stream));
     EHIP(e, snk::launch_select_batch(e->d_jobs, e->d_joblist, (int)fp.joblist.size(), dim, e->stream));
-    st = collect(e, fin);
+    st = collect(e, fp, fin);
     if (st != SNK_OK) return st;
     for (EJob *j : fin) release_device(e, *j);
     if (n_finished) *n_finished = (int32_t)fin.size();
@@ -1043,6 +1142,8 @@ snk_status snk_engine_release(snk_engine *e, uint64_t job) {
     auto it = e->jobs.find(job);
     if (it == e->jobs.end()) return efail(e, SNK_EINVAL, "unknown job");
     EJob *j = it->second;
+    snk_status st = flush(e);   // an upload to a released job's memory must not follow its next owner's
+    if (st != SNK_OK) return st;
     if (j->state == PENDING) e->pending.erase(std::find(e->pending.begin(), e->pending.end(), job));
     (void)hipSetDevice(e->device);
     (void)hipStreamSynchronize(e->stream);

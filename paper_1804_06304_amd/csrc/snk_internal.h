@@ -274,6 +274,15 @@ int evolve_stage_blocks_per_cu(int dim, int lanes, int unroll, int layout);
 hipError_t launch_reset_items(const JobDev *jobs, const int2 *items, int n_items, const DevContour *const *init,
                               hipStream_t s);
 hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s);
+// A stage of n pieces followed by their data: piece k's bytes (a multiple of 4) go to its dst.
+struct CopyPiece {
+    void *dst;
+    unsigned at, bytes;   // of the data
+};
+hipError_t launch_spread(const void *stage, int n, hipStream_t s);
+// out = the counter (in 16 bytes), then the states of the items.
+hipError_t launch_gather(const JobDev *jobs, const int2 *items, int n_items, const unsigned long long *counter, void *out,
+                         hipStream_t s);
 hipError_t launch_mark_unfinished(const JobDev *jobs, const int2 *items, int n_items, int *unfinished, hipStream_t s);
 // Indices of the ACTIVE contours among st[0..n-1] into idx, their number into *count (which must be
 // zero beforehand); the order of the indices is unspecified.

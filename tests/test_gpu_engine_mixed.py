@@ -70,3 +70,33 @@ def test_mixed_volumes_equal_plain(snk, served, layout):
         for k in KEYS:
             assert np.array_equal(got[k], ref[k], equal_nan=True), (raw.shape, k)
     eng.close()
+
+
+@pytest.mark.parametrize("served", [False, True])
+def test_many_jobs_and_many_contours_equal_plain(snk, served):
+    """Uploads and results beyond one staging copy: more jobs than the first table holds, and a job whose
+    contours (nearly all outside its volume) are copied directly and read back in more than one part."""
+    rng = np.random.default_rng(11)
+    p = synth.Params(dim=3, sigma_pre=1.0, dR=0.8, r_max=8.0, r_init=4.0, n_rays=16, n_dirs=162)
+    dirs = synth.directions_for(3, 162)
+    jobs = []
+    for k in range(70):
+        raw = rng.integers(0, 250, (12, 14, 16)).astype(np.uint8)
+        jobs.append((raw, rng.uniform(0.0, 11.0, (1 + k % 5, 3))))
+    far = np.full((90001, 3), -50.0)
+    far[::3000] = rng.uniform(0.0, 11.0, far[::3000].shape)
+    jobs.insert(35, (jobs[0][0], far))
+    print("served" if served else "batched", len(jobs), "jobs", flush=True)
+    eng = snk.Engine(0, None, 1 << 30)
+    eng.set_launch(64, 1, 0)
+    ids = [eng.submit(p, dirs, raw, cen, n_iter=30) for raw, cen in jobs]
+    if served:
+        for _ in range(4):
+            eng.step(10)
+    else:
+        eng.run()
+    for (raw, cen), j in list(zip(jobs, ids))[::7]:
+        got, ref = eng.read(j), _plain(snk, p, dirs, raw, cen, 0)
+        for k in KEYS:
+            assert np.array_equal(got[k], ref[k], equal_nan=True), (len(cen), k)
+    eng.close()
