@@ -596,7 +596,7 @@ snk_status run_star(snk_ctx *c, int32_t n_iter, bool standalone) {
         HIPTRY(c, hipEventRecord(c->ev[2], c->stream));
     }
     const int layout = c->layout;
-    HIPTRY(c, snk::launch_star(a, sa, c->P.dim, lanes, layout, c->stream));
+    HIPTRY(c, snk::launch_star(a, sa, c->P.dim, lanes, layout, c->cus, c->stream));
     if (standalone) {
         HIPTRY(c, hipEventRecord(c->ev[3], c->stream));
         c->ev_evo = true;

@@ -263,7 +263,7 @@ size_t evolve_lds_bytes(int dim, int lanes, int M, int tile_cap, bool two_waves 
 size_t evolve_rule_lds(int dim, int lanes, int M);
 bool evolve_lds_accepts(int dim, int lanes, int M, int tile_cap);
 // Star-shaped contours (one wave per contour, n_radial 16).
-hipError_t launch_star(const EvolveArgs &a, const StarArgs &sa, int dim, int lanes, int layout, hipStream_t s);
+hipError_t launch_star(const EvolveArgs &a, const StarArgs &sa, int dim, int lanes, int layout, int cus, hipStream_t s);
 size_t star_lds_bytes(int dim, int D, int M, int lanes);
 // Every direction's radius of contour i set to its R.
 hipError_t launch_star_init(const DevContour *st, float *Rk, int n, int D, hipStream_t s);

@@ -16,15 +16,26 @@ namespace snk {
 namespace {
 
 template <int DIM>
-__host__ __device__ __forceinline__ int star_lds_floats(int D, int M, int NT) {
+__host__ __device__ __forceinline__ int star_lds_floats(int D, int M, int NT, bool few = false) {
     const int per = (draw_floats(NT, M / 2) + 3) & ~3;
-    return per + 4 * D + 2 + 2 * M + (M / 2) * (2 + DIM) + 8 * (NT / 64);
+    return per + 4 * D + 2 + 2 * M + (M / 2) * (2 + DIM) * (few ? 2 : 1) + 8 * (NT / 64);
 }
+
+// Rows of the neighbour table that a lane of the FEW kernel keeps.
+constexpr int kStarRows = 6;
 
 // NT threads per contour (64: one wave; 128: two waves, whose partial sums meet in LDS in wave
 // order).
-template <int DIM, int LAYOUT, int NT>
-__global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs a, StarArgs sa) {
+//
+// FEW: no more contours than the chip holds with 256 registers per lane, D <= kStarRows NT, neighbour rows of one
+// chunk, M / 2 <= NT. An iteration is a chain of waits there (two gathers, the rays' table entries, two reads of
+// neighbour rows, LDS in between) with one or two waves per SIMD to cover them. So the registers take what shortens
+// the chain: the neighbour rows stay in them for the whole launch, four pair-points' gathers are in flight instead
+// of two, and the next iteration's table entries are read during this one. 600 contours, D 642, 60 iterations:
+// 560 -> 514 us; what is left is 1,470 vector instructions per wave and iteration, on half of the SIMDs for two
+// waves, and the chain through LDS. With more contours the other kernel holds four waves per SIMD.
+template <int DIM, int LAYOUT, int NT, bool FEW>
+__global__ __launch_bounds__(NT, FEW ? 2 : (NT == 128 ? 4 : 1)) void star_kernel(EvolveArgs a, StarArgs sa) {
     extern __shared__ float lds[];
     constexpr float RHO = DIM == 3 ? 0.79370052598409973738f : 0.70710678118654752440f;
     constexpr float BALL = DIM == 3 ? 4.18879020478639098462f : 3.14159265358979323846f;
@@ -51,7 +62,8 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
     int *rk = reinterpret_cast<int *>(ray_g + M);
     int *rka = rk + MH;
     float *ru = reinterpret_cast<float *>(rka + MH);
-    float *red = ru + MH * DIM;  // per-wave partials, 8 per wave
+    const int pairs_words = MH * (2 + DIM);                       // FEW: of the second buffer's offset
+    float *red = ru + MH * DIM + (FEW ? pairs_words : 0);         // per-wave partials, 8 per wave
     // lowest ray of each direction this iteration (INT_MAX for none; reset by that ray after use)
     int *own = reinterpret_cast<int *>(red + 8 * NW);
     float *Rg = sa.Rk + (long)cid * D;
@@ -96,6 +108,19 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
     const float hd = 0.5f * RHO * p.dR, hD = 0.5f * p.dR;
     int ran = 0;
     float *Rold = Ra, *Rnew = Rb;
+    const uint4 *nbrow = reinterpret_cast<const uint4 *>(sa.nb);
+    uint4 kept[FEW ? kStarRows : 1];
+    if constexpr (FEW) {
+#pragma unroll
+        for (int b = 0; b < kStarRows; ++b) kept[b] = nbrow[min(t + NT * b, D - 1)];
+        if (budget > 0 && t < MH) {
+            const int k = __float_as_int(dr.pu[t].x);
+            rk[t] = k;
+            rka[t] = sa.anti[k];
+#pragma unroll
+            for (int ax = 0; ax < DIM; ++ax) ru[t * DIM + ax] = p.dirs[k * DIM + ax];
+        }
+    }
 
     for (int it = 0; it < budget && (status & 0x0f) == SNK_ACTIVE; ++it) {
         const int blk = it / dr.K, sl = it - blk * dr.K;
@@ -119,32 +144,49 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
         }
         fr.base = base;
         // the ray pairs' tables entries, once per iteration (the pair-points below read them from LDS)
-        for (int m = t; m < MH; m += NT) {
-            const int k = __float_as_int(pu[m].x);
-            rk[m] = k;
-            rka[m] = sa.anti[k];
+        if constexpr (!FEW) {
+            for (int m = t; m < MH; m += NT) {
+                const int k = __float_as_int(pu[m].x);
+                rk[m] = k;
+                rka[m] = sa.anti[k];
 #pragma unroll
-            for (int ax = 0; ax < DIM; ++ax) ru[m * DIM + ax] = p.dirs[k * DIM + ax];
+                for (int ax = 0; ax < DIM; ++ax) ru[m * DIM + ax] = p.dirs[k * DIM + ax];
+            }
         }
         __syncthreads();
+        // FEW: the next iteration's entries, on their way until this one's pair-points are done (its draws are
+        // there: of this block, or of the next, which the block's first iteration drew before the barrier)
+        int next_k = 0, next_ka = 0;
+        float next_u[3] = {0.0f, 0.0f, 0.0f};
+        if constexpr (FEW) {
+            if (t < MH) {
+                const int sn = sl + 1 == dr.K ? dr.slot((blk + 1) & 1, 0) : dr.slot(blk & 1, sl + 1);
+                next_k = __float_as_int(dr.pu[sn * MH + t].x);
+                next_ka = sa.anti[next_k];
+#pragma unroll
+                for (int ax = 0; ax < DIM; ++ax) next_u[ax] = p.dirs[next_k * DIM + ax];
+            }
+        }
         float accE = 0.0f, accc[3] = {0.0f, 0.0f, 0.0f};
         // pair-points q = t + NT j: pair m = q / 16, radial index l = q % 16 (one DPP row per pair);
-        // two of them in flight, consumed in order
+        // H of them in flight, consumed in order
+        constexpr int H = FEW ? 4 : 2;
         const int PP = MH * L;
-        for (int q0 = t; q0 - t < PP; q0 += 2 * NT) {
-            Corners<DIM> cr[2][2];
-            float fv[2][2][3], Rv[2][2], ev[2], uv[2][3];
-            int mv2[2], lv[2], kv[2][2];
-            bool on[2];
+        for (int q0 = t; q0 - t < PP; q0 += H * NT) {
+            Corners<DIM> cr[H][2];
+            float fv[H][2][3], Rv[H][2], ev[H], uv[H][3];
+            int mv2[H], lv[H], kv[H][2];
+            bool on[H];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < H; ++h) {
                 const int q = q0 + NT * h;
                 on[h] = q < PP;
                 if (!on[h]) continue;
                 const int m = q >> 4, l = q & 15;
                 mv2[h] = m;
                 lv[h] = l;
-                const int k = rk[m], ka = rka[m];
+                const int at = FEW && (it & 1) ? pairs_words : 0;
+                const int k = rk[at + m], ka = rka[at + m];
                 kv[h][0] = k;
                 kv[h][1] = ka;
                 float du[3] = {0.0f, 0.0f, 0.0f};
@@ -152,7 +194,7 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
                 for (int ax = 0; ax < 3; ++ax) uv[h][ax] = 0.0f;
 #pragma unroll
                 for (int ax = 0; ax < DIM; ++ax) {
-                    uv[h][ax] = ru[m * DIM + ax];
+                    uv[h][ax] = ru[at + m * DIM + ax];
                     du[ax] = uv[h][ax] * inv_h[ax];
                 }
                 const float e = cube_or_square_root<DIM>(((float)l + pu[m].w) * invL);
@@ -175,7 +217,7 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
                 }
             }
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
+            for (int h = 0; h < H; ++h) {
                 if (!on[h]) continue;
                 const int m = mv2[h], l = lv[h];
                 const float e = ev[h];
@@ -221,6 +263,16 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
                     ray_dir[2 * m + 1] = kv[h][1];
                     ray_g[2 * m + 1] = qv[1] * (Bm - ((float)DIM / Rv[h][1]) * Am);
                 }
+            }
+        }
+        if constexpr (FEW) {
+            // into the buffer that the last iteration read
+            const int to = (it + 1) & 1 ? pairs_words : 0;
+            if (t < MH) {
+                rk[to + t] = next_k;
+                rka[to + t] = next_ka;
+#pragma unroll
+                for (int ax = 0; ax < DIM; ++ax) ru[to + t * DIM + ax] = next_u[ax];
             }
         }
         float E = 0.0f, gc[3] = {0.0f, 0.0f, 0.0f};
@@ -317,19 +369,19 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
         // read without a branch (the padding index D reads +0, which leaves the sum unchanged), so
         // a row's LDS reads are all issued before the first is added
         // (a direction past D loads the last row, unused)
-        const uint4 *nbrow = reinterpret_cast<const uint4 *>(sa.nb);
-        for (int k0 = t; k0 < D; k0 += 4 * NT) {
-            uint4 pre[4];
+        constexpr int ROWS = FEW ? kStarRows : 4;
+        for (int k0 = t; k0 < D; k0 += ROWS * NT) {
+            uint4 pre[ROWS];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) pre[b] = nbrow[min(k0 + NT * b, D - 1) * sa.nb_chunks];
+            for (int b = 0; b < ROWS; ++b) pre[b] = FEW ? kept[b] : nbrow[min(k0 + NT * b, D - 1) * sa.nb_chunks];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
+            for (int b = 0; b < ROWS; ++b) {
                 const int k = k0 + NT * b;
                 if (k < D) {
                     // neighbour mean in the rows' order
                     float ms = 0.0f;
                     int cnt = 0;
-                    for (int ch = 0; ch < sa.nb_chunks; ++ch) {
+                    for (int ch = 0; ch < (FEW ? 1 : sa.nb_chunks); ++ch) {
                         const uint4 w = ch == 0 ? pre[b] : nbrow[k * sa.nb_chunks + ch];
                         const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
                         float rv[8];
@@ -457,30 +509,37 @@ __global__ __launch_bounds__(NT, NT == 128 ? 4 : 1) void star_kernel(EvolveArgs 
     }
 }
 
-template <int DIM, int NT>
+template <int DIM, int NT, bool FEW>
 hipError_t launch_star_t(const EvolveArgs &a, const StarArgs &sa, int layout, hipStream_t s) {
-    const size_t lds = sizeof(float) * (size_t)star_lds_floats<DIM>(a.p.D, a.p.M, NT);
+    const size_t lds = sizeof(float) * (size_t)star_lds_floats<DIM>(a.p.D, a.p.M, NT, FEW);
     switch (layout) {
         case kBufferQuad:
-            hipLaunchKernelGGL((star_kernel<DIM, kBufferQuad, NT>), dim3(a.n), dim3(NT), lds, s, a, sa);
+            hipLaunchKernelGGL((star_kernel<DIM, kBufferQuad, NT, FEW>), dim3(a.n), dim3(NT), lds, s, a, sa);
             break;
         case kBufferPair:
-            hipLaunchKernelGGL((star_kernel<DIM, kBufferPair, NT>), dim3(a.n), dim3(NT), lds, s, a, sa);
+            hipLaunchKernelGGL((star_kernel<DIM, kBufferPair, NT, FEW>), dim3(a.n), dim3(NT), lds, s, a, sa);
             break;
         case kBufferPlain:
-            hipLaunchKernelGGL((star_kernel<DIM, kBufferPlain, NT>), dim3(a.n), dim3(NT), lds, s, a, sa);
+            hipLaunchKernelGGL((star_kernel<DIM, kBufferPlain, NT, FEW>), dim3(a.n), dim3(NT), lds, s, a, sa);
             break;
         default:
-            hipLaunchKernelGGL((star_kernel<DIM, kGlobalPlain, NT>), dim3(a.n), dim3(NT), lds, s, a, sa);
+            hipLaunchKernelGGL((star_kernel<DIM, kGlobalPlain, NT, FEW>), dim3(a.n), dim3(NT), lds, s, a, sa);
             break;
     }
     return hipGetLastError();
 }
 
+template <int DIM, int NT>
+hipError_t launch_star_n(const EvolveArgs &a, const StarArgs &sa, int layout, int cus, hipStream_t s) {
+    const bool few = (long)a.n * (NT / 64) <= 8l * cus && a.p.D <= kStarRows * NT && sa.nb_chunks == 1 &&
+                     a.p.M / 2 <= NT && sizeof(float) * star_lds_floats<DIM>(a.p.D, a.p.M, NT, true) <= 65536;
+    return few ? launch_star_t<DIM, NT, true>(a, sa, layout, s) : launch_star_t<DIM, NT, false>(a, sa, layout, s);
+}
+
 template <int DIM>
-hipError_t launch_star_d(const EvolveArgs &a, const StarArgs &sa, int lanes, int layout, hipStream_t s) {
-    if (lanes == 128) return launch_star_t<DIM, 128>(a, sa, layout, s);
-    if (lanes == 64) return launch_star_t<DIM, 64>(a, sa, layout, s);
+hipError_t launch_star_d(const EvolveArgs &a, const StarArgs &sa, int lanes, int layout, int cus, hipStream_t s) {
+    if (lanes == 128) return launch_star_n<DIM, 128>(a, sa, layout, cus, s);
+    if (lanes == 64) return launch_star_n<DIM, 64>(a, sa, layout, cus, s);
     return hipErrorInvalidValue;
 }
 
@@ -500,9 +559,9 @@ hipError_t launch_star_init(const DevContour *st, float *Rk, int n, int D, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_star(const EvolveArgs &a, const StarArgs &sa, int dim, int lanes, int layout, hipStream_t s) {
+hipError_t launch_star(const EvolveArgs &a, const StarArgs &sa, int dim, int lanes, int layout, int cus, hipStream_t s) {
     if (a.n <= 0 || a.n_iter <= 0) return hipSuccess;
-    return dim == 2 ? launch_star_d<2>(a, sa, lanes, layout, s) : launch_star_d<3>(a, sa, lanes, layout, s);
+    return dim == 2 ? launch_star_d<2>(a, sa, lanes, layout, cus, s) : launch_star_d<3>(a, sa, lanes, layout, cus, s);
 }
 
 size_t star_lds_bytes(int dim, int D, int M, int lanes) {
