@@ -833,7 +833,9 @@ __device__ __forceinline__ void lane_sums(const V &vol, const int *n, const Fram
 // Exact sums of one lane (flags bit 1): the lattice points of the box around the ball of radius
 // s_max, those inside the ball counted (the point set of Eq. (5)), I = J at the voxel itself
 // (clamp-to-edge outside the volume when CLAMP). Box points q = gl, gl + G, ..., x fastest; P
-// points are evaluated per pass with their loads issued first.
+// points are evaluated per pass with their loads issued first. Bound by issue, some 60 instructions per
+// point, 13 points per lane and iteration: so a lane's place in the box takes no integer division and no loop (600
+// contours, 60 iterations, 256 lanes: 343 -> 305 us; seven points per pass 330).
 template <int DIM, int G, bool CLAMP, int LAYOUT>
 __device__ __forceinline__ void lattice_sums(const Vol<DIM, LAYOUT> &vol, const int *n, const Frame<DIM> &fr, const float hh[3],
                                              const float inv_h[3], int gl, float acc[2 + DIM]) {
@@ -846,8 +848,13 @@ __device__ __forceinline__ void lattice_sums(const Vol<DIM, LAYOUT> &vol, const 
         cnt[a] = (int)floorf(fr.off[a] + e) - lo[a] + 1;
     }
     const int total = cnt[0] * cnt[1] * cnt[2];
-    int x = gl % cnt[0], y = (gl / cnt[0]) % cnt[1], z = gl / (cnt[0] * cnt[1]);
-    const int sx = G % cnt[0], sy = G / cnt[0];
+    // the lane's first point and the step of G points as digits of the box (a step carries at most once per digit)
+    const float i0 = 1.0f / (float)cnt[0], i1 = 1.0f / (float)cnt[1];
+    int x, y, z, sx, sy, sz;
+    divmod_small(gl, cnt[0], i0, y, x);
+    divmod_small(y, cnt[1], i1, z, y);
+    divmod_small(G, cnt[0], i0, sy, sx);
+    divmod_small(sy, cnt[1], i1, sz, sy);
     const float smax2 = fr.smax * fr.smax;
     for (int q0 = gl; q0 < total; q0 += G * P) {
         float I[P], d[P][3], r2[P];
@@ -856,12 +863,13 @@ __device__ __forceinline__ void lattice_sums(const Vol<DIM, LAYOUT> &vol, const 
         for (int k = 0; k < P; ++k) {
             const int j[3] = {lo[0] + x, lo[1] + y, lo[2] + z};
             x += sx;
+            y += sy;
+            z += sz;
             if (x >= cnt[0]) {
                 x -= cnt[0];
                 y += 1;
             }
-            y += sy;
-            while (y >= cnt[1]) {
+            if (y >= cnt[1]) {
                 y -= cnt[1];
                 z += 1;
             }
