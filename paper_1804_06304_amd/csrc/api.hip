@@ -743,11 +743,12 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
         HIPTRY(c, hipMemsetAsync(c->d_counters, 0, sizeof(unsigned long long), c->stream));
         HIPTRY(c, hipEventRecord(c->ev[2], c->stream));
     }
-    // A long evolve runs as two launches of half the iterations each: the second one starts only
-    // the contours still active, spread over every CU, instead of leaving them on the CUs the
-    // first launch gave them (the results are identical: every draw depends on the contour's id
-    // and iteration only).
-    int parts = (!trace && n_iter >= 64) ? 2 : 1;
+    // A long evolve of a volume runs as two launches of half the iterations each: the second one starts only
+    // the contours still active, spread over every CU (62,500 lattice contours, 500 iterations 9.22 -> 8.91 ms; the
+    // results are identical: every draw depends on the contour's id and iteration only). Where few have stopped
+    // by then, a launch more costs its start and the boxes' staging (1,200 contours, 100 iterations: one 504 us, two
+    // 521; 8 contours 260, 263), and in 2D the many rounds of resident groups spread them as well (4.86, 4.92 ms).
+    int parts = (!trace && n_iter >= 256 && c->P.dim == 3) ? 2 : 1;
     if (repel) {
         // the neighbours' snapshot and lists are rebuilt before every chunk of repel_every iterations
         parts = 0;
