@@ -7,8 +7,8 @@
 //
 //  - snk_engine_run (batched): every admitted job is evolved from its seeds to its iteration target
 //    and finalised in one captured hipGraph: state reset -> pre-pass -> one evolve launch
-//    per launch class (dim, D, M, L) -> exact energy over all items -> selection, one workgroup per
-//    job. The graph is replayed while the job set is unchanged. The launch shape of each class
+//    per launch class (dim, D, M, L) -> exact energy over all items -> selection, lists over all
+//    items and a workgroup per job. The graph is replayed while the job set is unchanged. The launch shape of each class
 //    (lanes per contour, pair-points in flight, persistent work queue or one workgroup per item) is
 //    picked once by timing short trials of every candidate. Every job keeps its volume in column
 //    pairs (or quad records, on request) next to the FP32 one; launches read that copy unless the
@@ -140,8 +140,10 @@ struct snk_engine {
     // item lists and per-launch scratch
     int2 *d_items = nullptr;
     size_t items_cap = 0;
-    int *d_joblist = nullptr;
+    int2 *d_joblist = nullptr;                 // row in the table, first item
     size_t joblist_cap = 0;
+    int *d_sel_list = nullptr;                 // selection's lists
+    size_t sel_list_cap = 0;
     snk::PrepassJob *d_pre = nullptr;          // the volumes to smooth, by launch
     size_t pre_cap = 0;
     std::vector<uint64_t> plan_jobs;           // the jobs whose items the lists hold
@@ -434,7 +436,6 @@ snk_status admit(snk_engine *e, EJob &j) {
     d.compete = 1;
     const size_t G1 = (size_t)j.grid_cells + 1;
     d.cell_start = j.d_sel;
-    d.cell_fill = j.d_sel + G1;
     d.items = j.d_sel + 2 * G1;
     d.cell_of = d.items + n;
     d.dec = d.cell_of + n;
@@ -563,7 +564,7 @@ struct ItemPlan {
     std::vector<int2> items;
     std::vector<std::pair<ClassKey, std::pair<int, int>>> classes;   // key -> [begin, end)
     std::vector<snk_params> params;                                   // one job's parameters per class
-    std::vector<int> joblist;
+    std::vector<int2> joblist;                                        // row in the table, first item
 };
 
 ItemPlan plan_items(const std::vector<EJob *> &js) {
@@ -572,12 +573,13 @@ ItemPlan plan_items(const std::vector<EJob *> &js) {
     for (const EJob *j : js) {
         ClassKey k{j->P.dim, (int)(j->dirs.size() / j->P.dim), j->P.n_rays, j->P.n_radial};
         by[k].push_back(j);
-        pl.joblist.push_back(j->slot);
     }
     for (auto &kv : by) {
         const int b = (int)pl.items.size();
-        for (const EJob *j : kv.second)
+        for (const EJob *j : kv.second) {
+            pl.joblist.push_back(make_int2(j->slot, (int)pl.items.size()));
             for (int c = 0; c < j->n; ++c) pl.items.push_back(make_int2(j->slot, c));
+        }
         pl.classes.push_back({kv.first, {b, (int)pl.items.size()}});
         pl.params.push_back(kv.second.front()->P);
     }
@@ -590,21 +592,28 @@ snk_status upload_plan(snk_engine *e, const ItemPlan &pl, const PrepassPlan &pp 
     snk_status st = grow(e, &e->d_items, &e->items_cap, pl.items.size());
     if (st == SNK_OK) st = grow(e, &e->d_joblist, &e->joblist_cap, pl.joblist.size());
     if (st == SNK_OK) st = grow(e, &e->d_pre, &e->pre_cap, pp.rows.size());
+    if (st == SNK_OK) st = grow(e, &e->d_sel_list, &e->sel_list_cap, snk::select_batch_ints(pl.items.size()));
     const size_t bytes = sizeof(snk::PrepassJob) * pp.rows.size() + sizeof(int2) * pl.items.size() +
-                         sizeof(int) * pl.joblist.size();
+                         sizeof(int2) * pl.joblist.size();
     if (st == SNK_OK && e->up_data.size() + bytes > kStageBytes) st = flush(e);
     if (st != SNK_OK) return st;
     const size_t pieces = e->up_pieces.size(), data = e->up_data.size();
     if (!pp.rows.empty()) st = put(e, e->d_pre, pp.rows.data(), sizeof(snk::PrepassJob) * pp.rows.size());
     if (st == SNK_OK && !pl.items.empty()) st = put(e, e->d_items, pl.items.data(), sizeof(int2) * pl.items.size());
     if (st == SNK_OK && !pl.joblist.empty())
-        st = put(e, e->d_joblist, pl.joblist.data(), sizeof(int) * pl.joblist.size());
+        st = put(e, e->d_joblist, pl.joblist.data(), sizeof(int2) * pl.joblist.size());
     if (st == SNK_OK) st = flush(e);
     if (st != SNK_OK) {   // the lists are sent anew: only one copy of a list may be on its way
         e->up_pieces.resize(std::min(pieces, e->up_pieces.size()));
         e->up_data.resize(std::min(data, e->up_data.size()));
     }
     return st;
+}
+
+// Exact energies and selection of the jobs of the plan in the device lists.
+hipError_t launch_finalize(snk_engine *e, const ItemPlan &pl, int dim) {
+    return snk::launch_select_batch(e->d_jobs, e->d_items, (int)pl.items.size(), e->d_joblist, (int)pl.joblist.size(),
+                                    e->d_sel_list, dim, e->stream);
 }
 
 int *queues(const snk_engine *e) { return reinterpret_cast<int *>(e->d_status + kQueueAt); }
@@ -813,7 +822,7 @@ snk_status snk_engine_destroy(snk_engine *e) {
         delete kv.second;
     }
     pool_drain(e);
-    void *bufs[] = {e->d_jobs, e->d_init_ptrs, e->d_items, e->d_joblist, e->d_pre,
+    void *bufs[] = {e->d_jobs, e->d_init_ptrs, e->d_items, e->d_joblist, e->d_pre, e->d_sel_list,
                     e->d_status, e->d_kept, e->d_stage, e->d_out};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -998,10 +1007,7 @@ snk_status snk_engine_run(snk_engine *e) {
         ok = ok && snk::launch_zero(e->d_status, kFlagsAt, e->stream) == hipSuccess;
         ok = ok && launch_prepasses(e, pp) == SNK_OK;
         ok = ok && launch_classes(e, pl, max_target, shapes) == SNK_OK;
-        ok = ok && snk::launch_energy_vox_batch(e->d_jobs, e->d_items, (int)pl.items.size(), js[0]->P.dim == 2 ? 2 : 3,
-                                                e->stream) == hipSuccess;
-        ok = ok && snk::launch_select_batch(e->d_jobs, e->d_joblist, (int)pl.joblist.size(), js[0]->P.dim == 2 ? 2 : 3,
-                                            e->stream) == hipSuccess;
+        ok = ok && launch_finalize(e, pl, js[0]->P.dim) == hipSuccess;
         hipError_t ce = hipStreamEndCapture(e->stream, &g);
         if (!ok || ce != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
@@ -1086,9 +1092,7 @@ snk_status snk_engine_step(snk_engine *e, int32_t chunk, int32_t *n_finished) {
     ItemPlan fp = plan_items(fin);
     st = upload_plan(e, fp);
     if (st != SNK_OK) return st;
-    const int dim = fin[0]->P.dim == 2 ? 2 : 3;
-    EHIP(e, snk::launch_energy_vox_batch(e->d_jobs, e->d_items, (int)fp.items.size(), dim, e->stream));
-    EHIP(e, snk::launch_select_batch(e->d_jobs, e->d_joblist, (int)fp.joblist.size(), dim, e->stream));
+    EHIP(e, launch_finalize(e, fp, fin[0]->P.dim));
     st = collect(e, fp, fin);
     if (st != SNK_OK) return st;
     for (EJob *j : fin) release_device(e, *j);

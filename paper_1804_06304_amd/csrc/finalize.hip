@@ -10,9 +10,9 @@
 // rejected once one of them is accepted; that decides the smallest undecided candidate at every step, so the
 // result equals the sequential greedy of the paper's competition (lower energy survives) taken in ascending
 // (E_vox, id) order.
-//   One volume (select_plain): chains of contours per cell, each candidate's overlapping smaller candidates
-//   listed once, then rounds over the lists of those that have any.
-//   Batch (select_job): one workgroup per job, items sorted by cell, rounds that walk the cells again.
+// Contours are chained per cell, each candidate's overlapping smaller candidates are listed once, and rounds over
+// the lists of those that have any decide the rest: of one volume by grid-wide steps (select_plain), of a batch
+// by grid-wide lists and a workgroup per job (launch_select_batch).
 #include <math.h>
 
 #include <algorithm>
@@ -137,17 +137,6 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
     }
 }
 
-template <int DIM>
-__global__ __launch_bounds__(ev_threads<DIM>()) void energy_vox_batch_kernel(const JobDev *jobs, const int2 *items,
-                                                                            int n_items) {
-    const int item = blockIdx.x;
-    if (item >= n_items) return;
-    const int job = __builtin_amdgcn_readfirstlane(items[item].x);
-    const int cid = __builtin_amdgcn_readfirstlane(items[item].y);
-    const JobDev &j = jobs[job];
-    energy_one<DIM>(j.p, j.st + cid, j.e_vox + cid);
-}
-
 enum : int { DEC_NONE = 0, DEC_UNDECIDED = 1, DEC_ACCEPT = 2, DEC_REJECT = 3 };
 
 template <int DIM>
@@ -168,47 +157,6 @@ __device__ __forceinline__ bool overlaps(const DevContour &x, const DevContour &
 // contours (mode 2).
 __device__ __forceinline__ double rank_energy(const JobDev &a, int i, const DevContour &s) {
     return a.mode == 0 ? a.e_vox[i] : (double)s.e_mc;
-}
-
-// One decision step for contour i (no-op unless undecided): reject if an overlapping neighbour is
-// accepted, accept if it has the smallest (E_vox, id) among its undecided overlapping neighbours.
-// Decisions of other contours may change concurrently; every decision taken is final and
-// correct whatever the interleaving, since a contour is accepted only once every overlapping
-// contour with a smaller key has been rejected.
-template <int DIM>
-__device__ int decide(const JobDev &a, int i) {
-    volatile int *dec = a.dec;
-    if (dec[i] != DEC_UNDECIDED) return dec[i];
-    const Geometry &g = a.p.g;
-    const DevContour si = a.st[i];
-    const double ei = rank_energy(a, i, si);
-    const int cell = a.cell_of[i];
-    const int gi[3] = {cell % a.G[0], (cell / a.G[0]) % a.G[1], cell / (a.G[0] * a.G[1])};
-    bool accepted_nb = false, minimal = true;
-    for (int dz = (DIM == 3 ? -1 : 0); dz <= (DIM == 3 ? 1 : 0) && !accepted_nb; ++dz)
-        for (int dy = -1; dy <= 1 && !accepted_nb; ++dy)
-            for (int dx = -1; dx <= 1 && !accepted_nb; ++dx) {
-                const int cx = gi[0] + dx, cy = gi[1] + dy, cz = gi[2] + dz;
-                if (cx < 0 || cy < 0 || cz < 0 || cx >= a.G[0] || cy >= a.G[1] || cz >= a.G[2]) continue;
-                const int c = (cz * a.G[1] + cy) * a.G[0] + cx;
-                for (int q = a.cell_start[c]; q < a.cell_start[c + 1]; ++q) {
-                    const int j = a.items[q];
-                    if (j == i) continue;
-                    const int dj = dec[j];
-                    if (dj == DEC_REJECT) continue;
-                    const DevContour sj = a.st[j];
-                    if (!overlaps<DIM>(si, sj, g.h)) continue;
-                    if (dj == DEC_ACCEPT) {
-                        accepted_nb = true;
-                        break;
-                    }
-                    const double ej = rank_energy(a, j, sj);
-                    if (ej < ei || (ej == ei && sj.id < si.id)) minimal = false;
-                }
-            }
-    const int d = accepted_nb ? DEC_REJECT : (minimal ? DEC_ACCEPT : DEC_UNDECIDED);
-    if (d != DEC_UNDECIDED) dec[i] = d;
-    return d;
 }
 
 // Whether contour i is a candidate of the selection (final: stopped contours at or below E0; culling
@@ -232,83 +180,6 @@ __device__ __forceinline__ int grid_cell(const JobDev &a, const DevContour &s) {
     return (gi[2] * a.G[1] + gi[1]) * a.G[0] + gi[0];
 }
 
-// Candidate flag and grid cell of contour i; counts the cell's members in cell_start[cell + 1].
-template <int DIM>
-__device__ __forceinline__ void bin_one(const JobDev &a, int i) {
-    const DevContour s = a.st[i];
-    const bool cand = is_candidate(a, s, rank_energy(a, i, s));
-    // a culling pass without competition keeps every candidate
-    a.dec[i] = cand ? (a.mode == 1 && !a.compete ? DEC_ACCEPT : DEC_UNDECIDED) : DEC_NONE;
-    int cell = -1;
-    if (cand) {
-        cell = grid_cell<DIM>(a, s);
-        atomicAdd(&a.cell_start[cell + 1], 1);
-    }
-    a.cell_of[i] = cell;
-}
-
-// Inclusive running sum of one tile of SEL_T * 8 cell counts cs[base ..] (in place), plus carry: 8
-// consecutive cells per thread, a shuffle scan of the thread sums inside each wave, the wave totals
-// scanned through LDS (ws: SEL_T / 64 + 1 ints). Returns the tile's total (every thread).
-__device__ int scan_tile(int *cs, int G, int base, int carry, int *ws) {
-    constexpr int V = 8;
-    constexpr int W = SEL_T / 64;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int i0 = base + t * V;
-    int v[V];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < V; ++k) {
-        s += i0 + k < G ? cs[i0 + k] : 0;
-        v[k] = s;
-    }
-    int incl = s;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += y;
-    }
-    if (lane == 63) ws[w] = incl;
-    __syncthreads();
-    if (w == 0) {
-        const int x = lane < W ? ws[lane] : 0;
-        int sc = x;
-#pragma unroll
-        for (int d = 1; d < W; d <<= 1) {
-            const int y = __shfl_up(sc, d, 64);
-            if (lane >= d) sc += y;
-        }
-        if (lane < W) ws[lane] = sc - x;  // exclusive prefix of the wave totals
-        if (lane == W - 1) ws[W] = sc;    // tile total
-    }
-    __syncthreads();
-    const int off = carry + ws[w] + (incl - s);
-#pragma unroll
-    for (int k = 0; k < V; ++k)
-        if (i0 + k < G) cs[i0 + k] = v[k] + off;
-    const int total = ws[W];
-    __syncthreads();
-    return total;
-}
-
-constexpr int SCAN_TILE = SEL_T * 8;
-
-// Inclusive running sum of the cell counts cell_start[1..G], in place, by one workgroup (tile by
-// tile, carrying the total across).
-__device__ void scan_cells(const JobDev &a, int G, int *ws) {
-    int *cs = a.cell_start + 1;
-    int carry = 0;
-    for (int base = 0; base < G; base += SCAN_TILE) carry += scan_tile(cs, G, base, carry, ws);
-}
-
-__device__ __forceinline__ void scatter_one(const JobDev &a, int i) {
-    const int cell = a.cell_of[i];
-    if (cell >= 0) {
-        const int pos = atomicAdd(&a.cell_fill[cell], 1);
-        a.items[a.cell_start[cell] + pos] = i;
-    }
-}
-
 // Outcome of the decisions for contour i: keep flag (final selection) or retirement (culling pass);
 // returns 1 when it counts (kept, or retired).
 __device__ __forceinline__ int apply_one(const JobDev &a, int i, int d) {
@@ -325,42 +196,6 @@ __device__ __forceinline__ int apply_one(const JobDev &a, int i, int d) {
         return 1;
     }
     return 0;
-}
-
-// Whole selection of one job by one workgroup.
-template <int DIM>
-__device__ void select_job(const JobDev &a) {
-    __shared__ int ws[SEL_T / 64 + 1];
-    const int t = threadIdx.x;
-    const int n = a.n;
-    const int G = a.G[0] * a.G[1] * a.G[2];
-    volatile int *dec = a.dec;
-    for (int c = t; c <= G; c += SEL_T) a.cell_start[c] = 0;
-    for (int c = t; c < G; c += SEL_T) a.cell_fill[c] = 0;
-    __syncthreads();
-    for (int i = t; i < n; i += SEL_T) bin_one<DIM>(a, i);
-    __syncthreads();
-    scan_cells(a, G, ws);
-    __syncthreads();
-    for (int i = t; i < n; i += SEL_T) scatter_one(a, i);
-    __syncthreads();
-    bool any = true;
-    while (any) {
-        int local = 0;
-        for (int i = t; i < n; i += SEL_T) local |= decide<DIM>(a, i) == DEC_UNDECIDED ? 1 : 0;
-        __threadfence_block();
-        any = __syncthreads_or(local) != 0;
-    }
-    unsigned long long count = 0;
-    for (int i = t; i < n; i += SEL_T) count += apply_one(a, i, dec[i]);
-    if (count) atomicAdd(a.kept, count);
-}
-
-template <int DIM>
-__global__ __launch_bounds__(SEL_T) void select_batch_kernel(const JobDev *jobs, const int *job_list, int n_jobs) {
-    if ((int)blockIdx.x >= n_jobs) return;
-    const JobDev &j = jobs[__builtin_amdgcn_readfirstlane(job_list[blockIdx.x])];
-    if (j.n > 0) select_job<DIM>(j);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -385,6 +220,10 @@ constexpr int kSelList = 8;
 // Contours above which grid-wide rounds come before the one-workgroup rounds: 32 candidates a step, one
 // workgroup takes a thousand in the time of a few launches.
 constexpr int kSelRounds = 1024;
+// Batch: items that have a list (the others walk their cells again), and contours that a job's workgroup takes at
+// a time.
+constexpr int kListItems = 1 << 20;
+constexpr int kSelChunk = 4096;
 
 __global__ __launch_bounds__(SG_T) void sel_clear_kernel(JobDev a, int G) {
     const int i = blockIdx.x * SG_T + threadIdx.x;
@@ -444,31 +283,32 @@ __device__ __forceinline__ void walk_smaller(const JobDev &a, int i, int sub, F 
     }
 }
 
-// Step 3.
+// Step 3 for candidate i by a group of lanes: accepted at once if no overlapping candidate has a smaller key, else
+// their number and the first of them into mine (null: none are kept), and true.
 template <int DIM>
-__global__ __launch_bounds__(SG_T) void sel_list_kernel(JobDev a, int *list, int *work, int *m) {
-    constexpr int LN = sel_lanes<DIM>();
-    const int i = (int)(((long)blockIdx.x * SG_T + threadIdx.x) / LN), sub = threadIdx.x & (LN - 1);
-    if (i >= a.n || a.dec[i] != DEC_UNDECIDED) return;   // whole groups
-    int *mine = list + (long)i * kSelList;
+__device__ __forceinline__ bool list_one(const JobDev &a, int i, int sub, int *mine) {
     int total = 0;
     const int lane = threadIdx.x & 63;
     walk_smaller<DIM>(a, i, sub, [&](int j, bool hit, uint64_t group) {
         const uint64_t h = __builtin_amdgcn_ballot_w64(hit) & group;
         const int pos = total + __builtin_popcountll(h & ((1ull << lane) - 1ull));
-        if (hit && pos + 1 < kSelList) mine[1 + pos] = j;
+        if (mine && hit && pos + 1 < kSelList) mine[1 + pos] = j;
         total += __builtin_popcountll(h);
         return false;
     });
     if (sub == 0) {
-        if (total == 0) {
-            // no other lane reads this decision in this launch
-            a.dec[i] = DEC_ACCEPT;
-        } else {
-            mine[0] = total;
-            work[atomicAdd(m, 1)] = i;
-        }
+        if (total == 0) a.dec[i] = DEC_ACCEPT;   // no other lane reads this decision in this launch
+        else if (mine) mine[0] = total;
     }
+    return total != 0;
+}
+
+template <int DIM>
+__global__ __launch_bounds__(SG_T) void sel_list_kernel(JobDev a, int *list, int *work, int *m) {
+    constexpr int LN = sel_lanes<DIM>();
+    const int i = (int)(((long)blockIdx.x * SG_T + threadIdx.x) / LN), sub = threadIdx.x & (LN - 1);
+    if (i >= a.n || a.dec[i] != DEC_UNDECIDED) return;   // whole groups
+    if (list_one<DIM>(a, i, sub, list + (long)i * kSelList) && sub == 0) work[atomicAdd(m, 1)] = i;
 }
 
 // A decision that other waves may be taking: a value read early only delays the reader's own decision.
@@ -479,11 +319,10 @@ __device__ __forceinline__ int decision(const JobDev &a, int i) {
 
 // One decision step of candidate i by a group of lanes (every decision taken is final and correct whatever
 // the others do meanwhile): accepted neighbour -> reject; none undecided -> accept. Returns whether it
-// stays undecided. SCOPE: of the waves that decide concurrently.
+// stays undecided. mine: its list (null: none). SCOPE: of the waves that decide concurrently.
 template <int DIM, int SCOPE>
-__device__ __forceinline__ bool decide_group(const JobDev &a, const int *list, int i, int sub) {
-    const int *mine = list + (long)i * kSelList;
-    const int cnt = mine[0];
+__device__ __forceinline__ bool decide_group(const JobDev &a, const int *mine, int i, int sub) {
+    const int cnt = mine ? mine[0] : kSelList;
     bool accepted = false, open = false;
     if (cnt < kSelList) {
         const int d = sub < cnt ? decision<SCOPE>(a, mine[1 + sub]) : (int)DEC_REJECT;
@@ -515,7 +354,7 @@ __global__ __launch_bounds__(SG_T) void sel_round_kernel(JobDev a, const int *li
     if (k >= *m) return;   // whole groups
     const int i = work[k];
     if (__shfl(decision<__HIP_MEMORY_SCOPE_AGENT>(a, i), 0, LN) != DEC_UNDECIDED) return;
-    if (decide_group<DIM, __HIP_MEMORY_SCOPE_AGENT>(a, list, i, sub) && sub == 0) atomicAdd(&left[r % 3], 1);
+    if (decide_group<DIM, __HIP_MEMORY_SCOPE_AGENT>(a, list + (long)i * kSelList, i, sub) && sub == 0) atomicAdd(&left[r % 3], 1);
 }
 
 // Steps 4 and 5 by one workgroup: rounds until nothing on the work list is undecided, then (apply) the outcome
@@ -533,7 +372,7 @@ __global__ __launch_bounds__(SEL_T) void sel_finish_kernel(JobDev a, const int *
         for (int k = t / LN; k < m; k += SEL_T / LN) {
             const int i = work[k];
             if (__shfl(decision<SCOPE>(a, i), 0, LN) == DEC_UNDECIDED)
-                local |= decide_group<DIM, SCOPE>(a, list, i, sub) ? 1 : 0;
+                local |= decide_group<DIM, SCOPE>(a, list + (long)i * kSelList, i, sub) ? 1 : 0;
         }
         __threadfence_block();
         any = __syncthreads_or(local) != 0;
@@ -619,6 +458,98 @@ hipError_t select_plain(const JobDev &j, int *list, int *work, hipStream_t s) {
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------
+// Selection of a batch
+// ---------------------------------------------------------------------------------------------
+//
+// The same steps over the items of many jobs: clear, link at the end of the exact energy, list, and a workgroup per
+// job for the rounds and the outcome, which takes kSelChunk contours at a time and gathers their undecided
+// candidates in LDS. Bound by latency, 4 to 5 us a launch: 24 jobs of up to 300 contours 14 us, against 60 for one
+// workgroup per job that sorted its cells and walked them again every round.
+
+__global__ __launch_bounds__(SEL_T) void sel_clear_batch_kernel(const JobDev *jobs, const int2 *job_list) {
+    const JobDev &j = jobs[__builtin_amdgcn_readfirstlane(job_list[blockIdx.x].x)];
+    const int G = j.G[0] * j.G[1] * j.G[2];
+    for (int c = threadIdx.x; c < G; c += SEL_T) j.cell_start[c] = 0;
+}
+
+template <int DIM>
+__global__ __launch_bounds__(ev_threads<DIM>()) void energy_link_batch_kernel(const JobDev *jobs, const int2 *items) {
+    const int2 it = items[blockIdx.x];
+    const int job = __builtin_amdgcn_readfirstlane(it.x), cid = __builtin_amdgcn_readfirstlane(it.y);
+    const JobDev &j = jobs[job];
+    energy_one<DIM>(j.p, j.st + cid, j.e_vox + cid, true);
+    if (threadIdx.x == 0) {
+        // this thread wrote the state and energy it reads here
+        const DevContour s = j.st[cid];
+        link_one<DIM>(j, cid, s, j.e_vox[cid]);
+    }
+}
+
+template <int DIM>
+__global__ __launch_bounds__(SG_T) void sel_list_batch_kernel(const JobDev *jobs, const int2 *items, int n_items,
+                                                              int *list) {
+    constexpr int LN = sel_lanes<DIM>();
+    const long q = ((long)blockIdx.x * SG_T + threadIdx.x) / LN;
+    if (q >= n_items) return;   // whole groups
+    const int2 it = items[q];
+    const JobDev a = jobs[it.x];
+    if (a.dec[it.y] != DEC_UNDECIDED) return;
+    list_one<DIM>(a, it.y, threadIdx.x & (LN - 1), q < kListItems ? list + q * kSelList : nullptr);
+}
+
+// job_list: the job's row of the table and its first item (its contours' items follow each other).
+template <int DIM>
+__global__ __launch_bounds__(SEL_T) void sel_finish_batch_kernel(const JobDev *jobs, const int2 *job_list,
+                                                                 const int *list) {
+    __shared__ int open[kSelChunk];
+    __shared__ int m;
+    constexpr int LN = sel_lanes<DIM>();
+    constexpr int SCOPE = __HIP_MEMORY_SCOPE_WORKGROUP;
+    const int t = threadIdx.x, sub = t & (LN - 1);
+    const int base = __builtin_amdgcn_readfirstlane(job_list[blockIdx.x].y);
+    const JobDev &a = jobs[__builtin_amdgcn_readfirstlane(job_list[blockIdx.x].x)];
+    const int n = a.n;
+    bool any = n > 0;
+    while (any) {
+        int local = 0;
+        for (int c0 = 0; c0 < n; c0 += kSelChunk) {
+            if (t == 0) m = 0;
+            __syncthreads();
+            for (int i = c0 + t; i < min(n, c0 + kSelChunk); i += SEL_T)
+                if (decision<SCOPE>(a, i) == DEC_UNDECIDED) open[atomicAdd(&m, 1)] = i;
+            __syncthreads();
+            const int cnt = m;
+            for (int k = t / LN; k < cnt; k += SEL_T / LN) {
+                const int i = open[k];
+                const long q = (long)base + i;
+                local |= decide_group<DIM, SCOPE>(a, q < kListItems ? list + q * kSelList : nullptr, i, sub) ? 1 : 0;
+            }
+            __threadfence_block();
+            __syncthreads();
+        }
+        any = __syncthreads_or(local) != 0;
+    }
+    int count = 0;
+    for (int i = t; i < n; i += SEL_T) count += apply_one(a, i, decision<SCOPE>(a, i));
+    for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, 64);
+    if ((t & 63) == 0 && count) atomicAdd(a.kept, (unsigned long long)count);
+}
+
+template <int DIM>
+hipError_t select_batch(const JobDev *jobs, const int2 *items, int n_items, const int2 *job_list, int n_jobs, int *list,
+                        hipStream_t s) {
+    hipLaunchKernelGGL(sel_clear_batch_kernel, dim3(n_jobs), dim3(SEL_T), 0, s, jobs, job_list);
+    if (n_items > 0) {
+        constexpr int per = SG_T / sel_lanes<DIM>();
+        hipLaunchKernelGGL(energy_link_batch_kernel<DIM>, dim3(n_items), dim3(ev_threads<DIM>()), 0, s, jobs, items);
+        hipLaunchKernelGGL(sel_list_batch_kernel<DIM>, dim3((n_items + per - 1) / per), dim3(SG_T), 0, s, jobs, items,
+                           n_items, list);
+        hipLaunchKernelGGL(sel_finish_batch_kernel<DIM>, dim3(n_jobs), dim3(SEL_T), 0, s, jobs, job_list, list);
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
 namespace {
@@ -648,20 +579,13 @@ hipError_t launch_select(const JobDev &j, int dim, int *list, int *work, hipStre
 
 size_t select_list_ints(int64_t n) { return (size_t)n * kSelList; }
 
-hipError_t launch_energy_vox_batch(const JobDev *jobs, const int2 *items, int n_items, int dim, hipStream_t s) {
-    if (n_items <= 0) return hipSuccess;
-    if (dim == 2)
-        hipLaunchKernelGGL(energy_vox_batch_kernel<2>, dim3(n_items), dim3(ev_threads<2>()), 0, s, jobs, items, n_items);
-    else
-        hipLaunchKernelGGL(energy_vox_batch_kernel<3>, dim3(n_items), dim3(ev_threads<3>()), 0, s, jobs, items, n_items);
-    return hipGetLastError();
+hipError_t launch_select_batch(const JobDev *jobs, const int2 *items, int n_items, const int2 *job_list, int n_jobs,
+                               int *list, int dim, hipStream_t s) {
+    if (n_jobs <= 0) return hipSuccess;
+    return dim == 2 ? select_batch<2>(jobs, items, n_items, job_list, n_jobs, list, s)
+                    : select_batch<3>(jobs, items, n_items, job_list, n_jobs, list, s);
 }
 
-hipError_t launch_select_batch(const JobDev *jobs, const int *job_list, int n_jobs, int dim, hipStream_t s) {
-    if (n_jobs <= 0) return hipSuccess;
-    if (dim == 2) hipLaunchKernelGGL(select_batch_kernel<2>, dim3(n_jobs), dim3(SEL_T), 0, s, jobs, job_list, n_jobs);
-    else hipLaunchKernelGGL(select_batch_kernel<3>, dim3(n_jobs), dim3(SEL_T), 0, s, jobs, job_list, n_jobs);
-    return hipGetLastError();
-}
+size_t select_batch_ints(size_t n_items) { return std::min(n_items, (size_t)kListItems) * kSelList; }
 
 }  // namespace snk

@@ -177,7 +177,7 @@ struct JobDev {
     int n;
     int target;                  // iteration count every contour evolves to
     float e0;
-    int *cell_start, *cell_fill, *items, *cell_of, *dec;   // selection scratch
+    int *cell_start, *items, *cell_of, *dec;   // selection scratch
     int G[3];
     float cell;
     unsigned long long *kept;    // final selection: contours kept; culling pass: contours retired
@@ -293,8 +293,10 @@ hipError_t launch_compact_active(const DevContour *st, int n, int *idx, int *cou
 // j.kept is the first of four 64-bit words, all written (kept, then counters).
 hipError_t launch_select(const JobDev &j, int dim, int *list, int *work, hipStream_t s);
 size_t select_list_ints(int64_t n);
-hipError_t launch_energy_vox_batch(const JobDev *jobs, const int2 *items, int n_items, int dim, hipStream_t s);
-hipError_t launch_select_batch(const JobDev *jobs, const int *job_list, int n_jobs, int dim, hipStream_t s);
+// Exact energies and selection of the jobs of a list (row of the table, first item); list of select_batch_ints.
+hipError_t launch_select_batch(const JobDev *jobs, const int2 *items, int n_items, const int2 *job_list, int n_jobs,
+                               int *list, int dim, hipStream_t s);
+size_t select_batch_ints(size_t n_items);
 
 }  // namespace snk
 

@@ -100,3 +100,49 @@ def test_many_jobs_and_many_contours_equal_plain(snk, served):
         for k in KEYS:
             assert np.array_equal(got[k], ref[k], equal_nan=True), (len(cen), k)
     eng.close()
+
+
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("served", [False, True])
+def test_dense_competition_equals_plain(snk, dim, served):
+    """Selection of a batch: jobs with none, one, a few and more contours than a job's workgroup takes at a time, so
+    dense that a candidate has more overlapping rivals than its list holds."""
+    rng = np.random.default_rng(17)
+    shape = (24, 40, 44) if dim == 3 else (1, 150, 160)
+    top = (np.array(shape[::-1]) - 1.0)
+    p = synth.Params(dim=dim, sigma_pre=1.0, dR=0.8, r_max=8.0, r_init=5.0, n_rays=16, e0=10.0,
+                     n_dirs=64 if dim == 2 else 162)
+    dirs = synth.directions_for(dim, p.n_dirs)
+    raw = rng.integers(0, 250, shape).astype(np.uint8)
+    jobs = []
+    for n in (0, 1, 31, 700, 4096, 9001):
+        cen = rng.uniform(0.0, 1.0, (n, 3)) * top
+        cen[:, dim:] = 0.0
+        jobs.append(cen)
+    print("served" if served else "batched", dim, flush=True)
+    eng = snk.Engine(0, None, 1 << 30)
+    eng.set_launch(64, 1, 0)
+    ids = [eng.submit(p, dirs, raw, cen, n_iter=6) for cen in jobs]
+    if served:
+        eng.step(6)
+    else:
+        eng.run()
+    for cen, j in zip(jobs, ids):
+        got = eng.read(j)
+        if len(cen) == 0:
+            assert len(got["keep"]) == 0
+            continue
+        ctx = snk.Context(0)
+        ctx.set_params(p)
+        ctx.set_launch(64, 1, 0)
+        ctx.set_directions(dirs)
+        ctx.load_volume(raw)
+        ctx.load_seeds(cen)
+        ctx.evolve(6)
+        ctx.finalize()
+        ref = ctx.read()
+        ctx.close()
+        assert 0 < ref["keep"].sum() <= len(cen)
+        for k in KEYS:
+            assert np.array_equal(got[k], ref[k], equal_nan=True), (len(cen), k)
+    eng.close()
