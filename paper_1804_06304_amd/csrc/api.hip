@@ -326,7 +326,7 @@ snk_status run_prepass(snk_ctx *c) {
     if (layout < 0)
         return fail(c, SNK_EINVAL, "volume too large for the requested layout");
     // a 2D image whose contours will evolve in boxes (mc_shape) is read from the plain copy alone: without
-    // the column pairs the pre-pass writes a third of the bytes (8192^2: 245 -> 172 us)
+    // the column pairs the pre-pass writes a third of the bytes (8192^2: 245 -> 127 us)
     if (c->layout_req == 0 && c->P.dim == 2 && layout == snk::kBufferPair && c->cus > 0 && c->n > 4 * (int64_t)c->cus &&
         c->tile_req < 0)
         layout = snk::kBufferPlain;

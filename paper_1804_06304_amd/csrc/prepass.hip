@@ -63,41 +63,48 @@ hipError_t launch_typed(const PrepassJob &one, const PrepassJob *jobs, int n, in
 }
 }  // namespace
 
-// A workgroup of z_chunk planes filters 2 rz more, so a launch takes as long as its rounds of resident workgroups
-// times z_chunk + 2 rz: the chunk is the one of the least product, at least rz and 2 planes (411 x 387 x 131,
-// sigma 1.6: 5 chunks, one round, 169 us; 6 chunks, a little more than a round, 194; 12 chunks 180).
+// A workgroup's chunk of z planes (an image's rows of tiles) takes 2 rz more, so a launch takes as long as its rounds of
+// resident workgroups times chunk + 2 rz: the chunk is the one of the least product, at least rz and 2 planes (411 x 387
+// x 131, sigma 1.6: 5 chunks, one round, 169 us; 6 chunks, a little more than a round, 194; 12 chunks 180).
 int prepass_plan(PrepassJob *jobs, int n) {
     if (n <= 0) return 0;
     const int ty = 4 * prepass_rows_per_thread(jobs[0].a), tx = jobs[0].a.Jq ? 63 : 64;
     int top = 0;
     for (int i = 0; i < n; ++i) {
-        jobs[i].cut.bx = (jobs[i].a.nx + tx - 1) / tx;
-        jobs[i].cut.by = (jobs[i].a.ny + ty - 1) / ty;
-        top = std::max(top, jobs[i].a.nz);
+        PrepassJob &j = jobs[i];
+        const int rows = (j.a.ny + ty - 1) / ty;
+        const bool image = j.a.nz == 1 && !j.a.Jq;   // marched over by rows of tiles
+        j.cut.bx = (j.a.nx + tx - 1) / tx;
+        j.cut.by = image ? 1 : rows;
+        j.cut.len = image ? rows : j.a.nz;
+        top = std::max(top, j.cut.len);
     }
     int slots = 1024;
     (void)launch_typed(jobs[0], nullptr, 0, 0, nullptr, &slots);
-    const int rz = jobs[0].a.rz, least = std::max(rz, 2);
+    const int rz = jobs[0].a.rz, least = jobs[0].a.nz == 1 ? 1 : std::max(rz, 2);
+    auto groups_of = [](const PrepassJob &j, int chunk) {
+        return (long)j.cut.bx * j.cut.by * ((j.cut.len + chunk - 1) / chunk);
+    };
     int chunk = top;
     long best = 0;
-    for (int c = 1; c <= 64; ++c) {
+    for (int c = 1; c <= top; ++c) {
         const int z = std::max((top + c - 1) / c, least);
         long groups = 0;
-        for (int i = 0; i < n; ++i) groups += (long)jobs[i].cut.bx * jobs[i].cut.by * ((jobs[i].a.nz + z - 1) / z);
+        for (int i = 0; i < n; ++i) groups += groups_of(jobs[i], z);
         const long cost = (groups + slots - 1) / slots * (z + 2 * rz);
         if (c == 1 || cost < best) {
             best = cost;
             chunk = z;
         }
-        if (z == least || groups > 8l * slots) break;
+        if (z == least || groups > 4l * slots) break;
     }
     int first = 0;
     for (int i = 0; i < n; ++i) {
         PrepassJob &j = jobs[i];
         j.first = first;
-        const int k = (j.a.nz + chunk - 1) / chunk;
-        j.cut.z_chunk = (j.a.nz + k - 1) / k;
-        first += j.cut.bx * j.cut.by * ((j.a.nz + j.cut.z_chunk - 1) / j.cut.z_chunk);
+        const int k = (j.cut.len + chunk - 1) / chunk;
+        j.cut.chunk = (j.cut.len + k - 1) / k;
+        first += (int)groups_of(j, j.cut.chunk);
     }
     return first;
 }

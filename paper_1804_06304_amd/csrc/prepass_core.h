@@ -122,7 +122,9 @@ constexpr int rows_evaluated() {
     return ROWS + (SECOND ? 1 : 0);
 }
 
-// Tile (bx, by) of the planes z0 .. z1 - 1 of volume a.
+// Tile (bx, by) of the planes z0 .. z1 - 1 of volume a; of an image (nz = 1) without quad records the tiles (bx, z0 ..
+// z1 - 1), which a workgroup marches over as it does over planes, its next loads in flight (8192^2 u8 alone 154 -> 127
+// us; with quad records 4096^2 71 -> 91, their rows fall on the same channels).
 template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND>
 __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, int z1, float *lds) {
     constexpr int EV = rows_evaluated<ROWS, SECOND>();
@@ -151,6 +153,9 @@ __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, 
     const int tx = t & (EX - 1);
     const int ty = __builtin_amdgcn_readfirstlane(t >> 6);   // row group: one wave
     const long nxy = (long)nx * ny;
+    const bool down = RZ == 0 && !ZMAX && SECOND != 1 && nz == 1;
+    auto plane_of = [&](int zi) { return down ? 0 : zi; };
+    auto first_row = [&](int zi) { return down ? zi * TY : y0; };
     const T *raw = static_cast<const T *>(a->raw);
     const float off = a->i_offset, scale = a->i_scale;
 
@@ -159,11 +164,12 @@ __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, 
     // address and are not stored), so the loads stay in flight while the current plane is filtered
     T pre[NRA][NCA];
     auto fetch = [&](int zi) {
-        const long zoff = (long)min(max(zi, 0), nz - 1) * nxy;
+        const long zoff = (long)min(max(plane_of(zi), 0), nz - 1) * nxy;
+        const int top = first_row(zi) - ry;
 #pragma unroll
         for (int i = 0; i < NRA; ++i) {
             const int r = min(ty + GROUPS * i, PH - 1);
-            const T *row = raw + (zoff + (long)min(max(y0 + r - ry, 0), ny - 1) * nx);
+            const T *row = raw + (zoff + (long)min(max(top + r, 0), ny - 1) * nx);
 #pragma unroll
             for (int j = 0; j < NCA; ++j) {
                 const int c = min(tx + EX * j, PW - 1);
@@ -236,10 +242,11 @@ __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, 
                 fx[i] = x + 1 < nx ? n : f[i];
             }
         }
-        const long o0 = zo * nxy + (long)(y0 + ty * ROWS) * nx + x0;
+        const int yt = first_row(zo) + ty * ROWS;
+        const long o0 = plane_of(zo) * nxy + (long)yt * nx + x0;
 #pragma unroll
         for (int i = 0; i < ROWS; ++i) {
-            const int y = y0 + ty * ROWS + i;
+            const int y = yt + i;
             const bool in = y < ny, last = y + 1 >= ny;
             const long o = in ? o0 + (long)i * nx : 0;
             const int cells = in ? min(nx - x0, TX) : 0;
@@ -286,8 +293,8 @@ __global__ __launch_bounds__(NT) void prepass_kernel(PrepassJob one, const Prepa
         by = k / j->cut.bx % j->cut.by;
         bz = k / j->cut.bx / j->cut.by;
     }
-    const int z0 = bz * j->cut.z_chunk;
-    prepass_tile<T, ROWS, RXY, RB, RZ, ZMAX, SECOND>(&j->a, bx, by, z0, min(j->a.nz, z0 + j->cut.z_chunk), lds);
+    const int z0 = bz * j->cut.chunk;
+    prepass_tile<T, ROWS, RXY, RB, RZ, ZMAX, SECOND>(&j->a, bx, by, z0, min(j->cut.len, z0 + j->cut.chunk), lds);
 }
 
 // Workgroups of a kernel that a CU holds, by its registers: a workgroup is one wave on each SIMD, which has 512

@@ -214,12 +214,13 @@ struct PrepassArgs {
 
 constexpr int kPrepassMaxR = 16;
 
-// One volume of a launch: cut into bx x by tiles and chunks of z_chunk planes, its first workgroup.
+// One volume of a launch: cut into bx x by tiles and chunks of its len planes (an image without quad records:
+// bx x 1 and chunks of its len rows of tiles), its first workgroup.
 struct PrepassJob {
     PrepassArgs a;
     int first;
     struct {
-        int bx, by, z_chunk;
+        int bx, by, chunk, len;
     } cut;
 };
 
