@@ -135,7 +135,8 @@ snk_status snk_set_params(snk_ctx *ctx, const snk_params *params);
  * pair-points whose gathers one lane issues before consuming them (0 = automatic, 1, 2 or 4; 4 is
  * taken with 64 or 128 lanes and outside snk_trace_step, otherwise it runs as 2), and the
  * layout the kernel reads the smoothed volume from (0 = automatic: column pairs when they fit, else
- * plain; 1 = plain FP32,
+ * plain; plain too for a 2D image with automatic boxes whose contours are loaded before the pre-pass and are
+ * more than four per compute unit, which boxes serve from the plain copy; 1 = plain FP32,
  * 2 = quad: one 16-byte record per voxel with its +x, +y, +xy neighbours, 4x the FP32 volume; needs
  * 16 * nx*ny*nz below 2 GiB and ny, nz <= 65535, else SNK_EINVAL at the next evolve; 3 = plain FP32
  * with 64-bit addressing, the path of volumes beyond 2 GiB; 4 = column pairs: (J(x,y,z),
@@ -150,9 +151,9 @@ snk_status snk_set_launch(snk_ctx *ctx, int32_t lanes_per_contour, int32_t pairs
 /* LDS box of the Monte-Carlo evolution (whole-wave launch shapes, layouts 1, 2 and 4): each contour
  * keeps a box of the smoothed volume around its sample ball (Sec. II-E) in on-chip memory, staged
  * with a margin and re-staged only when the ball leaves it, and reads the trilinear corners of its
- * samples from there. tile_voxels = -1: automatic (boxes only when more than four contours per
- * compute unit must stay resident, where their footprints overflow the L2: the largest capacity
- * that keeps them all resident), 0: off (every corner read from the volume), 1..16384: capacity in
+ * samples from there. tile_voxels = -1: automatic (none with four or fewer contours per
+ * compute unit, whose footprints fit the L2; above, the largest capacity that keeps all contours
+ * resident or, where they are more than can be, as many as registers allow), 0: off (every corner read from the volume), 1..16384: capacity in
  * voxels (4 bytes each). An iteration whose ball does not fit, or
  * reaches the volume's edge, reads the volume. Results are bit-identical with and without the box.
  * SNK_EINVAL if tile_voxels is out of range, or at the next evolve if the box and the kernel's other
