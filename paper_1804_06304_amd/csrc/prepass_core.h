@@ -301,7 +301,10 @@ __global__ __launch_bounds__(NT) void prepass_kernel(PrepassJob one, const Prepa
 // registers per lane to give out in eights.
 inline int groups_by_registers(const void *kernel) {
     hipFuncAttributes at{};
-    if (hipFuncGetAttributes(&at, kernel) != hipSuccess || at.numRegs <= 0) return 4;
+    if (hipFuncGetAttributes(&at, kernel) != hipSuccess || at.numRegs <= 0) {
+        (void)hipGetLastError();   // the launch's own check follows
+        return 4;
+    }
     return std::max(1, std::min(8, 512 / ((at.numRegs + 7) & ~7)));
 }
 
