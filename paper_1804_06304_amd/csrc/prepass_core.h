@@ -7,8 +7,7 @@
 // Per input plane: stage the plane with its x/y halo in LDS from registers that were fetched while the
 // previous plane was filtered; barrier; filter along x into LDS; barrier; then every thread filters its own
 // ROWS neighbouring rows of one column along y (from the 2 ry + ROWS values they share) and z (a ring of
-// 2 rz + 1 planes of its own rows, in registers for the radii that have an instance), and stores J and the
-// second copy. A column pair's lower row is a row that the thread evaluates too (one more than it stores); a
+// 2 rz + 1 planes of its own rows, in its registers), and stores J and the second copy. A column pair's lower row is a row that the thread evaluates too (one more than it stores); a
 // quad record's +x values come from the next lane, so tiles are 63 columns wide there and 64, whole cache
 // lines, otherwise.
 //
