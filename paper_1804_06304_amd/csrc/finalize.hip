@@ -65,9 +65,10 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
     }
     const float smax = R + 0.5f * p.dR;
     const double R_d = (double)R, dR_d = (double)p.dR, smax_d = R_d + 0.5 * dR_d, smax2 = smax_d * smax_d;
-    // S(r) = min(clamp(2 (r - rho R) / (rho dR), -1, 1), clamp(1/2 - (r - R) / dR, 0, 1)): each ramp is
-    // constant where the other one runs (Sec. II-B)
+    // S(r) (Sec. II-B), region by region in this order: a radius below the smallest admissible one (a state set by
+    // the caller) has an inner ramp that reaches into the outer one, and the first region that holds r counts
     const double is = 2.0 / (RHO * dR_d), in0 = -is * (RHO * R_d), os = 1.0 / dR_d, out0 = 0.5 + os * R_d;
+    const double core = RHO * R_d - 0.5 * (RHO * dR_d), ramp = RHO * R_d + 0.5 * (RHO * dR_d), shell = R_d - 0.5 * dR_d;
     // rows within the ball's range (a row or point of the margin has no point inside, or weight 0)
     int lo[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
 #pragma unroll
@@ -108,10 +109,11 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
                 const double y0 = __builtin_amdgcn_rsq(d2);
                 const double r0 = d2 * y0;
                 const double r = fma(0.5 * r0, fma(-r0, y0, 1.0), r0);
-                const double sin_ = fmin(fmax(fma(r, is, in0), -1.0), 1.0);
-                const double sout = fmin(fmax(fma(r, -os, out0), 0.0), 1.0);
+                double w = r < ramp ? fma(r, is, in0) : fma(r, -os, out0);
+                w = r < core ? -1.0 : w;
+                w = r >= ramp && r < shell ? 1.0 : w;
                 // a point outside the ball does not count, whatever its value
-                acc = fma(fmin(sin_, sout), (double)(r < smax_d ? v[u] : 0.0f), acc);
+                acc = r < smax_d ? fma(w, (double)v[u], acc) : acc;
             }
         }
     }
