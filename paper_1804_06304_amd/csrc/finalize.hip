@@ -97,15 +97,22 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
         const float *rowp = g.J + ((long)z * g.ny + y) * g.nx;
         // the row's points inside the ball, with a rounding margin
         const float ex = fmaf(sqrtf((float)rem) * g.inv_h[0], 1.0001f, 1e-3f);
-        const int x1 = (int)floorf(s.off[0] + ex);
-        for (int x = (int)ceilf(s.off[0] - ex) + q % SHARE; x <= x1; x += 4 * SHARE) {
+        // counted from the first, so that the ends of a centre beyond the integers (a seed may be anywhere, infinite
+        // too), which the conversions hold at the largest integer, end the walk as well
+        const unsigned xa = (unsigned)(int)ceilf(s.off[0] - ex);
+        const int last = (int)((unsigned)(int)floorf(s.off[0] + ex) - xa);
+        for (int k = q % SHARE; k <= last; k += 4 * SHARE) {
+            int x[4];
             float v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = rowp[min(max(s.anc[0] + x + u * SHARE, 0), nn[0] - 1)];
+            for (int u = 0; u < 4; ++u) {
+                x[u] = (int)(xa + (unsigned)(k + u * SHARE));
+                v[u] = rowp[min(max((int)((unsigned)s.anc[0] + (unsigned)x[u]), 0), nn[0] - 1)];
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const double d = ((double)(x + u * SHARE) - ox) * hx;
-                const double d2 = fmax(fma(d, d, r2), 1e-290);
+                const double d = ((double)x[u] - ox) * hx;
+                const double e2 = fma(d, d, r2), d2 = e2 < 1e-290 ? 1e-290 : e2;   // (not a number stays one: outside)
                 const double y0 = __builtin_amdgcn_rsq(d2);
                 const double r0 = d2 * y0;
                 const double r = fma(0.5 * r0, fma(-r0, y0, 1.0), r0);
