@@ -39,13 +39,15 @@ constexpr int ev_share() {
     return DIM == 3 ? 1 : 2;
 }
 
-// Bound by instruction issue (62,500 lattice contours: 1,685 vector instructions per wave before). So a lane
-// takes one row of the lattice and walks only the points of it inside the ball, about a quarter of the
-// ball's box, and a point costs about 25 instructions instead of 75: the row's part of the distance is
-// formed once, the square root is the hardware's reciprocal root (relative error 2^-28 or less) with one
-// correction step (its square, 2^-54), the weight is two clamped ramps by reciprocals formed once. Four
-// points' loads are in flight per lane. Finalize, before -> now: 62,500 lattice contours 754 -> 315 us, 2,000
-// contours 71 -> 48, 40,000 in 2D 143 -> 108, 8 contours 30 -> 21; the FP32 energies did not change.
+// Bound by instruction issue (62,500 lattice contours: 1,685 vector instructions per wave with a lane per point of the
+// ball's box). So a lane takes one row of the lattice and walks only the points of it inside the ball, about a
+// quarter of the box, the row's part of the distance is formed once and the weight takes no division. Four points'
+// loads are in flight per lane. Finalize, a lane per point -> now: 62,500 lattice contours 754 -> 330 us, 2,000
+// contours 71 -> 48, 40,000 in 2D 143 -> 98, 8 contours 30 -> 21.
+// Every point's distance has the bits of a correctly rounded root or is next to them: the hardware's reciprocal root,
+// one coupled step for the root and half its reciprocal and one for the root's remainder (P. Markstein, IA-64 and
+// Elementary Functions, 2000). With the first step alone, and ramps as slope times r plus an offset, sums that
+// cancel were off by up to 9 x 2^-53 of their magnitude; now by 0.6, a lane per point and divisions left 1.8.
 template <int DIM>
 __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, bool finalize = true) {
     constexpr int EV_T = ev_threads<DIM>();
@@ -65,10 +67,12 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
     }
     const float smax = R + 0.5f * p.dR;
     const double R_d = (double)R, dR_d = (double)p.dR, smax_d = R_d + 0.5 * dR_d, smax2 = smax_d * smax_d;
-    // S(r) (Sec. II-B), region by region in this order: a radius below the smallest admissible one (a state set by
-    // the caller) has an inner ramp that reaches into the outer one, and the first region that holds r counts
-    const double is = 2.0 / (RHO * dR_d), in0 = -is * (RHO * R_d), os = 1.0 / dR_d, out0 = 0.5 + os * R_d;
-    const double core = RHO * R_d - 0.5 * (RHO * dR_d), ramp = RHO * R_d + 0.5 * (RHO * dR_d), shell = R_d - 0.5 * dR_d;
+    // S(r) (Sec. II-B). Of a radius below the smallest admissible one (a state set by the caller) the inner ramp reaches
+    // into the outer one: the first region in order that holds r counts. Else each ramp, held between its ends, is
+    // constant where the other one runs. (rho R has twice the bits: what its rounding leaves is in the ramp's offset.)
+    const double ain = RHO * R_d, dr = RHO * dR_d, is = 2.0 / dr, in0 = -is * fma(RHO, R_d, -ain), os = -1.0 / dR_d;
+    const double core = ain - 0.5 * dr, ramp = ain + 0.5 * dr, shell = R_d - 0.5 * dR_d;
+    const bool disjoint = __builtin_amdgcn_readfirstlane(ramp <= shell);
     // rows within the ball's range (a row or point of the margin has no point inside, or weight 0)
     int lo[3] = {0, 0, 0}, cnt[3] = {1, 1, 1};
 #pragma unroll
@@ -84,10 +88,10 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
     for (int q = t; q < total; q += EV_T) {
         const int row = q / SHARE, yy = row % cnt[1], zz = row / cnt[1];
         const double dy = ((double)(lo[1] + yy) - (double)s.off[1]) * (double)g.h[1];
-        double r2 = dy * dy;
+        double dz = 0.0, r2 = dy * dy;
         int z = 0;
         if constexpr (DIM == 3) {
-            const double dz = ((double)(lo[2] + zz) - (double)s.off[2]) * (double)g.h[2];
+            dz = ((double)(lo[2] + zz) - (double)s.off[2]) * (double)g.h[2];
             r2 = fma(dz, dz, r2);
             z = min(max(s.anc[2] + lo[2] + zz, 0), nn[2] - 1);
         }
@@ -109,18 +113,31 @@ __device__ void energy_one(const JobParams &p, DevContour *slot, double *e_out, 
                 x[u] = (int)(xa + (unsigned)(k + u * SHARE));
                 v[u] = rowp[min(max((int)((unsigned)s.anc[0] + (unsigned)x[u]), 0), nn[0] - 1)];
             }
+            double r[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const double d = ((double)x[u] - ox) * hx;
-                const double e2 = fma(d, d, r2), d2 = e2 < 1e-290 ? 1e-290 : e2;   // (not a number stays one: outside)
-                const double y0 = __builtin_amdgcn_rsq(d2);
-                const double r0 = d2 * y0;
-                const double r = fma(0.5 * r0, fma(-r0, y0, 1.0), r0);
-                double w = r < ramp ? fma(r, is, in0) : fma(r, -os, out0);
-                w = r < core ? -1.0 : w;
-                w = r >= ramp && r < shell ? 1.0 : w;
-                // a point outside the ball does not count, whatever its value
-                acc = r < smax_d ? fma(w, (double)v[u], acc) : acc;
+                double d2 = fma(dy, dy, fma(d, d, 1e-290));   // never 0
+                if constexpr (DIM == 3) d2 = fma(dz, dz, d2);
+                const double y0 = __builtin_amdgcn_rsq(d2), g0 = d2 * y0, h0 = 0.5 * y0, e0 = fma(-h0, g0, 0.5);
+                const double g1 = fma(g0, e0, g0), h1 = fma(h0, e0, h0);
+                r[u] = fma(fma(-g1, g1, d2), h1, g1);
+            }
+            // a point outside the ball does not count, whatever its value
+            if (disjoint) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double in = fma(r[u] - ain, is, in0), out = fma(r[u] - R_d, os, 0.5);
+                    const double w = fmin(fmax(in, -1.0), fmin(out, 1.0));
+                    acc = r[u] < smax_d ? fma(w, (double)v[u], acc) : acc;
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double in = fma(r[u] - ain, is, in0), out = fma(r[u] - R_d, os, 0.5);
+                    const double w = r[u] < core ? -1.0 : (r[u] < ramp ? in : (r[u] < shell ? 1.0 : out));
+                    acc = r[u] < smax_d ? fma(w, (double)v[u], acc) : acc;
+                }
             }
         }
     }
