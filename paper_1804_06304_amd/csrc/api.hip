@@ -408,9 +408,10 @@ int sum_lanes(const snk_ctx *c, int M, int layout) {
 // LDS box (automatic): none with four or fewer contours per CU, whose footprints fit the L2 (8 contours of
 // 64^3: 160 us without, 167 with). Above, the largest that leaves room for every contour of the CU. More
 // contours than can be resident (3D groups of two waves or more, 2D): the largest that leaves room for as
-// many as registers allow, 8 of two waves in 3D, 20 of one wave in 2D; there 256 lanes run as two waves.
-// Evolve, no box -> box: 62,500 lattice contours 9.1 -> 7.8 ms; 40,000 in 2D 4.2 -> 4.1 ms, and the pre-pass
-// need not write the column pairs.
+// many as registers allow, 8 of two waves in 3D, 20 waves in 2D (20 contours of one, 10 of two, 5 of four); in 3D 256
+// lanes run as two waves there. Evolve, no box -> box: 62,500 lattice contours 9.1 -> 7.8 ms; 40,000 in 2D 4.2 -> 4.1
+// ms, and the pre-pass need not write the column pairs. 6,900 disks of R 19.8, 60 iterations, with a box for 20
+// contours whatever their lanes -> for 20 waves: 32 rays 517 -> 362 us, 64 rays 959 -> 711, 96 rays 1,838 -> 977.
 McShape mc_shape(snk_ctx *c, int M, int layout) {
     McShape s;
     s.lanes = sum_lanes(c, M, layout);
@@ -437,11 +438,13 @@ McShape mc_shape(snk_ctx *c, int M, int layout) {
     };
     int64_t resident = per_cu;
     bool two_waves = false;
-    if (per_cu > blocks(G)) {
-        if (dim == 3 && G < 128) return s;
-        two_waves = G == 256 && dim == 3 && s.unroll == 2 && layout != snk::kBufferQuad &&
-                    !(c->P.flags & snk::kFlagGradI) && snk::full_passes(256, 2, M, c->P.n_radial);
-        resident = dim == 2 ? 20 : blocks(two_waves ? 128 : G);
+    if (dim == 2) {
+        resident = std::min<int64_t>(per_cu, 1280 / G);
+    } else if (per_cu > blocks(G)) {
+        if (G < 128) return s;
+        two_waves = G == 256 && s.unroll == 2 && layout != snk::kBufferQuad && !(c->P.flags & snk::kFlagGradI) &&
+                    snk::full_passes(256, 2, M, c->P.n_radial);
+        resident = blocks(two_waves ? 128 : G);
         if (resident <= 0) return s;
     }
     // (a box of one voxel: the LDS beside it)
