@@ -135,8 +135,9 @@ snk_status snk_set_params(snk_ctx *ctx, const snk_params *params);
  * pair-points whose gathers one lane issues before consuming them (0 = automatic, 1, 2 or 4; 4 is
  * taken with 64 or 128 lanes and outside snk_trace_step, otherwise it runs as 2), and the
  * layout the kernel reads the smoothed volume from (0 = automatic: column pairs when they fit, else
- * plain; plain too for a 2D image with automatic boxes whose contours are loaded before the pre-pass and are
- * more than four per compute unit, which boxes serve from the plain copy; 1 = plain FP32,
+ * plain; an image with automatic boxes and more than four contours per compute unit is read plain where boxes
+ * serve the gathers, where its pairs overflow the cache, and by the options that read it plain: its pre-pass then
+ * writes no pairs, and a later evolve that reads them makes them; 1 = plain FP32,
  * 2 = quad: one 16-byte record per voxel with its +x, +y, +xy neighbours, 4x the FP32 volume; needs
  * 16 * nx*ny*nz below 2 GiB and ny, nz <= 65535, else SNK_EINVAL at the next evolve; 3 = plain FP32
  * with 64-bit addressing, the path of volumes beyond 2 GiB; 4 = column pairs: (J(x,y,z),

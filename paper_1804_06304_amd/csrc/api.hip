@@ -73,6 +73,7 @@ struct snk_ctx {
     bool J_dirty = true;
 
     int64_t n = 0;
+    double r_mean = 0.0;   // of the radii that were loaded
     DevContour *d_st = nullptr;
     double *d_evox = nullptr;
     size_t n_cap = 0, evox_cap = 0;
@@ -295,6 +296,8 @@ snk_status ensure_layout_buffer(snk_ctx *c, int layout) {
     return SNK_OK;
 }
 
+int read_layout(snk_ctx *c, int layout);
+
 snk_status run_prepass(snk_ctx *c) {
     snk::PrepassArgs a{};
     a.raw = c->raw;
@@ -325,11 +328,7 @@ snk_status run_prepass(snk_ctx *c) {
     int layout = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
     if (layout < 0)
         return fail(c, SNK_EINVAL, "volume too large for the requested layout");
-    // a 2D image whose contours will evolve in boxes (mc_shape) is read from the plain copy alone: without
-    // the column pairs the pre-pass writes a third of the bytes (8192^2: 245 -> 127 us)
-    if (c->layout_req == 0 && c->P.dim == 2 && layout == snk::kBufferPair && c->cus > 0 && c->n > 4 * (int64_t)c->cus &&
-        c->tile_req < 0)
-        layout = snk::kBufferPlain;
+    layout = read_layout(c, layout);
     snk_status lst = ensure_layout_buffer(c, layout);
     if (lst != SNK_OK) return lst;
     a.Jq = layout == snk::kBufferQuad ? c->Jq : nullptr;
@@ -378,6 +377,7 @@ snk::JobParams job_params(const snk_ctx *c) {
 struct McShape {
     int lanes, unroll, tile;
     bool two_waves;   // of 256 lanes
+    bool wide;        // 2D, no box: the column pairs that the resident contours read overflow the L2
 };
 
 // Lanes per contour of a Monte-Carlo evolve over `layout` (the layout the volume takes by its size, whatever
@@ -423,11 +423,19 @@ McShape mc_shape(snk_ctx *c, int M, int layout) {
         return s;
     }
     const int G = s.lanes, dim = c->P.dim;
-    if (c->tile_req == 0 || c->n <= 0 || c->cus <= 0 || c->lds_per_cu <= 0 || G < 64) return s;
+    if (c->tile_req == 0 || c->n <= 0 || c->cus <= 0 || c->lds_per_cu <= 0) return s;
     if (layout != snk::kBufferQuad && layout != snk::kBufferPlain && layout != snk::kBufferPair) return s;
     const int64_t per_cu = (c->n + c->cus - 1) / c->cus;
+    const int64_t nvol[3] = {c->nx, c->ny, c->nz};
+    double ball = 1.0;   // voxels of the box that holds a contour's samples, no margin
+    for (int a = 0; a < dim; ++a)
+        ball *= std::min((2.0 * c->r_mean + c->P.dR) / c->P.spacing[a] + 2.0, (double)nvol[a]);
+    // the pairs (8 bytes) that an XCD's contours gather from, of its 4 MiB of L2
+    const double pairs = 8.0 * ball * (double)(std::min<int64_t>(per_cu, 1280 / G) * c->cus / 8);
+    if (dim == 2) s.wide = pairs > (double)(7 << 20);
     // (fewer than 128 pair-points an iteration do not repay a box)
-    if (per_cu <= 4 || (int64_t)(M / 2) * c->P.n_radial < 128) return s;
+    if (G < 64 || per_cu <= 4 || (int64_t)(M / 2) * c->P.n_radial < 128) return s;
+    if (dim == 2 && layout == snk::kBufferPair && G > 64 && pairs <= (double)(3 << 20)) return s;
     auto blocks = [&](int g) {
         const int key = ((dim * 512 + g) * 8 + s.unroll) * 4 + layout;
         if (key != c->stage_key) {
@@ -454,20 +462,33 @@ McShape mc_shape(snk_ctx *c, int M, int layout) {
     if (budget <= other) return s;
     const int tile = (int)std::min<size_t>((budget - other) / 4, 16384) & ~15;
     if (tile < (dim == 3 ? 1024 : 512)) return s;
+    if (dim == 2 && layout == snk::kBufferPair && ball > (double)tile) return s;
     s.tile = tile;
     s.two_waves = two_waves;
     return s;
 }
 
-// Re-packs the current J when the requested layout changed after the pre-pass.
+// The copy that an evolve reads of a volume whose layout is `layout` by its size or by request. An image by size
+// alone, with automatic boxes, is read from the plain copy where boxes serve the gathers, where the pairs
+// overflow the L2 by far and where the kernel reads single pixels (more than four contours per CU each); the pre-pass
+// then writes a third of the bytes (8192^2: 245 -> 127 us). Else, and by star contours, from the pairs.
+int read_layout(snk_ctx *c, int layout) {
+    if (c->layout_req != 0 || c->P.dim != 2 || layout != snk::kBufferPair || c->tile_req >= 0 ||
+        c->n <= 4 * (int64_t)c->cus || c->cus <= 0 || c->star_lambda >= 0.0)
+        return layout;
+    if (c->P.flags & (snk::kFlagExact | snk::kFlagGradI)) return snk::kBufferPlain;
+    const McShape sh = mc_shape(c, c->P.n_rays, layout);
+    return sh.tile > 0 || sh.wide ? snk::kBufferPlain : layout;
+}
+
+// Re-packs the current J when the next evolve reads another layout than the pre-pass wrote.
 snk_status ensure_layout(snk_ctx *c) {
-    const int layout = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
-    if (layout < 0)
+    const int by_size = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
+    if (by_size < 0)
         return fail(c, SNK_EINVAL, "volume too large for the requested layout");
-    if (layout == c->layout) return SNK_OK;
-    // an automatic 2D layout is whichever of the two the pre-pass wrote
-    if (c->layout_req == 0 && c->P.dim == 2 && layout == snk::kBufferPair && c->layout == snk::kBufferPlain)
-        return SNK_OK;
+    const int layout = read_layout(c, by_size);
+    // (pairs are kept for a later evolve that reads them: the plain copy is there too)
+    if (layout == c->layout || (layout != by_size && c->layout == by_size)) return SNK_OK;
     snk_status st = ensure_layout_buffer(c, layout);
     if (st != SNK_OK) return st;
     if (layout == snk::kBufferQuad)
@@ -696,17 +717,18 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
     // exact sums read single voxels from J (the plain layout); so does the gradient-form kernel in
     // place of column pairs
     const bool gradi = (c->P.flags & snk::kFlagGradI) != 0;
+    const int by_size = snk::volume_layout(c->P.dim, c->nx, c->ny, c->nz, c->layout_req);
     int layout = (exact && (c->layout == snk::kBufferQuad || c->layout == snk::kBufferPair)) ||
                          (gradi && c->P.dim == 2 && c->layout == snk::kBufferPair)
                      ? snk::kBufferPlain
-                     : c->layout;
+                     : (c->layout == snk::kBufferPair ? read_layout(c, by_size) : c->layout);
     int lanes, unroll;
     if (exact) {
         lanes = c->lanes > 0 ? c->lanes : 256;
         unroll = 1;
     } else {
-        // a 2D image whose pre-pass left out the column pairs counts as one that has them
-        const McShape sh = mc_shape(c, a.p.M, gradi || c->P.dim == 3 ? layout : snk::volume_layout(2, c->nx, c->ny, c->nz, c->layout_req));
+        // an image that is read from the plain copy by read_layout counts as one in pairs
+        const McShape sh = mc_shape(c, a.p.M, gradi || c->P.dim == 3 ? layout : by_size);
         lanes = sh.lanes;
         unroll = sh.unroll;
         // LDS boxes: whole-wave groups over a buffer layout
@@ -1120,6 +1142,7 @@ snk_status snk_load_seeds(snk_ctx *c, const double *centers, const float *r0, co
     st = stage(c, (size_t)n, &h);
     if (st != SNK_OK) return st;
     const double lo = r_low(c->P), hi = c->P.r_max;
+    double sum_r = 0.0;
     for (int64_t i = 0; i < n; ++i) {
         DevContour &s = h[i];
         memset(&s, 0, sizeof(s));
@@ -1135,6 +1158,7 @@ snk_status snk_load_seeds(snk_ctx *c, const double *centers, const float *r0, co
         s.status = inside(c, s) ? SNK_ACTIVE : SNK_OUT;
         s.streak = 0;
         s.keep = 0;
+        sum_r += s.R;
     }
     st = ensure(c, &c->d_st, &c->n_cap, (size_t)n);
     if (st != SNK_OK) return st;
@@ -1143,6 +1167,7 @@ snk_status snk_load_seeds(snk_ctx *c, const double *centers, const float *r0, co
     st = upload_stage(c, (size_t)n);
     if (st != SNK_OK) return st;
     c->n = n;
+    c->r_mean = n > 0 ? sum_r / (double)n : 0.0;
     c->Rk_valid = false;
     return SNK_OK;
 }
@@ -1370,6 +1395,7 @@ snk_status snk_set_state(snk_ctx *c, const double *centers, const float *radii, 
     std::vector<DevContour> h;
     st = unpack(c, h);
     if (st != SNK_OK) return st;
+    double sum_r = 0.0;
     for (int64_t i = 0; i < n; ++i) {
         if (!(radii[i] > 0.0f) || !(radii[i] <= (float)c->P.r_max) || iters[i] < 0)
             return fail(c, SNK_EINVAL, "state radius outside (0, r_max] or negative iteration count");
@@ -1380,6 +1406,7 @@ snk_status snk_set_state(snk_ctx *c, const double *centers, const float *radii, 
         h[i].status = status[i];
         h[i].streak = streak ? streak[i] : 0;
         h[i].keep = 0;
+        sum_r += radii[i];
     }
     DevContour *buf = nullptr;
     st = stage(c, (size_t)n, &buf);
@@ -1387,6 +1414,7 @@ snk_status snk_set_state(snk_ctx *c, const double *centers, const float *radii, 
     if (n > 0) memcpy(buf, h.data(), sizeof(DevContour) * n);
     st = upload_stage(c, (size_t)n);
     if (st != SNK_OK) return st;
+    c->r_mean = sum_r / (double)n;
     c->Rk_valid = false;
     return SNK_OK;
 }
