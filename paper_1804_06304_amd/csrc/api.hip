@@ -408,10 +408,19 @@ int sum_lanes(const snk_ctx *c, int M, int layout) {
 // LDS box (automatic): none with four or fewer contours per CU, whose footprints fit the L2 (8 contours of
 // 64^3: 160 us without, 167 with). Above, the largest that leaves room for every contour of the CU. More
 // contours than can be resident (3D groups of two waves or more, 2D): the largest that leaves room for as
-// many as registers allow, 8 of two waves in 3D, 20 waves in 2D (20 contours of one, 10 of two, 5 of four); in 3D 256
-// lanes run as two waves there. Evolve, no box -> box: 62,500 lattice contours 9.1 -> 7.8 ms; 40,000 in 2D 4.2 -> 4.1
-// ms, and the pre-pass need not write the column pairs. 6,900 disks of R 19.8, 60 iterations, with a box for 20
-// contours whatever their lanes -> for 20 waves: 32 rays 517 -> 362 us, 64 rays 959 -> 711, 96 rays 1,838 -> 977.
+// many as registers allow, 8 of two waves in 3D, 20 waves in 2D (20 contours of one, 10 of two, 5 of four). In 3D
+// 256 lanes run as two waves there if the balls fit their box: 62,500 lattice contours without a box -> with one, 9.1
+// -> 7.8 ms. Balls that do not, as four: gathering from the volume, two waves' 8 contours a CU overflow the L2
+// where four waves' 4 do not, whose box is larger too (60 iterations, no box, two waves, four waves: 8,000 balls of R
+// 6.3 1,367, 1,092, - us; R 8.2 1,931, 2,639, 1,327; R 10.1 3,170, 4,008, 2,745; R 15.1 6,494, 7,017, 5,778).
+// In 2D over pairs, which gather as fast while they fit the L2, no box that the disks do not fit, and for groups of two
+// or four waves none where the pairs take less than 3 MiB of an XCD's L2 (60 iterations, pairs -> box: 38,000 disks of R
+// 8.5, 32 rays, 64 rays 1,672 -> 1,649, 3,285 -> 3,523 us; 6,900 of R 19.8 400 -> 362, 725 -> 711; one wave, 16
+// rays, 782 -> 813, where the pre-pass saves more, and 11,200 of R 15.6 409 -> 282). Pairs without a box up to 7 MiB,
+// beyond that plain (pairs, plain: 3,400 of R 28.3 with 64 rays, 4.4 MiB, 443, 557; 1,760 of R 39.6, 8.2 MiB, 483, 388;
+// 6,900 of R 19.8 with 16 rays, 8.9 MiB, 429, 324; 6,000 of R 15.6, 6.3 MiB, 254, 252). 6,900 disks of R 19.8 with
+// a box for 20 contours whatever their lanes -> for 20 waves: 32 rays 517 -> 362 us, 64 rays 959 -> 711, 96 rays 1,838
+// -> 977.
 McShape mc_shape(snk_ctx *c, int M, int layout) {
     McShape s;
     s.lanes = sum_lanes(c, M, layout);
@@ -444,27 +453,27 @@ McShape mc_shape(snk_ctx *c, int M, int layout) {
         }
         return c->stage_blocks;
     };
-    int64_t resident = per_cu;
-    bool two_waves = false;
+    // the largest box that leaves room for n contours, and whether 256 lanes run as two waves
+    auto box = [&](int64_t n, bool two_waves) {
+        // (a box of one voxel: the LDS beside it)
+        const size_t other = snk::evolve_lds_bytes(dim, G, M, 1, two_waves) - 4;
+        // LDS is handed out in blocks of 1,280 bytes (160 KiB / 128): slab 2.37 ms with 8 x 20,480 bytes, 2.46 above
+        const size_t budget = n > 0 ? std::min<size_t>((size_t)c->lds_per_cu / (size_t)n, 65536) / 1280 * 1280 : 0;
+        s.tile = budget > other ? (int)std::min<size_t>((budget - other) / 4, 16384) & ~15 : 0;
+        if (s.tile < (dim == 3 ? 1024 : 512)) s.tile = 0;
+        s.two_waves = two_waves && s.tile > 0;
+    };
     if (dim == 2) {
-        resident = std::min<int64_t>(per_cu, 1280 / G);
-    } else if (per_cu > blocks(G)) {
-        if (G < 128) return s;
-        two_waves = G == 256 && s.unroll == 2 && layout != snk::kBufferQuad && !(c->P.flags & snk::kFlagGradI) &&
-                    snk::full_passes(256, 2, M, c->P.n_radial);
-        resident = blocks(two_waves ? 128 : G);
-        if (resident <= 0) return s;
+        box(std::min<int64_t>(per_cu, 1280 / G), false);
+        if (layout == snk::kBufferPair && ball > (double)s.tile) s.tile = 0;
+    } else if (per_cu <= blocks(G)) {
+        box(per_cu, false);
+    } else if (G >= 128) {
+        if (G == 256 && s.unroll == 2 && layout != snk::kBufferQuad && !(c->P.flags & snk::kFlagGradI) &&
+            snk::full_passes(256, 2, M, c->P.n_radial))
+            box(blocks(128), true);
+        if (!s.two_waves || ball > (double)s.tile) box(blocks(G), false);
     }
-    // (a box of one voxel: the LDS beside it)
-    const size_t other = snk::evolve_lds_bytes(dim, G, M, 1, two_waves) - 4;
-    // LDS is handed out in blocks of 1,280 bytes (160 KiB / 128): slab 2.37 ms with 8 x 20,480 bytes, 2.46 above
-    const size_t budget = std::min<size_t>((size_t)c->lds_per_cu / (size_t)resident, 65536) / 1280 * 1280;
-    if (budget <= other) return s;
-    const int tile = (int)std::min<size_t>((budget - other) / 4, 16384) & ~15;
-    if (tile < (dim == 3 ? 1024 : 512)) return s;
-    if (dim == 2 && layout == snk::kBufferPair && ball > (double)tile) return s;
-    s.tile = tile;
-    s.two_waves = two_waves;
     return s;
 }
 
