@@ -402,7 +402,7 @@ int sum_lanes(const snk_ctx *c, int M, int layout) {
     return budget >= other + 4096 ? G : lanes;
 }
 
-// Launch shape of a Monte-Carlo evolve over `layout`. Explicit knobs are taken as set; of the shapes that give
+// Launch shape of a Monte-Carlo evolve over `layout` by launches of `iters` iterations. Explicit knobs are taken as set; of the shapes that give
 // the same bits the library picks. Two pair-points in flight (slab evolve 2.34 ms; four need 128 registers
 // and spill, 2.80).
 // LDS box (automatic): none with four or fewer contours per CU, whose footprints fit the L2 (8 contours of
@@ -413,6 +413,9 @@ int sum_lanes(const snk_ctx *c, int M, int layout) {
 // -> 7.8 ms. Balls that do not, as four: gathering from the volume, two waves' 8 contours a CU overflow the L2
 // where four waves' 4 do not, whose box is larger too (60 iterations, no box, two waves, four waves: 8,000 balls of R
 // 6.3 1,367, 1,092, - us; R 8.2 1,931, 2,639, 1,327; R 10.1 3,170, 4,008, 2,745; R 15.1 6,494, 7,017, 5,778).
+// Launches of fewer than 16 iterations do not repay the staging there, least of all a run's first, whose steps are the
+// largest (a run of 5, 12, 25 iterations, no box -> box: 6,000 balls of R 6.3, 32 rays 98 -> 119, 143 -> 182, 288 -> 294
+// us, 64 rays 107 -> 140, 213 -> 242, 441 -> 454; balls that do not fit stage nothing).
 // In 2D over pairs, which gather as fast while they fit the L2, no box that the disks do not fit, and for groups of two
 // or four waves none where the pairs take less than 3 MiB of an XCD's L2 (60 iterations, pairs -> box: 38,000 disks of R
 // 8.5, 32 rays, 64 rays 1,672 -> 1,649, 3,285 -> 3,523 us; 6,900 of R 19.8 400 -> 362, 725 -> 711; one wave, 16
@@ -421,7 +424,7 @@ int sum_lanes(const snk_ctx *c, int M, int layout) {
 // 6,900 of R 19.8 with 16 rays, 8.9 MiB, 429, 324; 6,000 of R 15.6, 6.3 MiB, 254, 252). 6,900 disks of R 19.8 with
 // a box for 20 contours whatever their lanes -> for 20 waves: 32 rays 517 -> 362 us, 64 rays 959 -> 711, 96 rays 1,838
 // -> 977.
-McShape mc_shape(snk_ctx *c, int M, int layout) {
+McShape mc_shape(snk_ctx *c, int M, int layout, int32_t iters) {
     McShape s;
     s.lanes = sum_lanes(c, M, layout);
     s.unroll = c->unroll > 0 ? c->unroll : (s.lanes >= 64 ? 2 : 1);
@@ -473,6 +476,10 @@ McShape mc_shape(snk_ctx *c, int M, int layout) {
             snk::full_passes(256, 2, M, c->P.n_radial))
             box(blocks(128), true);
         if (!s.two_waves || ball > (double)s.tile) box(blocks(G), false);
+        if (iters < 16 && ball <= (double)s.tile) {
+            s.tile = 0;
+            s.two_waves = false;
+        }
     }
     return s;
 }
@@ -486,7 +493,7 @@ int read_layout(snk_ctx *c, int layout) {
         c->n <= 4 * (int64_t)c->cus || c->cus <= 0 || c->star_lambda >= 0.0)
         return layout;
     if (c->P.flags & (snk::kFlagExact | snk::kFlagGradI)) return snk::kBufferPlain;
-    const McShape sh = mc_shape(c, c->P.n_rays, layout);
+    const McShape sh = mc_shape(c, c->P.n_rays, layout, INT32_MAX);
     return sh.tile > 0 || sh.wide ? snk::kBufferPlain : layout;
 }
 
@@ -737,7 +744,8 @@ snk_status run_evolve(snk_ctx *c, int32_t n_iter, bool trace, bool standalone = 
         unroll = 1;
     } else {
         // an image that is read from the plain copy by read_layout counts as one in pairs
-        const McShape sh = mc_shape(c, a.p.M, gradi || c->P.dim == 3 ? layout : by_size);
+        const McShape sh = mc_shape(c, a.p.M, gradi || c->P.dim == 3 ? layout : by_size,
+                                    c->repel_kappa > 0.0 ? std::min(n_iter, c->repel_every) : n_iter);
         lanes = sh.lanes;
         unroll = sh.unroll;
         // LDS boxes: whole-wave groups over a buffer layout
