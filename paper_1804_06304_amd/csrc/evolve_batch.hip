@@ -11,7 +11,7 @@ namespace {
 // a.tile_cap voxels for the contour it is running (restaged for each item).
 // FULL: L = 16 and whole passes (full_passes).
 template <int DIM, int G, int U, int LAYOUT, bool PERSISTENT, bool STAGE, bool FULL>
-__global__ __launch_bounds__(G, (waves_asked<DIM, G, U, STAGE, false, FULL>())) void evolve_batch_kernel(BatchArgs a) {
+__global__ __launch_bounds__(G, (waves_asked<DIM, G, U, LAYOUT, STAGE, false, FULL>())) void evolve_batch_kernel(BatchArgs a) {
     static_assert(G >= 64, "batched groups span whole waves");
     extern __shared__ __align__(16) float lds[];
     __shared__ int item_sh;

@@ -1695,18 +1695,20 @@ __host__ __device__ __forceinline__ int sub_lds_floats(int MH) {
     return Grp<G>::CPB * ((draw_floats(G, MH) + 3) & ~3);
 }
 
-// Waves per SIMD asked of the compiler (1: its choice). One pair-point in flight fits 64 vector registers (8
-// waves: a full CU of 4-wave groups holds 8 contours). FULL 3D instances with two in flight and no box: 93
-// registers, 5 waves (98 and 4 waves unasked; lattice 10.6 ms against 10.9). In 2D the compiler's 86 registers
-// (5 waves) are the best: 6 or 7 waves spill nothing but put more contours' footprints in the L2 than it
+// Waves per SIMD asked of the compiler (1: its choice), the most that spill no vector register. One pair-point in
+// flight: 2D 64 registers, 8 waves; 3D 74, 6 waves, and 85 with a box, 5 (at 8 waves up to 38 spilled: 2,000 contours,
+// 128 lanes, 30 iterations with a box 274 us, now 230; 256 lanes 308, now 221). FULL 3D instances with two in flight
+// and no box: 93 registers, 5 waves (98 and 4 waves unasked; lattice 10.6 ms against 10.9). In 2D the compiler's 86
+// registers (5 waves) are the best: 6 or 7 waves spill nothing but put more contours' footprints in the L2 than it
 // holds (8192^2 image 5.1 ms; 7 waves 5.3, 8 waves 6.2; 4 waves, held by LDS, 5.4). Two-wave groups with four
-// in flight: 128 registers, so 8 contours per CU stay resident. With a box the LDS holds 8 contours of
-// two waves per CU, so registers are left alone (109).
-template <int DIM, int G, int U, bool STAGE, bool GRADI, bool FULL>
+// in flight: 2D 114 registers, 4 waves; 3D 163, 3 waves (2,000 contours with a box 279 -> 230 us), but 4 where pairs or
+// quads are gathered without a box, so that 8 contours per CU stay resident: 14 spilled (251 us, 266 at 3 waves). With
+// a box and two in flight the LDS holds 8 contours of two waves per CU, so registers are left alone (109).
+template <int DIM, int G, int U, int LAYOUT, bool STAGE, bool GRADI, bool FULL>
 constexpr int waves_asked() {
     if (G < 64) return 1;
-    if (U == 1) return 8;
-    if (U == 4) return G == 128 ? 4 : 1;
+    if (U == 1) return DIM == 2 ? 8 : (STAGE ? 5 : 6);
+    if (U == 4) return G != 128 ? 1 : (DIM == 2 || (!STAGE && (LAYOUT == kBufferPair || LAYOUT == kBufferQuad)) ? 4 : 3);
     return DIM == 3 && FULL && !STAGE && !GRADI ? 5 : 1;
 }
 
@@ -1715,7 +1717,7 @@ constexpr int waves_asked() {
 // PG: lanes of the workgroup (whole-wave groups: see run_wave).
 template <int DIM, int G, int U, bool TRACE, int LAYOUT, bool EXACT, bool STAGE, bool GRADI, bool FULL,
           int PG = Grp<G>::NT>
-__global__ __launch_bounds__(PG, (waves_asked<DIM, G, U, STAGE, GRADI, FULL>()))
+__global__ __launch_bounds__(PG, (waves_asked<DIM, G, U, LAYOUT, STAGE, GRADI, FULL>()))
 void evolve_kernel(EvolveArgs a) {
     extern __shared__ __align__(16) float lds[];
     if constexpr (G < 64) {
