@@ -1365,7 +1365,7 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
     long base = 0;
     Tile tile;
     tile.valid = false;
-    float retry = 3.0e38f;     // no box fitted a ball this large: not tried again until it has shrunk
+    float retry = 3.0e38f;     // no box fitted a ball this large: not tried again until it has shrunk or moved
     auto axis = [&](int t, int v0, int v1, int v2) {
         const int l = opaque(t) & 3;
         return DIM == 3 && l == 3 ? v2 : (l == 2 ? v1 : v0);
@@ -1465,7 +1465,8 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
                             staged = true;
                             retry = 3.0e38f;
                         } else {
-                            retry = fr.smax - 0.05f;
+                            // 1/20 of the finest voxel smaller, or at another voxel
+                            retry = fr.smax - 0.05f * __builtin_amdgcn_rcpf(fmaxf(inv_h[0], fmaxf(inv_h[1], DIM == 3 ? inv_h[2] : 0.0f)));
                         }
                         anchored();
                     }
@@ -1635,6 +1636,7 @@ __device__ void run_wave(const JobParams &p, Cold<JobParams> cp, DevContour *slo
 #pragma unroll
                 for (int i = 0; i < DIM; ++i) anc[i] += __builtin_amdgcn_readlane((int)k, 1 + i);
                 anchored();
+                retry = 3.0e38f;
                 if ((__builtin_amdgcn_ballot_w64(off_l < rec[1] || off_l > rec[2]) & AXES) != 0) st = SNK_OUT;
             }
         }
