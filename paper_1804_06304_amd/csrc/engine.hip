@@ -180,6 +180,8 @@ struct snk_engine {
 namespace {
 
 void unstage(snk_engine *e);
+void drop_uploads(snk_engine *e, const EJob &j);
+void release_device(snk_engine *e, EJob &j);
 
 snk_status efail(snk_engine *e, snk_status code, const std::string &m) {
     if (e) e->err = m;
@@ -418,39 +420,48 @@ snk_status admit(snk_engine *e, EJob &j) {
     j.d_init = reinterpret_cast<DevContour *>(b + o_init);
     j.d_evox = reinterpret_cast<double *>(b + o_evox);
     j.d_sel = reinterpret_cast<int *>(b + o_sel);
-    if (!j.borrowed)
-        EHIP(e, hipMemcpyAsync(b + o_raw, j.host_raw.data(), j.raw_bytes, hipMemcpyHostToDevice, e->stream));
-    st = put(e, j.d_dirs, j.dirs.data(), j.dirs.size() * 4);
-    if (st == SNK_OK && j.n > 0) st = put(e, j.d_init, j.init.data(), sizeof(DevContour) * j.n, j.d_st);
-    if (st != SNK_OK) return st;
-    j.slot = e->free_slots.back();
-    e->free_slots.pop_back();
-    JobDev d{};
-    d.p = params_of(j);
-    d.st = j.d_st;
-    d.e_vox = j.d_evox;
-    d.n = j.n;
-    d.target = j.n_iter;
-    d.e0 = (float)j.P.e0;
-    d.e_cull = d.e0;
-    d.compete = 1;
-    const size_t G1 = (size_t)j.grid_cells + 1;
-    d.cell_start = j.d_sel;
-    d.items = j.d_sel + 2 * G1;
-    d.cell_of = d.items + n;
-    d.dec = d.cell_of + n;
-    for (int i = 0; i < 3; ++i) d.G[i] = j.G[i];
-    d.cell = (float)j.cell;
-    d.kept = e->d_kept;
-    e->h_jobs[j.slot] = d;
-    e->h_init_ptrs[j.slot] = j.d_init;
-    st = put(e, e->d_jobs + j.slot, &e->h_jobs[j.slot], sizeof(JobDev));
-    if (st == SNK_OK) st = put(e, e->d_init_ptrs + j.slot, &e->h_init_ptrs[j.slot], sizeof(DevContour *));
-    if (st != SNK_OK) return st;
-    e->staged.push_back(&j);
-    j.state = RUNNING;
     j.charged = cap;
     e->in_use += cap;
+    auto enter = [&]() -> snk_status {
+        if (!j.borrowed)
+            EHIP(e, hipMemcpyAsync(b + o_raw, j.host_raw.data(), j.raw_bytes, hipMemcpyHostToDevice, e->stream));
+        snk_status st = put(e, j.d_dirs, j.dirs.data(), j.dirs.size() * 4);
+        if (st == SNK_OK && j.n > 0) st = put(e, j.d_init, j.init.data(), sizeof(DevContour) * j.n, j.d_st);
+        if (st != SNK_OK) return st;
+        j.slot = e->free_slots.back();
+        e->free_slots.pop_back();
+        JobDev d{};
+        d.p = params_of(j);
+        d.st = j.d_st;
+        d.e_vox = j.d_evox;
+        d.n = j.n;
+        d.target = j.n_iter;
+        d.e0 = (float)j.P.e0;
+        d.e_cull = d.e0;
+        d.compete = 1;
+        const size_t G1 = (size_t)j.grid_cells + 1;
+        d.cell_start = j.d_sel;
+        d.items = j.d_sel + 2 * G1;
+        d.cell_of = d.items + n;
+        d.dec = d.cell_of + n;
+        for (int i = 0; i < 3; ++i) d.G[i] = j.G[i];
+        d.cell = (float)j.cell;
+        d.kept = e->d_kept;
+        e->h_jobs[j.slot] = d;
+        e->h_init_ptrs[j.slot] = j.d_init;
+        st = put(e, e->d_jobs + j.slot, &e->h_jobs[j.slot], sizeof(JobDev));
+        if (st == SNK_OK) st = put(e, e->d_init_ptrs + j.slot, &e->h_init_ptrs[j.slot], sizeof(DevContour *));
+        return st;
+    };
+    st = enter();
+    if (st != SNK_OK) {   // still pending: its memory goes back
+        drop_uploads(e, j);
+        (void)hipStreamSynchronize(e->stream);
+        release_device(e, j);
+        return st;
+    }
+    e->staged.push_back(&j);
+    j.state = RUNNING;
     e->admitted += 1;
     return SNK_OK;
 }
@@ -463,6 +474,20 @@ void unstage(snk_engine *e) {
     }
     e->staged.clear();
     e->stage_busy = false;
+}
+
+// Forgets what put() collected for a job's memory and table row (a run or step that ended early leaves it): sent
+// with what their next owner uploads, it could arrive last.
+void drop_uploads(snk_engine *e, const EJob &j) {
+    auto within = [](const void *p, const void *b, size_t bytes) {
+        return b && p >= b && p < static_cast<const char *>(b) + bytes;
+    };
+    auto of_job = [&](const snk::CopyPiece &p) {
+        return within(p.dst, j.block, j.charged) ||
+               (j.slot >= 0 && (p.dst == e->d_jobs + j.slot || p.dst == e->d_init_ptrs + j.slot));
+    };
+    e->up_pieces.erase(std::remove_if(e->up_pieces.begin(), e->up_pieces.end(), of_job), e->up_pieces.end());
+    if (e->up_pieces.empty()) e->up_data.clear();
 }
 
 // Returns a job's device memory and table row; idempotent (a finished job is released when it
@@ -1146,11 +1171,11 @@ snk_status snk_engine_release(snk_engine *e, uint64_t job) {
     auto it = e->jobs.find(job);
     if (it == e->jobs.end()) return efail(e, SNK_EINVAL, "unknown job");
     EJob *j = it->second;
-    snk_status st = flush(e);   // an upload to a released job's memory must not follow its next owner's
-    if (st != SNK_OK) return st;
     if (j->state == PENDING) e->pending.erase(std::find(e->pending.begin(), e->pending.end(), job));
     (void)hipSetDevice(e->device);
+    drop_uploads(e, *j);
     (void)hipStreamSynchronize(e->stream);
+    unstage(e);   // the list names this job when a run or step ended early
     if (j->slot >= 0 || j->block) drop_graph(e);
     release_device(e, *j);
     delete j;
