@@ -334,7 +334,7 @@ snk_status run_prepass(snk_ctx *c) {
     a.Jq = layout == snk::kBufferQuad ? c->Jq : nullptr;
     a.Jp = layout == snk::kBufferPair ? reinterpret_cast<float2 *>(c->Jq) : nullptr;
     HIPTRY(c, hipEventRecord(c->ev[0], c->stream));
-    HIPTRY(c, snk::launch_prepass(a, c->stream));
+    HIPTRY(c, snk::launch_prepass(a, c->cus, c->lds_per_cu, c->stream));
     HIPTRY(c, hipEventRecord(c->ev[1], c->stream));
     c->layout = layout;
     c->ev_pre = true;

@@ -127,7 +127,7 @@ struct snk_engine {
     std::map<uint64_t, EJob *> jobs;     // every job not yet released
     std::deque<uint64_t> pending;        // FIFO of PENDING jobs
     std::vector<uint64_t> done_unpolled;
-    int cus = 256;
+    int cus = 256, lds_per_cu = 0;
 
     // device job table
     JobDev *d_jobs = nullptr;
@@ -570,7 +570,7 @@ PrepassPlan plan_prepass(const snk_engine *e, const std::vector<EJob *> &js) {
         by[k].push_back(r);
     }
     for (auto &g : by) {
-        const int blocks = snk::prepass_plan(g.data(), (int)g.size());
+        const int blocks = snk::prepass_plan(g.data(), (int)g.size(), e->cus, e->lds_per_cu);
         pp.groups.push_back({(int)pp.rows.size(), (int)g.size(), blocks});
         pp.rows.insert(pp.rows.end(), g.begin(), g.end());
     }
@@ -823,6 +823,8 @@ snk_status snk_engine_create(snk_engine **out, int device, void *hip_stream, uin
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
         e->cus = prop.multiProcessorCount;
+    if (hipDeviceGetAttribute(&e->lds_per_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device) != hipSuccess)
+        e->lds_per_cu = 0;
     if (hipEventCreate(&e->ev0) != hipSuccess || hipEventCreate(&e->ev1) != hipSuccess ||
         hipEventCreate(&e->ev2) != hipSuccess || hipMalloc(&e->d_kept, sizeof(unsigned long long)) != hipSuccess) {
         snk_engine_destroy(e);

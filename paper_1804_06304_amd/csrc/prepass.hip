@@ -66,7 +66,7 @@ hipError_t launch_typed(const PrepassJob &one, const PrepassJob *jobs, int n, in
 // A workgroup's chunk of z planes (an image's rows of tiles) takes 2 rz more, so a launch takes as long as its rounds of
 // resident workgroups times chunk + 2 rz: the chunk is the one of the least product, at least rz and 2 planes (411 x 387
 // x 131, sigma 1.6: 5 chunks, one round, 169 us; 6 chunks, a little more than a round, 194; 12 chunks 180).
-int prepass_plan(PrepassJob *jobs, int n) {
+int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu) {
     if (n <= 0) return 0;
     const int ty = 4 * prepass_rows_per_thread(jobs[0].a), tx = jobs[0].a.Jq ? 63 : 64;
     int top = 0;
@@ -79,8 +79,10 @@ int prepass_plan(PrepassJob *jobs, int n) {
         j.cut.len = image ? rows : j.a.nz;
         top = std::max(top, j.cut.len);
     }
-    int slots = 1024;
+    // (a device that did not say: a whole chip's)
+    int slots = lds_per_cu > 0 ? lds_per_cu : 160 * 1024;
     (void)launch_typed(jobs[0], nullptr, 0, 0, nullptr, &slots);
+    slots *= cus > 0 ? cus : 256;
     const int rz = jobs[0].a.rz, least = jobs[0].a.nz == 1 ? 1 : std::max(rz, 2);
     auto groups_of = [](const PrepassJob &j, int chunk) {
         return (long)j.cut.bx * j.cut.by * ((j.cut.len + chunk - 1) / chunk);
@@ -109,10 +111,10 @@ int prepass_plan(PrepassJob *jobs, int n) {
     return first;
 }
 
-hipError_t launch_prepass(const PrepassArgs &a, hipStream_t s) {
+hipError_t launch_prepass(const PrepassArgs &a, int cus, int lds_per_cu, hipStream_t s) {
     PrepassJob one{};
     one.a = a;
-    const int blocks = prepass_plan(&one, 1);
+    const int blocks = prepass_plan(&one, 1, cus, lds_per_cu);
     return launch_typed(one, nullptr, 0, blocks, s, nullptr);
 }
 

@@ -307,15 +307,15 @@ inline int groups_by_registers(const void *kernel) {
     return std::max(1, std::min(8, 512 / ((at.numRegs + 7) & ~7)));
 }
 
-// The planned volume one, or with n > 0 the n of a table of which it is the first. With slots the workgroups that
-// the chip holds, and no launch.
+// The planned volume one, or with n > 0 the n of a table of which it is the first. With slots, the LDS of a CU, the
+// workgroups that a CU holds in its place, and no launch.
 template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND>
 hipError_t launch_k(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s, int *slots) {
     const size_t lds = prepass_lds(ROWS, one.a.rx, one.a.ry, SECOND != 0);
     if (slots) {
         static const int per_cu =
             groups_by_registers(reinterpret_cast<const void *>(&prepass_kernel<T, ROWS, RXY, RB, RZ, ZMAX, SECOND>));
-        *slots = 256 * std::min(per_cu, (int)(160 * 1024 / lds));
+        *slots = std::max(1, std::min(per_cu, (int)((size_t)*slots / lds)));
         return hipSuccess;
     }
     const dim3 grid = n > 0 ? dim3(blocks) : dim3(one.cut.bx, one.cut.by, blocks / (one.cut.bx * one.cut.by));

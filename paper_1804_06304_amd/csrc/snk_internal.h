@@ -224,12 +224,13 @@ struct PrepassJob {
     } cut;
 };
 
-hipError_t launch_prepass(const PrepassArgs &a, hipStream_t s);
+// cus, lds_per_cu: of the device (a partition has fewer CUs), which a launch should fill in whole rounds.
+hipError_t launch_prepass(const PrepassArgs &a, int cus, int lds_per_cu, hipStream_t s);
 int prepass_rows_per_thread(const PrepassArgs &a);
 // Pre-pass of n volumes in one launch: they must agree in prepass_same_launch. prepass_plan fills first and cut and
 // returns the workgroups; host and dev are the same table.
 bool prepass_same_launch(const PrepassArgs &a, const PrepassArgs &b);
-int prepass_plan(PrepassJob *jobs, int n);
+int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu);
 hipError_t launch_prepass_batch(const PrepassJob *host, const PrepassJob *dev, int n, int blocks, hipStream_t s);
 hipError_t launch_prepass_u8(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s,
                               int *slots);
