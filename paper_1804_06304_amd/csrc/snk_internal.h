@@ -121,8 +121,8 @@ __host__ __device__ inline int wave_draw_floats(int dim, int K, int KR, int MH) 
     return (8 * K * MH + KR * (dim == 3 ? 9 : 2) + 3) & ~3;
 }
 // LDS of a whole-wave workgroup of PG lanes: draws, the partial sums of the group's G / 64 waves (two sets of 8
-// floats each) and axis records (32 floats per wave), the box. Up to a few hundred bytes over 64 KiB with
-// the largest box that evolve_lds_accepts takes; a workgroup may have 160 KiB.
+// floats each) and axis records (32 floats per wave), the box. With the largest box that evolve_lds_accepts takes up to
+// 71,040 bytes (102 rays, 128 lanes, 2D), without a box up to 67,072; a workgroup may have 160 KiB.
 inline size_t wave_lds_bytes(int G, int PG, int draw_floats, int tile_cap) {
     return sizeof(float) * ((size_t)draw_floats + (G > 64 ? G / 64 * 16 : 0) + PG / 64 * 32 + (size_t)tile_cap);
 }
