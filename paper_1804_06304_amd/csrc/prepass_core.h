@@ -40,8 +40,8 @@ typedef const __attribute__((address_space(4))) float *TapsPtr;
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
-// f(integral_constant) of a radius known when the kernel runs: 0 .. 8 unrolled, -1 beyond.
-template <int RXY, typename F>
+// f(integral_constant) of a radius known when the kernel runs: 0 .. 8 unrolled, -1 beyond (of kernels that take more).
+template <int RXY, int RB, typename F>
 __device__ __forceinline__ void with_radius(int r, F f) {
     if constexpr (RXY >= 0) {
         f(std::integral_constant<int, RXY>());
@@ -56,22 +56,18 @@ __device__ __forceinline__ void with_radius(int r, F f) {
             case 6: return f(std::integral_constant<int, 6>());
             case 7: return f(std::integral_constant<int, 7>());
             case 8: return f(std::integral_constant<int, 8>());
-            default: return f(std::integral_constant<int, -1>());
+            default:
+                if constexpr (RB > 8) return f(std::integral_constant<int, -1>());
         }
     }
 }
 
-// One value filtered along x: sum over the 2 r + 1 taps, in tap order.
+// One value filtered along x: sum over the 2 R + 1 taps, in tap order.
 template <int R>
-__device__ __forceinline__ float filter_row(TapsPtr g, int r, const float *row) {
+__device__ __forceinline__ float filter_row(TapsPtr g, const float *row) {
     float acc = 0.0f;
-    if constexpr (R >= 0) {
 #pragma unroll
-        for (int k = 0; k <= 2 * R; ++k) acc = fmaf(g[k], row[k], acc);
-    } else {
-#pragma unroll 4
-        for (int k = 0; k <= 2 * r; ++k) acc = fmaf(g[k], row[k], acc);
-    }
+    for (int k = 0; k <= 2 * R; ++k) acc = fmaf(g[k], row[k], acc);
     return acc;
 }
 
@@ -92,6 +88,7 @@ __device__ __forceinline__ void filter_column(TapsPtr g, int r, const float *col
         float c[N];
 #pragma unroll
         for (int i = 0; i + 1 < N; ++i) c[i] = col[i * EX];
+#pragma unroll 4
         for (int k = 0; k <= 2 * r; ++k) {
             c[N - 1] = col[(k + N - 1) * EX];
 #pragma unroll
@@ -193,17 +190,37 @@ __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, 
         }
         __syncthreads();
         fetch(zi + 1);
-        with_radius<RXY>(rx, [&](auto R) {
+        with_radius<RXY, RB>(rx, [&](auto R) {
+            if constexpr (decltype(R)::value >= 0) {
 #pragma unroll
-            for (int i = 0; i < NRA; ++i) {
-                const int r = ty + GROUPS * i;
-                if (r < PH) tmp[r * EX + tx] = filter_row<decltype(R)::value>(a->gx, rx, plane + r * PW + tx);
+                for (int i = 0; i < NRA; ++i) {
+                    const int r = ty + GROUPS * i;
+                    if (r < PH) tmp[r * EX + tx] = filter_row<decltype(R)::value>(a->gx, plane + r * PW + tx);
+                }
+            } else {
+                // the thread's rows side by side: their reads are in flight together (a row past the plane sums its last)
+                float acc[NRA];
+                const float *row[NRA];
+#pragma unroll
+                for (int i = 0; i < NRA; ++i) {
+                    acc[i] = 0.0f;
+                    row[i] = plane + min(ty + GROUPS * i, PH - 1) * PW + tx;
+                }
+#pragma unroll 2
+                for (int k = 0; k <= 2 * rx; ++k) {
+                    const float g = a->gx[k];
+#pragma unroll
+                    for (int i = 0; i < NRA; ++i) acc[i] = fmaf(g, row[i][k], acc[i]);
+                }
+#pragma unroll
+                for (int i = 0; i < NRA; ++i)
+                    if (ty + GROUPS * i < PH) tmp[(ty + GROUPS * i) * EX + tx] = acc[i];
             }
         });
         // the plane is free for the next one's staging, and the filtered rows until the barrier after that
         __syncthreads();
         float v[EV];
-        with_radius<RXY>(ry, [&](auto R) {
+        with_radius<RXY, RB>(ry, [&](auto R) {
             filter_column<decltype(R)::value, EV>(a->gy, ry, tmp + ty * ROWS * EX + tx, v);
         });
 #pragma unroll
