@@ -63,9 +63,12 @@ hipError_t launch_typed(const PrepassJob &one, const PrepassJob *jobs, int n, in
 }
 }  // namespace
 
-// A workgroup's chunk of z planes (an image's rows of tiles) takes 2 rz more, so a launch takes as long as its rounds of
-// resident workgroups times chunk + 2 rz: the chunk is the one of the least product, at least rz and 2 planes (411 x 387
-// x 131, sigma 1.6: 5 chunks, one round, 169 us; 6 chunks, a little more than a round, 194; 12 chunks 180).
+// A workgroup's chunk of z planes (an image's rows of tiles) takes 2 rz more to fill its ring, so small chunks are more
+// work, and large ones leave the chip idle. A plane takes a CU some 6 + w units with w workgroups on it (512 x 512
+// planes, radius 3: 1.35 us alone, 2.1 with two, 3.6 with six), so the chunk is the one of least (chunk + 2 rz + 2) times
+// that, summed over the rounds of resident workgroups (411 x 387 x 131, sigma 1.6: 5 chunks, one round, 139 us; 6
+// chunks, a little more than a round, 164; 64^3, sigma 1.6 / 3 / 5.3: chunks of 5 / 9 / 16 planes 41 / 135 / 397 us, of
+// 1 / 2 / 2 31 / 101 / 275).
 int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu) {
     if (n <= 0) return 0;
     const int ty = 4 * prepass_rows_per_thread(jobs[0].a), tx = jobs[0].a.Jq ? 63 : 64;
@@ -73,32 +76,38 @@ int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu) {
     for (int i = 0; i < n; ++i) {
         PrepassJob &j = jobs[i];
         const int rows = (j.a.ny + ty - 1) / ty;
-        const bool image = j.a.nz == 1 && !j.a.Jq;   // marched over by rows of tiles
+        const bool march = j.a.nz == 1 && !j.a.Jq;
         j.cut.bx = (j.a.nx + tx - 1) / tx;
-        j.cut.by = image ? 1 : rows;
-        j.cut.len = image ? rows : j.a.nz;
+        j.cut.by = march ? 1 : rows;
+        j.cut.len = march ? rows : j.a.nz;
         top = std::max(top, j.cut.len);
     }
     // (a device that did not say: a whole chip's)
-    int slots = lds_per_cu > 0 ? lds_per_cu : 160 * 1024;
-    (void)launch_typed(jobs[0], nullptr, 0, 0, nullptr, &slots);
-    slots *= cus > 0 ? cus : 256;
-    const int rz = jobs[0].a.rz, least = jobs[0].a.nz == 1 ? 1 : std::max(rz, 2);
+    if (cus <= 0) cus = 256;
+    int per_cu = lds_per_cu > 0 ? lds_per_cu : 160 * 1024;
+    (void)launch_typed(jobs[0], nullptr, 0, 0, nullptr, &per_cu);
+    const long slots = (long)per_cu * cus;
+    const int rz = jobs[0].a.rz;
     auto groups_of = [](const PrepassJob &j, int chunk) {
         return (long)j.cut.bx * j.cut.by * ((j.cut.len + chunk - 1) / chunk);
     };
     int chunk = top;
-    long best = 0;
-    for (int c = 1; c <= top; ++c) {
-        const int z = std::max((top + c - 1) / c, least);
+    double best = 0.0;
+    // (the chunk lengths that cut `top` evenly, longest first; the stream may be idle meanwhile)
+    for (int z = top;;) {
         long groups = 0;
         for (int i = 0; i < n; ++i) groups += groups_of(jobs[i], z);
-        const long cost = (groups + slots - 1) / slots * (z + 2 * rz);
-        if (c == 1 || cost < best) {
+        const long rest = groups % slots;
+        const double round = (double)(groups / slots) * (6.0 + per_cu) +
+                             (rest ? 6.0 + std::max(1.0, (double)rest / cus) : 0.0);
+        const double cost = round * (z + 2 * rz + 2);
+        if (z == top || cost < best) {
             best = cost;
             chunk = z;
         }
-        if (z == least || groups > 4l * slots) break;
+        if (z == 1 || groups > 4 * slots) break;
+        const int c = (top + z - 2) / (z - 1);   // the fewest chunks of less than z
+        z = (top + c - 1) / c;
     }
     int first = 0;
     for (int i = 0; i < n; ++i) {
