@@ -63,12 +63,22 @@ hipError_t launch_typed(const PrepassJob &one, const PrepassJob *jobs, int n, in
 }
 }  // namespace
 
+// Whether workgroups march down an image's rows of tiles (prepass_tile): by chunks of six, for all but 32-bit images
+// written in pairs by the kernel of radius 3, bound by memory (march, a tile each: 8,192^2 u8, sigma 0 / 1 / 3: 111 / 108
+// / 419 us, 171 / 155 / 476; 60,000 x 64 15 / 14 / 38, 17 / 16 / 38; pairs, sigma 1: 8,192^2 u8 210, 248, f32 234, 231;
+// 4,096^2 u8 49, 51, f32 62, 51).
+bool prepass_marches(const PrepassArgs &a) {
+    return a.nz == 1 && !a.Jq && !(a.Jp && a.dtype == SNK_F32 && a.rx == 3 && a.ry == 3);
+}
+
 // A workgroup's chunk of z planes (an image's rows of tiles) takes 2 rz more to fill its ring, so small chunks are more
 // work, and large ones leave the chip idle. A plane takes a CU some 6 + w units with w workgroups on it (512 x 512
 // planes, radius 3: 1.35 us alone, 2.1 with two, 3.6 with six), so the chunk is the one of least (chunk + 2 rz + 2) times
 // that, summed over the rounds of resident workgroups (411 x 387 x 131, sigma 1.6: 5 chunks, one round, 139 us; 6
 // chunks, a little more than a round, 164; 64^3, sigma 1.6 / 3 / 5.3: chunks of 5 / 9 / 16 planes 41 / 135 / 397 us, of
-// 1 / 2 / 2 31 / 101 / 275).
+// 1 / 2 / 2 31 / 101 / 275). Where no ring is to be filled chunks are short, and several rounds even out (at most 6:
+// 8,192^2 u8, sigma 1, 32 rows of tiles 122 us, 6 103; u16 with pairs, sigma 1.6, 37 rows 310, 6 259; 512 x 512 x 128
+// unsmoothed with quads, 22 planes 160, 6 145).
 int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu) {
     if (n <= 0) return 0;
     const int ty = 4 * prepass_rows_per_thread(jobs[0].a), tx = jobs[0].a.Jq ? 63 : 64;
@@ -76,7 +86,7 @@ int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu) {
     for (int i = 0; i < n; ++i) {
         PrepassJob &j = jobs[i];
         const int rows = (j.a.ny + ty - 1) / ty;
-        const bool march = j.a.nz == 1 && !j.a.Jq;
+        const bool march = prepass_marches(j.a);
         j.cut.bx = (j.a.nx + tx - 1) / tx;
         j.cut.by = march ? 1 : rows;
         j.cut.len = march ? rows : j.a.nz;
@@ -109,6 +119,7 @@ int prepass_plan(PrepassJob *jobs, int n, int cus, int lds_per_cu) {
         const int c = (top + z - 2) / (z - 1);   // the fewest chunks of less than z
         z = (top + c - 1) / c;
     }
+    if (rz == 0) chunk = std::min(chunk, std::max(6, (top + 65534) / 65535));   // (a grid has 65,535 chunks)
     int first = 0;
     for (int i = 0; i < n; ++i) {
         PrepassJob &j = jobs[i];
@@ -128,7 +139,8 @@ hipError_t launch_prepass(const PrepassArgs &a, int cus, int lds_per_cu, hipStre
 }
 
 bool prepass_same_launch(const PrepassArgs &a, const PrepassArgs &b) {
-    return a.dtype == b.dtype && a.rx == b.rx && a.ry == b.ry && a.rz == b.rz && !a.Jq == !b.Jq && !a.Jp == !b.Jp;
+    return a.dtype == b.dtype && a.rx == b.rx && a.ry == b.ry && a.rz == b.rz && !a.Jq == !b.Jq && !a.Jp == !b.Jp &&
+           prepass_marches(a) == prepass_marches(b);
 }
 
 hipError_t launch_prepass_batch(const PrepassJob *host, const PrepassJob *dev, int n, int blocks, hipStream_t s) {

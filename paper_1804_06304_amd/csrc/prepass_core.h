@@ -118,10 +118,10 @@ constexpr int rows_evaluated() {
     return ROWS + (SECOND ? 1 : 0);
 }
 
-// Tile (bx, by) of the planes z0 .. z1 - 1 of volume a; of an image (nz = 1) without quad records the tiles (bx, z0 ..
-// z1 - 1), which a workgroup marches over as it does over planes, its next loads in flight (8192^2 u8 alone 154 -> 127
-// us; with quad records 4096^2 71 -> 91, their rows fall on the same channels).
-template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND>
+// Tile (bx, by) of the planes z0 .. z1 - 1 of volume a; with MARCH, of an image (nz = 1) the tiles (bx, z0 .. z1 - 1),
+// which a workgroup marches over as it does over planes, its next loads in flight (8192^2 u8 alone 154 -> 127
+// us, 103 by chunks of six; never with quad records, 4096^2 71 -> 91, whose rows fall on the same channels).
+template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND, bool MARCH>
 __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, int z1, float *lds) {
     constexpr int EV = rows_evaluated<ROWS, SECOND>();
     constexpr int TX = tile_columns<SECOND>();
@@ -149,9 +149,8 @@ __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, 
     const int tx = t & (EX - 1);
     const int ty = __builtin_amdgcn_readfirstlane(t >> 6);   // row group: one wave
     const long nxy = (long)nx * ny;
-    const bool down = RZ == 0 && !ZMAX && SECOND != 1 && nz == 1;
-    auto plane_of = [&](int zi) { return down ? 0 : zi; };
-    auto first_row = [&](int zi) { return down ? zi * TY : y0; };
+    auto plane_of = [&](int zi) { return MARCH ? 0 : zi; };
+    auto first_row = [&](int zi) { return MARCH ? zi * TY : y0; };
     const T *raw = static_cast<const T *>(a->raw);
     const float off = a->i_offset, scale = a->i_scale;
 
@@ -288,7 +287,7 @@ size_t prepass_lds(int rows, int rx, int ry, bool second) {
 
 // Workgroup b of a table belongs to the volume whose `first` is the last at or below b; without a table there is
 // one volume, the first argument, read where the launch put it, and the grid is its cut.
-template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND>
+template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND, bool MARCH>
 __global__ __launch_bounds__(NT) void prepass_kernel(PrepassJob one, const PrepassJob *jobs, int n) {
     extern __shared__ float lds[];
     typedef const __attribute__((address_space(4))) PrepassJob *JobPtr;
@@ -310,7 +309,7 @@ __global__ __launch_bounds__(NT) void prepass_kernel(PrepassJob one, const Prepa
         bz = k / j->cut.bx / j->cut.by;
     }
     const int z0 = bz * j->cut.chunk;
-    prepass_tile<T, ROWS, RXY, RB, RZ, ZMAX, SECOND>(&j->a, bx, by, z0, min(j->cut.len, z0 + j->cut.chunk), lds);
+    prepass_tile<T, ROWS, RXY, RB, RZ, ZMAX, SECOND, MARCH>(&j->a, bx, by, z0, min(j->cut.len, z0 + j->cut.chunk), lds);
 }
 
 // Workgroups of a kernel that a CU holds, by its registers: a workgroup is one wave on each SIMD, which has 512
@@ -326,22 +325,26 @@ inline int groups_by_registers(const void *kernel) {
 
 // The planned volume one, or with n > 0 the n of a table of which it is the first. With slots, the LDS of a CU, the
 // workgroups that a CU holds in its place, and no launch.
-template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND>
+template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND, bool MARCH = false>
 hipError_t launch_k(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s, int *slots) {
     const size_t lds = prepass_lds(ROWS, one.a.rx, one.a.ry, SECOND != 0);
     if (slots) {
         static const int per_cu =
-            groups_by_registers(reinterpret_cast<const void *>(&prepass_kernel<T, ROWS, RXY, RB, RZ, ZMAX, SECOND>));
+            groups_by_registers(reinterpret_cast<const void *>(&prepass_kernel<T, ROWS, RXY, RB, RZ, ZMAX, SECOND, MARCH>));
         *slots = std::max(1, std::min(per_cu, (int)((size_t)*slots / lds)));
         return hipSuccess;
     }
     const dim3 grid = n > 0 ? dim3(blocks) : dim3(one.cut.bx, one.cut.by, blocks / (one.cut.bx * one.cut.by));
-    hipLaunchKernelGGL((prepass_kernel<T, ROWS, RXY, RB, RZ, ZMAX, SECOND>), grid, dim3(NT), lds, s, one, jobs, n);
+    hipLaunchKernelGGL((prepass_kernel<T, ROWS, RXY, RB, RZ, ZMAX, SECOND, MARCH>), grid, dim3(NT), lds, s, one, jobs, n);
     return hipGetLastError();
 }
 
 template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX = false>
 hipError_t launch_s(const PrepassJob &one, const PrepassJob *jobs, int n, int blocks, hipStream_t s, int *slots) {
+    if constexpr (RZ == 0)
+        if (prepass_marches(one.a))
+            return one.a.Jp ? launch_k<T, ROWS, RXY, RB, RZ, ZMAX, 2, true>(one, jobs, n, blocks, s, slots)
+                            : launch_k<T, ROWS, RXY, RB, RZ, ZMAX, 0, true>(one, jobs, n, blocks, s, slots);
     if (one.a.Jq) return launch_k<T, ROWS, RXY, RB, RZ, ZMAX, 1>(one, jobs, n, blocks, s, slots);
     if (one.a.Jp) return launch_k<T, ROWS, RXY, RB, RZ, ZMAX, 2>(one, jobs, n, blocks, s, slots);
     return launch_k<T, ROWS, RXY, RB, RZ, ZMAX, 0>(one, jobs, n, blocks, s, slots);

@@ -214,7 +214,7 @@ struct PrepassArgs {
 
 constexpr int kPrepassMaxR = 16;
 
-// One volume of a launch: cut into bx x by tiles and chunks of its len planes (an image without quad records:
+// One volume of a launch: cut into bx x by tiles and chunks of its len planes (an image that workgroups march down:
 // bx x 1 and chunks of its len rows of tiles), its first workgroup.
 struct PrepassJob {
     PrepassArgs a;
@@ -227,6 +227,7 @@ struct PrepassJob {
 // cus, lds_per_cu: of the device (a partition has fewer CUs), which a launch should fill in whole rounds.
 hipError_t launch_prepass(const PrepassArgs &a, int cus, int lds_per_cu, hipStream_t s);
 int prepass_rows_per_thread(const PrepassArgs &a);
+bool prepass_marches(const PrepassArgs &a);   // down the rows of an image's tiles
 // Pre-pass of n volumes in one launch: they must agree in prepass_same_launch. prepass_plan fills first and cut and
 // returns the workgroups; host and dev are the same table.
 bool prepass_same_launch(const PrepassArgs &a, const PrepassArgs &b);

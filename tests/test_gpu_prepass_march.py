@@ -1,5 +1,5 @@
-"""The pre-pass of images with more rows of tiles than the chip holds workgroups, where a workgroup marches down several
-of them, its next tile's loads in flight: odd sizes that no tile and no chunk divides, against the FP64 oracle and, for
+"""The pre-pass of images whose workgroups march down several rows of tiles, the next tile's loads in flight (up to six rows,
+where there are more tiles than the chip holds workgroups): odd sizes that no tile and no chunk divides, against the FP64 oracle and, for
 the column pairs, the bits that evolve to. Quad records are not marched. Bound of |J - oracle| as in the test of the
 tiles' edges: an axis of radius r rounds 2 r + 1 products and their taps, the intensity map twice.
 """
@@ -33,8 +33,7 @@ def _run(p, raw, layout, cen):
     return J, st
 
 
-# tiles are 64 columns by 16 rows and the chip holds at most 2,048 workgroups: 65 x 257 tiles (9 rows a workgroup), 17 x
-# 376, 3 x 2,050; radii 3 (its own kernel), 6, 9 (of the largest kernel), 1 and 0
+# tiles are 64 columns by 16 rows, and a workgroup takes up to 6 rows of them: 65 x 257 tiles, 17 x 376, 3 x 2,050; radii 3 (its own kernel), 6, 9 (of the largest kernel), 1 and 0
 @pytest.mark.parametrize("ny,nx,dtype,sigma", [(4099, 4111, np.uint8, 1.0), (6011, 1037, np.uint16, 2.0),
                                                (4099, 4111, np.float32, 0.3), (32797, 131, np.uint8, 3.0),
                                                (4100, 4090, np.uint16, 0.0)])
@@ -55,3 +54,11 @@ def test_marching(orc, ny, nx, dtype, sigma):
         first = first or st
         for k in st:
             assert np.array_equal(st[k], first[k], equal_nan=True), k
+
+
+def test_more_rows_of_chunks_than_a_grid_has(orc):
+    ny, nx = 7_000_003, 2
+    raw = np.random.default_rng(1).uniform(0.0, 250.0, (1, ny, nx)).astype(np.uint8)
+    p = synth.Params(dim=2, sigma_pre=1.0, dR=0.8, r_max=8.0, r_init=4.0, n_rays=16, n_dirs=64)
+    J, _ = _run(p, raw, 0, np.array([[0.5, 3.5e6, 0.0]]))
+    assert np.max(np.abs(J - orc.prepass(raw, p))) <= (3 * 8 + 2) * 2.0 ** -24 * raw.max()
