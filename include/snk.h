@@ -153,8 +153,11 @@ snk_status snk_set_launch(snk_ctx *ctx, int32_t lanes_per_contour, int32_t pairs
  * keeps a box of the smoothed volume around its sample ball (Sec. II-E) in on-chip memory, staged
  * with a margin and re-staged only when the ball leaves it, and reads the trilinear corners of its
  * samples from there. tile_voxels = -1: automatic (none with four or fewer contours per
- * compute unit, whose footprints fit the L2; above, the largest capacity that keeps all contours
- * resident or, where they are more than can be, as many as registers allow), 0: off (every corner read from the volume), 1..16384: capacity in
+ * compute unit, whose footprints fit the L2, or with fewer than 128 pair-points an iteration; above,
+ * the largest capacity that keeps all contours resident or, where they are more than can be (two or
+ * more waves per contour in 3D, 2D), as many as registers allow; of those, none in 3D for calls of
+ * fewer than 16 iterations, and none in 2D over column pairs that fit the L2 or when the mean seed's
+ * disk does not fit the box), 0: off (every corner read from the volume), 1..16384: capacity in
  * voxels (4 bytes each). An iteration whose ball does not fit, or
  * reaches the volume's edge, reads the volume. Results are bit-identical with and without the box.
  * SNK_EINVAL if tile_voxels is out of range, or at the next evolve if the box and the kernel's other
@@ -218,9 +221,9 @@ snk_status snk_load_seeds(snk_ctx *ctx, const double *centers, const float *r0, 
 
 /* Run up to n_iter further iterations of every SNK_ACTIVE contour (Eqs. (7)-(15) with
  * Monte-Carlo sums, Sec. II-E); each contour continues its own iteration counter, so
- * evolve(a) then evolve(b) equals evolve(a + b). Runs the pre-pass first if needed. With 64 or
- * more iterations (and no per-iteration trace) the iterations are enqueued as two kernel launches
- * of about half each, which only changes how the still-active contours are spread over the CUs. */
+ * evolve(a) then evolve(b) equals evolve(a + b). Runs the pre-pass first if needed. In 3D, 256 or
+ * more iterations are enqueued as two kernel launches of about half each, which only changes how
+ * the still-active contours are spread over the CUs. */
 snk_status snk_evolve(snk_ctx *ctx, int32_t n_iter);
 
 /* End of evolution (Results): contours still ACTIVE become SNK_MAXITER; compute the exact

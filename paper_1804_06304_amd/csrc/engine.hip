@@ -309,7 +309,9 @@ size_t footprint(const EJob &j, int64_t grid_cells) {
     b += align256(j.dirs.size() * 4);
     b += 2 * align256((size_t)std::max(j.n, 1) * sizeof(DevContour));
     b += align256((size_t)std::max(j.n, 1) * 8);               // e_vox
-    b += align256(((size_t)grid_cells + 1) * 2 * 4 + (size_t)std::max(j.n, 1) * 3 * 4);   // selection
+    // selection: a chain head per cell, the items' chains, cells and decisions. (As much again as the heads stays
+    // unused, so that a budget admits the jobs that it did when the cells had fill counts.)
+    b += align256(((size_t)grid_cells + 1) * 2 * 4 + (size_t)std::max(j.n, 1) * 3 * 4);
     return b;
 }
 

@@ -7,16 +7,16 @@
 // Per input plane: stage the plane with its x/y halo in LDS from registers that were fetched while the
 // previous plane was filtered; barrier; filter along x into LDS; barrier; then every thread filters its own
 // ROWS neighbouring rows of one column along y (from the 2 ry + ROWS values they share) and z (a ring of
-// 2 rz + 1 planes of its own rows, in its registers), and stores J and the second copy. A column pair's lower row is a row that the thread evaluates too (one more than it stores); a
-// quad record's +x values come from the next lane, so tiles are 63 columns wide there and 64, whole cache
-// lines, otherwise.
+// 2 rz + 1 planes of its own rows, in its registers), and stores J and the second copy. A column pair's lower row
+// is a row that the thread evaluates too (one more than it stores); a quad record's +x values come from the next
+// lane, so tiles are 63 columns wide there and 64, whole cache lines, otherwise.
 //
 // Small radii are bound by HBM (raw read, 4 B of J and 8 B of pairs or 16 B of quads per voxel), larger ones by
 // the latency of a plane's two barriers and LDS reads. A thread's rows lie next to each other because they share
 // their column's values, the ring is in registers because LDS rings left two workgroups on a CU, and nothing is
 // read back to find a neighbour. Against rows 4 apart, their ring in LDS and the filtered plane exchanged through
-// it (J of 411 x 387 x 131 f32, sigma 1.6: 289 -> 150 us; 384 x 384 x 96 u8 with pairs, sigma 1 / 1.6 / 2.6 / 5.3:
-// 86 / 394 / 440 / 585 -> 65 / 107 / 202 / 426 us; 4096^2 u8 alone, sigma 1 / 1.6: 54 / 152 -> 52 / 73 us).
+// it (411 x 387 x 131 f32 with pairs, sigma 1.6: 460 -> 148 us; 384 x 384 x 96 u8 with pairs, sigma 1 / 1.6 / 2.6 /
+// 5.3: 80 / 388 / 430 / 1,889 -> 56 / 96 / 195 / 953 us; 4096^2 u8 alone, sigma 1 / 1.6: 44 / 135 -> 35 / 52 us).
 // Sums kept per output instead of a ring (no moves) measured the same: the moves are hidden.
 #pragma once
 
@@ -119,8 +119,8 @@ constexpr int rows_evaluated() {
 }
 
 // Tile (bx, by) of the planes z0 .. z1 - 1 of volume a; with MARCH, of an image (nz = 1) the tiles (bx, z0 .. z1 - 1),
-// which a workgroup marches over as it does over planes, its next loads in flight (8192^2 u8 alone 154 -> 127
-// us, 103 by chunks of six; never with quad records, 4096^2 71 -> 91, whose rows fall on the same channels).
+// which a workgroup marches over as it does over planes, its next loads in flight (8192^2 u8 alone 155 -> 127
+// us, 106 by chunks of six; never with quad records, 4096^2 71 -> 91, whose rows fall on the same channels).
 template <typename T, int ROWS, int RXY, int RB, int RZ, bool ZMAX, int SECOND, bool MARCH>
 __device__ __forceinline__ void prepass_tile(ArgsPtr a, int bx, int by, int z0, int z1, float *lds) {
     constexpr int EV = rows_evaluated<ROWS, SECOND>();

@@ -130,7 +130,8 @@ inline size_t wave_lds_bytes(int G, int PG, int draw_floats, int tile_cap) {
 // MH / 64 per iteration), of those that take 8 KiB at most; KR: the rotations of as many iterations as save
 // most of a pass: 64 in 2D, 32 in 3D; 8 in 3D with a box, where their 36 bytes each compete with it (32 save 19
 // instructions of 546 per iteration, but the 864 bytes are 216 voxels, and 4,432 hold balls that 4,224 do
-// not: slab 2.20 ms against 2.36).
+// not: slab 2.20 ms against 2.36, 2,000 balls of R 6.9 445 us against 487; where both hold them 32 is better by
+// 1 to 2.4%: 8,000 balls of R 5 1,046 us against 1,075, of R 6.3 1,111 against 1,138).
 inline DrawPlan draw_plan(int dim, int MH, bool box) {
     DrawPlan d{2, 2};
     double best = 1e30;
