@@ -155,8 +155,8 @@ snk_status snk_set_launch(snk_ctx *ctx, int32_t lanes_per_contour, int32_t pairs
  * samples from there. tile_voxels = -1: automatic (none with four or fewer contours per
  * compute unit, whose footprints fit the L2, or with fewer than 128 pair-points an iteration; above,
  * the largest capacity that keeps all contours resident or, where they are more than can be (two or
- * more waves per contour in 3D, 2D), as many as registers allow; of those, none in 3D for calls of
- * fewer than 16 iterations, and none in 2D over column pairs that fit the L2 or when the mean seed's
+ * more waves per contour in 3D, 2D), as many as registers allow; of those, none in 3D for launches
+ * too short to repay the staging (at most 15 iterations), and none in 2D over column pairs that fit the L2 or when the mean seed's
  * disk does not fit the box), 0: off (every corner read from the volume), 1..16384: capacity in
  * voxels (4 bytes each). An iteration whose ball does not fit, or
  * reaches the volume's edge, reads the volume. Results are bit-identical with and without the box.

@@ -413,9 +413,12 @@ int sum_lanes(const snk_ctx *c, int M, int layout) {
 // -> 7.8 ms. Balls that do not, as four: gathering from the volume, two waves' 8 contours a CU overflow the L2
 // where four waves' 4 do not, whose box is larger too (60 iterations, no box, two waves, four waves: 8,000 balls of R
 // 6.3 1,367, 1,092, - us; R 8.2 1,931, 2,639, 1,327; R 10.1 3,170, 4,008, 2,745; R 15.1 6,494, 7,017, 5,778).
-// Launches of fewer than 16 iterations do not repay the staging there, least of all a run's first, whose steps are the
-// largest (a run of 5, 12, 25 iterations, no box -> box: 6,000 balls of R 6.3, 32 rays 98 -> 119, 143 -> 182, 288 -> 294
-// us, 64 rays 107 -> 140, 213 -> 242, 441 -> 454; balls that do not fit stage nothing).
+// Short launches do not repay the staging there: fewer than 16 iterations, down to 2,200 pair-points of a contour in
+// all with so many contours per CU that other groups hide its latency (no box -> box of a lattice on 512 x 512 x 128
+// after 24 iterations, 64 rays, 5 / 8 / 12 iterations: 12 per CU 37 -> 42, 47 -> 50, 63 -> 64 us; 47 per CU 93 -> 98,
+// 130 -> 119, 179 -> 155; 244 per CU 397 -> 356, 570 -> 475, 793 -> 641; 32 rays, 244 per CU 358 -> 391, 382 -> 381,
+// 495 -> 478; worse in a run's first launches, whose steps are the largest: 6,000 balls of R 6.3, 32 rays, 12
+// iterations 143 -> 182). Balls that do not fit stage nothing.
 // In 2D over pairs, which gather as fast while they fit the L2, no box that the disks do not fit, and for groups of two
 // or four waves none where the pairs take less than 3 MiB of an XCD's L2 (60 iterations, pairs -> box: 38,000 disks of R
 // 8.5, 32 rays, 64 rays 1,672 -> 1,649, 3,285 -> 3,523 us; 6,900 of R 19.8 400 -> 362, 725 -> 711; one wave, 16
@@ -476,7 +479,8 @@ McShape mc_shape(snk_ctx *c, int M, int layout, int32_t iters) {
             snk::full_passes(256, 2, M, c->P.n_radial))
             box(blocks(128), true);
         if (!s.two_waves || ball > (double)s.tile) box(blocks(G), false);
-        if (iters < 16 && ball <= (double)s.tile) {
+        const double points = (double)iters * (M / 2) * c->P.n_radial;
+        if (iters < 16 && points < 2200.0 * (1.0 + 30.0 / (double)per_cu) && ball <= (double)s.tile) {
             s.tile = 0;
             s.two_waves = false;
         }

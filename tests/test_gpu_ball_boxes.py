@@ -51,7 +51,7 @@ def test_box_of_256_lanes(R, M, least, most):
 
 @pytest.mark.parametrize("R,M,n,iters,box", [(6.0, 64, 2600, 15, False), (6.0, 64, 2600, 16, True), (8.0, 64, 2600, 5, False),
                                              (14.0, 64, 2600, 5, True), (6.0, 32, 5200, 15, False), (6.0, 32, 5200, 16, True),
-                                             (6.0, 64, 2000, 5, True)])
+                                             (6.0, 64, 2000, 5, True), (6.0, 64, 16000, 6, False), (6.0, 64, 16000, 7, True)])
 def test_short_launches_take_no_box(R, M, n, iters, box):
     """More contours than can be resident, launches too short to repay the staging; balls beyond the box stage nothing."""
     t, out = _run(R, M, iters=iters, n=n)
