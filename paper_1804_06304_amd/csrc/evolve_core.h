@@ -1294,8 +1294,8 @@ __device__ void run_group(const JobParams &p, DevContour *slot, int n_iter, floa
 //   - the draws: see WaveDraws.
 // Vector instructions per wave and iteration, before -> now, and the evolve's time: slab (3D, two waves, 512
 // pair-points, boxes) 748 -> 546, 2.70 -> 2.34 ms (2.20 with the box's present size); 8192^2 image (one wave, 128
-// pair-points) 280 -> 231, 5.1 -> 4.2 ms; 62,500 lattice contours (four waves' work) 456 -> 323, 10.6 -> 9.1 ms,
-// and 7.8 ms by two waves with boxes.
+// pair-points, from pairs) 280 -> 231, 5.1 -> 4.2 ms (248 from boxes, which spare the pre-pass the pairs); 62,500
+// lattice contours (four waves' work) 456 -> 323, 10.6 -> 9.1 ms, and 7.8 ms by two waves with boxes.
 //
 // STAGE: iterations whose ball fits a box of tile_cap voxels read their corners from an LDS box, the others
 // from the volume in LAYOUT. lds: draws, the waves' partial sums, the box.
