@@ -509,7 +509,18 @@ snk_status ensure_layout(snk_ctx *c) {
     const int layout = read_layout(c, by_size);
     // (pairs are kept for a later evolve that reads them: the plain copy is there too)
     if (layout == c->layout || (layout != by_size && c->layout == by_size)) return SNK_OK;
+    // pairs that nobody asked for are a matter of speed: where no memory may be allocated (a stream under capture) or
+    // there is none, the plain copy serves
+    const bool optional = c->layout_req == 0 && layout == snk::kBufferPair && c->layout == snk::kBufferPlain;
+    if (optional && 2 * c->Jq_cap < (size_t)(c->nx * c->ny * c->nz)) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return SNK_OK;
+    }
     snk_status st = ensure_layout_buffer(c, layout);
+    if (st == SNK_ENOMEM && optional) {
+        (void)hipGetLastError();
+        return SNK_OK;
+    }
     if (st != SNK_OK) return st;
     if (layout == snk::kBufferQuad)
         HIPTRY(c, snk::launch_pack_quad(c->J, c->Jq, (int)c->nx, (int)c->ny, (int)c->nz, c->stream));
